@@ -153,9 +153,12 @@ int cg_create(const cg_csr *A, const cg_opts *opts, void *hip_stream, cg_ctx **o
  * alias b.  Stops when the recurrence residual satisfies ||r|| <= tol ||b||
  * and the true residual b - A x confirms it (otherwise r is replaced by the
  * true residual and the loop continues).  maxit <= 0 means n.  ||b|| = 0
- * gives x = 0 and 0 iterations.  Iterations run as two kernels each,
- * launched in hipGraph chunks; every scalar stays on the device.  The call
- * synchronises the context's stream.
+ * gives x = 0 and 0 iterations.  Every scalar stays on the device.  A system of
+ * at most 262144 rows of at most 28 nonzeros, created without a launch shape in
+ * its options, is solved by one kernel that holds the matrix in registers (such
+ * solves on one device, and batched ones, wait for each other); otherwise
+ * iterations run as kernels launched in hipGraph chunks.  The call synchronises
+ * the context's stream.
  * info may be NULL.  Returns the status (>= 0) or an API error (< 0).
  */
 int cg_solve(cg_ctx *ctx, const double *b, double *x, double tol, int32_t maxit, cg_info *info);

@@ -20,6 +20,7 @@
 #include <vector>
 
 #include "context.hpp"
+#include "resident_host.hpp"
 
 namespace jpcg {
 
@@ -109,6 +110,7 @@ constexpr int kBatchBS = 256;
 
 struct cg_batch {
     hipStream_t stream = nullptr;
+    int device = 0;
     int nsys = 0;
     int64_t n_total = 0;
     int64_t nnz_total = 0;
@@ -329,6 +331,7 @@ int cg_batch_create(int32_t nsys, const cg_csr* systems, const cg_opts* opts, vo
         // many waves in flight as fit.
         int dev = 0, cus = 0, per_cu = 0, wall_khz = 0;
         JPCG_HIP(hipGetDevice(&dev));
+        b->device = dev;
         JPCG_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
         JPCG_HIP(hipDeviceGetAttribute(&wall_khz, hipDeviceAttributeWallClockRate, dev));
         JPCG_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, batch_kernel(b->npl), kBatchBS, 0));
@@ -472,6 +475,8 @@ int cg_batch_solve(cg_batch* b, const double* b_cat, double* x_cat, double tol, 
         JPCG_HIP(hipEventRecord(b->ev0, st));
         JPCG_HIP(hipMemcpyAsync((void*)b->args.b, b_cat, vb, hipMemcpyDeviceToDevice, st));
         JPCG_HIP(hipMemcpyAsync(b->args.x, x_cat, vb, hipMemcpyDeviceToDevice, st));
+        // Teams wait for their workgroups: one such launch per device at a time.
+        std::lock_guard<std::mutex> lock(resident_mutex(b->device));
         JPCG_HIP(hipGraphLaunch(b->exec, st));
         JPCG_HIP(hipMemcpyAsync(x_cat, b->args.x, vb, hipMemcpyDeviceToDevice, st));
         JPCG_HIP(hipEventRecord(b->ev1, st));

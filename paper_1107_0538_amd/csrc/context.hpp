@@ -47,6 +47,7 @@ struct cg_ctx {
     struct cg_graphs* graphs_m32 = nullptr;  // standard form FP64 with the FP32 matrix stream
     void* mixed_dev = nullptr;
     void* mixed_host = nullptr;
+    struct cg_resident* resident = nullptr;  // the on-chip solver, where the system fits it
     struct cg_spmv_plan* spmv = nullptr;     // the standalone product's tiling and grid
     struct cg_multi* multi = nullptr;        // multi-RHS solver for one block width
     struct cg_multi* multi32 = nullptr;      // FP32 multi-RHS inner solver (mixed form)

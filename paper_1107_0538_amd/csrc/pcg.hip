@@ -3,7 +3,8 @@
 // The paper's case study (Section IV) runs the CG loop on the host and the
 // repetitive vector and matrix work on the GPU, crossing the bus every
 // iteration.  Here the scalars (alpha, beta, the continue-condition) never
-// leave the device.  Each iteration is two kernels:
+// leave the device.  A system that fits the card's registers is solved by one
+// kernel (resident.hpp).  For the others each iteration is two kernels:
 //
 //   A_k  (direction + SpMV + dot)  reduce the previous B's partials of r'z and
 //        r'r, apply the continue-condition / breakdown / iteration-limit
@@ -31,6 +32,7 @@
 #include <new>
 
 #include "context.hpp"
+#include "resident_host.hpp"
 #include "sr_kernels.hpp"
 #include "std_kernels.hpp"
 #include "tiles.hpp"
@@ -290,8 +292,7 @@ static void fill_args(CgArgsT<T>& a, const SysView<T>& s, const TileMap& tm, int
     a.drop2 = 0.0;
 }
 
-// Build the kernels' arguments and capture the two chunk graphs (first
-// iteration of parity 0 or 1) for one form, precision and launch shape.
+// Build the kernels' arguments for one form, precision and launch shape.
 // mat32: the FP32-matrix form (FP64 standard form whose iteration products
 // stream the FP32 values), confirming on the FP64 true residual each time the
 // recurrence residual has fallen by `drop` since the last replacement.
@@ -370,35 +371,41 @@ static cg_graphs* make_graphs(cg_ctx* c, int form, bool fp32, int npl, int bs, i
             sa.hist = nullptr;
         }
         JPCG_HIP(hipStreamSynchronize(c->stream));
-        hipStream_t cap;
-        JPCG_HIP(hipStreamCreateWithFlags(&cap, hipStreamNonBlocking));
-        for (int pq = 0; pq < 8; ++pq) {
-            const int par = pq >> 2, q = pq & 3;
-            hipGraph_t graph;
-            JPCG_HIP(hipStreamBeginCapture(cap, hipStreamCaptureModeThreadLocal));
-            for (int it = 0; it < chunk; ++it) {
-                int P = (par + it) & 1;
-                if (form == CG_FORM_SINGLE_REDUCTION) {
-                    void* args[] = {&g->sargs, &P};
-                    launch(g->kern.sr_iter, G, bs, cap, args);
-                } else {
-                    void* args[] = {fp32 ? (void*)&g->args32 : (void*)&g->args, &P};
-                    launch(g->kern.direction, G, bs, cap, args);
-                    launch(g->kern.update, G, bs, cap, args);
-                }
-            }
-            JPCG_HIP(hipMemcpyAsync((char*)g->hst + q * g->st_bytes, g->st, g->st_bytes, hipMemcpyDeviceToHost, cap));
-            JPCG_HIP(hipStreamEndCapture(cap, &graph));
-            hipError_t e = hipGraphInstantiate(&g->exec[par][q], graph, nullptr, nullptr, 0);
-            (void)hipGraphDestroy(graph);
-            JPCG_HIP(e);
-        }
-        JPCG_HIP(hipStreamDestroy(cap));
         return g;
     } catch (...) {
         destroy_graphs(g);
         throw;
     }
+}
+
+// The chunk graphs, captured when a solve first runs through them.
+static void capture_graphs(cg_graphs* g)
+{
+    if (g->exec[1][3]) return;
+    hipStream_t cap;
+    JPCG_HIP(hipStreamCreateWithFlags(&cap, hipStreamNonBlocking));
+    for (int pq = 0; pq < 8; ++pq) {
+        const int par = pq >> 2, q = pq & 3;
+        hipGraph_t graph;
+        JPCG_HIP(hipStreamBeginCapture(cap, hipStreamCaptureModeThreadLocal));
+        for (int it = 0; it < g->chunk; ++it) {
+            int P = (par + it) & 1;
+            if (g->form == CG_FORM_SINGLE_REDUCTION) {
+                void* args[] = {&g->sargs, &P};
+                launch(g->kern.sr_iter, g->G, g->bs, cap, args);
+            } else {
+                void* args[] = {g->fp32 ? (void*)&g->args32 : (void*)&g->args, &P};
+                launch(g->kern.direction, g->G, g->bs, cap, args);
+                launch(g->kern.update, g->G, g->bs, cap, args);
+            }
+        }
+        JPCG_HIP(hipMemcpyAsync((char*)g->hst + q * g->st_bytes, g->st, g->st_bytes, hipMemcpyDeviceToHost, cap));
+        JPCG_HIP(hipStreamEndCapture(cap, &graph));
+        hipError_t e = hipGraphInstantiate(&g->exec[par][q], graph, nullptr, nullptr, 0);
+        (void)hipGraphDestroy(graph);
+        JPCG_HIP(e);
+    }
+    JPCG_HIP(hipStreamDestroy(cap));
 }
 
 }  // namespace jpcg
@@ -475,6 +482,7 @@ static void chunk_loop(cg_ctx* c, cg_graphs* g, int first_k, int maxit, bool use
                        Stopped stopped)
 {
     hipStream_t s = c->stream;
+    if (use_graph) capture_graphs(g);
     int next_k = first_k, slot = 0, pending = 0;
     const long long guard = (long long)maxit + 8LL * g->chunk + 64;
     long long launched = 0;
@@ -635,6 +643,26 @@ static SolveResult run_solve(cg_ctx* c, cg_graphs* g, const double* b, double* x
     JPCG_HIP(hipMemcpyAsync(x, g->cx, vb, hipMemcpyDeviceToDevice, s));
     JPCG_HIP(hipStreamSynchronize(s));
     return r;
+}
+
+// The solve on chip where the context has that (resident.hpp), else, or if the
+// device cannot hold it just now, through the graphs that `graphs` gives.
+template <typename Graphs>
+static SolveResult run_any(cg_ctx* c, int form, const double* b, double* x, double tol, int maxit, double drop,
+                           double* hist, Graphs graphs)
+{
+    RsOut o;
+    if (c->resident && run_resident(c, c->resident, form, b, x, tol, maxit, drop, hist, o)) {
+        SolveResult r;
+        r.stop = o.stop;
+        r.iters = o.iters;
+        r.replacements = o.replacements;
+        r.nb = o.nb;
+        r.rr = o.rr;
+        r.rr_true = o.rr_true;
+        return r;
+    }
+    return run_solve(c, graphs(), b, x, tol, maxit, hist);
 }
 
 // Mixed precision: FP64 outer residual, scaling, refinement update and final
@@ -866,6 +894,7 @@ static void free_ctx(cg_ctx* c)
     destroy_graphs(c->graphs32);
     destroy_graphs(c->graphs_m32);
     destroy_spmv_plan(c->spmv);
+    destroy_resident(c->resident);
     free_multi(c);
     free_block(c);
     if (c->mixed_dev) (void)hipFree(c->mixed_dev);
@@ -1029,6 +1058,10 @@ int cg_create(const cg_csr* A, const cg_opts* opts, void* hip_stream, cg_ctx** o
             c->spmv = explicit_shape ? make_spmv_plan(c, c->npl, c->bs, c->grid)
                                      : make_spmv_plan(c, 8, 512, default_grid(c, 8, 512, 2));
         }
+        // The on-chip solver, unless the caller gave a launch shape: that asks
+        // for the kernels it shapes.
+        if (!c->opts.nnz_per_lane && !c->opts.block_size && !c->opts.blocks_per_cu && !c->opts.chunk)
+            c->resident = make_resident(c);
         // The mixed form needs the standard FP64 graphs (outer residual) and
         // FP32 standard graphs (inner solve) with the same tile shape.
         if (c->opts.fp32_copy) {
@@ -1075,7 +1108,8 @@ int cg_solve(cg_ctx* c, const double* b, double* x, double tol, int32_t maxit, c
             hist = c->hist;
         }
         JPCG_HIP(hipEventRecord(c->ev0, c->stream));
-        const SolveResult st = run_solve(c, c->graphs, b, x, tol, maxit, hist);
+        const SolveResult st = run_any(c, c->form == CG_FORM_SINGLE_REDUCTION ? RS_SINGLE : RS_STANDARD, b, x, tol,
+                                       maxit, 0.0, hist, [&] { return c->graphs; });
         JPCG_HIP(hipEventRecord(c->ev1, c->stream));
         JPCG_HIP(hipEventSynchronize(c->ev1));
         float ms = 0.f;
@@ -1140,17 +1174,20 @@ int cg_solve_mixed_matrix(cg_ctx* c, const double* b, double* x, double tol, int
     if (maxit <= 0) maxit = c->n;
     if (drop == 0.0) drop = 1e-2;
     try {
-        if (!c->graphs_m32 || c->graphs_m32->args.drop2 != drop * drop) {
-            destroy_graphs(c->graphs_m32);
-            c->graphs_m32 = nullptr;
-            // Each reliable update drains the chunk in flight, so this form
-            // takes chunks of 8 unless the caller chose a length (at 51^3:
-            // 8.25 ms against 8.42 ms at 16; unchanged at 128^3).
-            const int chunk = c->opts.chunk ? c->chunk : std::min(c->chunk, 8);
-            c->graphs_m32 = make_graphs(c, CG_FORM_STANDARD, false, c->npl, c->bs, c->grid, chunk, true, drop);
-        }
+        auto graphs = [&] {
+            if (!c->graphs_m32 || c->graphs_m32->args.drop2 != drop * drop) {
+                destroy_graphs(c->graphs_m32);
+                c->graphs_m32 = nullptr;
+                // Each reliable update drains the chunk in flight, so this form
+                // takes chunks of 8 unless the caller chose a length (at 51^3:
+                // 8.25 ms against 8.42 ms at 16; unchanged at 128^3).
+                const int chunk = c->opts.chunk ? c->chunk : std::min(c->chunk, 8);
+                c->graphs_m32 = make_graphs(c, CG_FORM_STANDARD, false, c->npl, c->bs, c->grid, chunk, true, drop);
+            }
+            return c->graphs_m32;
+        };
         JPCG_HIP(hipEventRecord(c->ev0, c->stream));
-        const SolveResult st = run_solve(c, c->graphs_m32, b, x, tol, maxit, nullptr);
+        const SolveResult st = run_any(c, RS_FP32_MATRIX, b, x, tol, maxit, drop, nullptr, graphs);
         JPCG_HIP(hipEventRecord(c->ev1, c->stream));
         JPCG_HIP(hipEventSynchronize(c->ev1));
         float ms = 0.f;
