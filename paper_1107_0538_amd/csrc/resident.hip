@@ -136,7 +136,7 @@ static const void* rs_kernel(int form, int K, int bs)
 // blocks of 640 threads, else all groups.  The round across XCDs costs 1.1 us
 // more than the one within an XCD; 640 rows a workgroup instead of 80 cost
 // about 0.3 us more per product, and blocks of 1024 threads leave 128 registers
-// a thread, too few for a row of 27 without spills.
+// a thread, so that part of the row moves to LDS.
 static bool rs_geometry(int n, int cus, int& groups, int& members, int& rpw)
 {
     const int per_group = std::min(cus / kRsGroups, kRsGroup);
@@ -246,6 +246,14 @@ cg_resident* make_resident(cg_ctx* c)
     }
 }
 
+// LDS of a workgroup: the vector and what an iteration keeps of the halo, and
+// (blocks of 1024 threads) the columns' offsets from double `slots` on.
+static size_t rs_lds(int form, int K, int bs, int rows, int halo, int& slots)
+{
+    slots = (rows + 1 + (1 + (form == RS_SINGLE ? kRsHaloState : 1)) * halo + 1) / 2 * 2;
+    return sizeof(double) * (size_t)slots + (bs == 1024 ? sizeof(unsigned) * (size_t)(K / 2) * bs : 0);
+}
+
 bool run_resident(cg_ctx* c, cg_resident* r, int form, const double* b, double* x, double tol, int maxit, double drop,
                   double* hist, RsOut& res)
 {
@@ -256,7 +264,8 @@ bool run_resident(cg_ctx* c, cg_resident* r, int form, const double* b, double* 
     s.hist = hist;
     RsRun run{tol, drop * drop, maxit, r->abort, c->limit_ticks / 80, c->limit_ticks};
     const void* fn = rs_kernel(form, r->K, r->bs);
-    const size_t lds = sizeof(double) * (size_t)(r->rpw + 1 + (1 + (form == RS_SINGLE ? kRsHaloState : 1)) * r->halo);
+    const size_t lds = rs_lds(form, r->K, r->bs, r->rpw, r->halo, s.lds_slots);
+    if (lds > kRsMaxLds) return false;
     JPCG_HIP(hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, kRsMaxLds));
     void* args[] = {&s, &run};
     // One resident solve per device at a time: two of them, each partly on

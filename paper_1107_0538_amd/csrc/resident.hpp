@@ -98,6 +98,7 @@ struct RsSys {
     const int* hcol;        // [G][hcap]: columns of each workgroup's halo, from row0
     const int* hcount;      // [G]
     int hcap;
+    int lds_slots;          // where the columns' offsets start in LDS, in doubles
     const double* b;
     double* x;
     u64* xch[2];            // two words per row of the system, by the round's parity
@@ -191,7 +192,10 @@ __device__ __forceinline__ double rs_half_sum(double v)
 // (its longest row, rounded up); NH: halo entries per thread at most.
 template <int K, int BS, int NH, bool M32>
 struct RsTeam {
-    static constexpr int kWaves = BS / kWave;
+    static constexpr int kSlotWords = BS == 1024 ? 2 : K / 2;
+    // Blocks of 1024 threads have 128 registers a thread: there the columns'
+    // offsets and the halo's p stay in LDS, and a product reads fewer entries ahead.
+    static constexpr bool kSlotsInLds = BS == 1024, kHaloInLds = BS == 1024;
     using VT = std::conditional_t<M32, float, double>;
 
     const RsSys& s;
@@ -210,7 +214,8 @@ struct RsTeam {
     bool near;    // and only they read this thread's row
     int k0, len;
     VT v[K];
-    unsigned c[K / 2];  // byte offsets of the columns' LDS slots, two to a word
+    unsigned c[kSlotWords];  // byte offsets of the columns' LDS slots, two to a word
+    unsigned* lc;  // the same in LDS: [K / 4][BS] pairs of words
     unsigned hc[NH];  // halo columns, from row0
     double d, xo;
 
@@ -230,6 +235,8 @@ struct RsTeam {
         k0 = s.rowptr[row];
         len = has() ? s.rowptr[row + 1] - k0 : 0;
         const unsigned zero = 8u * (unsigned)(nown + H);
+        hs = pl + nown + H + 1;
+        lc = (unsigned*)(lds + s.lds_slots);
 #pragma unroll
         for (int j = 0; j < K; j += 2) {
             const int ka = j < len ? k0 + j : 0, kb = j + 1 < len ? k0 + j + 1 : 0;
@@ -244,8 +251,9 @@ struct RsTeam {
             const unsigned ca = 8u * s.lidx[ka], cb = 8u * s.lidx[kb];
             v[j] = j < len ? va : VT(0);
             v[j + 1] = j + 1 < len ? vb : VT(0);
-            c[j / 2] = (j < len ? ca : zero) | ((j + 1 < len ? cb : zero) << 16);
-            if (j % 8 == 6) __builtin_amdgcn_sched_barrier(0);  // few addresses in registers at a time
+            c[j / 2 % kSlotWords] = (j < len ? ca : zero) | ((j + 1 < len ? cb : zero) << 16);
+            if (kSlotsInLds && j % 4 == 2) *(uint2*)(lc + 2 * (j / 4 * BS + tid)) = make_uint2(c[0], c[1]);
+            if (j % 4 == 2) __builtin_amdgcn_sched_barrier(0);  // few addresses in registers at a time
         }
 #pragma unroll
         for (int j = 0; j < NH; ++j) {
@@ -254,7 +262,6 @@ struct RsTeam {
         }
         d = s.dinv[row];
         xo = s.x[row];
-        hs = pl + nown + H + 1;
         local = false;
         near = !(s.exported[(row - s.row0) >> 5] >> ((row - s.row0) & 31) & 1u);
         if (tid == 0) {
@@ -407,9 +414,7 @@ struct RsTeam {
 #pragma unroll
         for (int g = 0; g < K; g += kGroup) {
             double e[kGroup];
-#pragma unroll
-            for (int j = 0; j < kGroup; ++j)
-                if (g + j < K) e[j] = entry(g + j);
+            entries(g, e);
             __builtin_amdgcn_sched_barrier(0);  // a group's reads in flight together, and no more registers than that
 #pragma unroll
             for (int j = 0; j < kGroup; ++j)
@@ -421,18 +426,31 @@ struct RsTeam {
         }
         return t;
     }
-    static constexpr int kGroup = 14;
-    __device__ __forceinline__ double entry(int j) const
+    // Entries of the LDS vector read ahead of their use.
+    static constexpr int kGroup = kSlotsInLds ? 4 : 14;
+    // The LDS vector's entries for the columns g .. g + kGroup of the row.
+    __device__ __forceinline__ void entries(int g, double (&e)[kGroup])
     {
-        const unsigned o = (j & 1) ? c[j / 2] >> 16 : c[j / 2] & 0xffffu;
-        return *(const double*)((const char*)pl + o);
+        unsigned o[kGroup / 2];
+        if constexpr (kSlotsInLds) {
+            const uint2 two = *(const uint2*)(lc + 2 * (g / 4 * BS + tid));
+            o[0] = two.x;
+            o[1] = two.y;
+        } else {
+#pragma unroll
+            for (int j = 0; j < kGroup / 2; ++j) o[j] = g / 2 + j < K / 2 ? c[(g / 2 + j) % kSlotWords] : 0u;
+        }
+#pragma unroll
+        for (int j = 0; j < kGroup; ++j)
+            if (g + j < K)
+                e[j] = *(const double*)((const char*)pl + ((j & 1) ? o[j / 2] >> 16 : o[j / 2] & 0xffffu));
     }
     // Keeps what is cheaply formed from these (unpacked offsets, addresses)
     // from being held in registers across iterations.
     __device__ __forceinline__ void repack()
     {
 #pragma unroll
-        for (int j = 0; j < K / 2; ++j) asm volatile("" : "+v"(c[j]));
+        for (int j = 0; j < kSlotWords; ++j) asm volatile("" : "+v"(c[j]));
         if constexpr (M32) {
 #pragma unroll
             for (int j = 0; j < K; ++j) asm volatile("" : "+v"(v[j]));  // their conversions to double
@@ -452,10 +470,16 @@ struct RsTeam {
         repack();
         double t = 0.0;
 #pragma unroll
-        for (int j = 0; j < K; ++j) {
-            const double a = (j < len ? s.val[k0 + j] : 0.0) * entry(j);
-            t = t + a;
-            if (j % 4 == 3) asm volatile("" : "+v"(t));
+        for (int g = 0; g < K; g += kGroup) {
+            double e[kGroup];
+            entries(g, e);
+#pragma unroll
+            for (int j = 0; j < kGroup; ++j)
+                if (g + j < K) {
+                    const double a = (g + j < len ? s.val[k0 + g + j] : 0.0) * e[j];
+                    t = t + a;
+                }
+            asm volatile("" : "+v"(t));
         }
         return t;
     }
@@ -467,9 +491,7 @@ struct RsTeam {
 #pragma unroll
         for (int g = 0; g < K; g += kGroup) {
             double e[kGroup];
-#pragma unroll
-            for (int j = 0; j < kGroup; ++j)
-                if (g + j < K) e[j] = entry(g + j);
+            entries(g, e);
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int j = 0; j < kGroup; ++j)
@@ -522,6 +544,14 @@ struct RsTeam {
         for (int j = 0; j < NH; ++j) hv[j] = s.x[(unsigned)s.row0 + hc[j]];
     }
 
+    // A value that is the same in every lane, in scalar registers where vector
+    // registers are short.
+    static __device__ __forceinline__ double keep(double v)
+    {
+        if constexpr (kSlotsInLds) return rs_uniform(v);
+        else return v;
+    }
+
     // Branches on values that are the same in every lane are taken on a ballot:
     // one scalar branch, no masked execution of both sides.
     static __device__ __forceinline__ bool any(bool c) { return __ballot(c) != 0ull; }
@@ -533,12 +563,14 @@ struct RsTeam {
     // the inner one iterates.
     __device__ __forceinline__ bool solve_standard()
     {
-        double hv[NH] = {}, ph[NH] = {};
+        double hv[NH] = {};
+        double ph[kHaloInLds ? 1 : NH] = {};  // the halo's p
         double r, z, p = 0.0, rho = 0.0, beta = 0.0, nb = 0.0, thr = 0.0, rec = 0.0, drop = 0.0, bound = 0.0;
         int k = 0, repl = 0, stop = RUNNING;
         bool begin = true;
         if (!start()) return false;
         caller_halo(hv);
+        if constexpr (kHaloInLds) each_halo([&](int, int h) { hs[h] = 0.0; });
         while (true) {
             if (!begin) {
                 double none[1] = {0.0};
@@ -561,8 +593,8 @@ struct RsTeam {
                 if (!round<true>(q, hv)) return false;
                 rr = q[1];
                 if (begin) {
-                    nb = sqrt(q[2]);
-                    thr = run.tol * nb;
+                    nb = rs_uniform(sqrt(q[2]));
+                    thr = rs_uniform(run.tol * nb);
                     record(0, rr, nb);
                     if (any(nb == 0.0)) {
                         finish(STOP_ZERO_RHS, 0, 0, nb, rr, 0.0);
@@ -572,8 +604,8 @@ struct RsTeam {
                         finish(STOP_CONV0, 0, 0, nb, rr, rr);
                         return true;
                     }
-                    rec = rr;
-                    rho = q[0];
+                    rec = keep(rr);
+                    rho = keep(q[0]);
                 } else {
                     if (stop != RUNNING) {
                         finish(stop, k, repl, nb, rec, rr);
@@ -585,24 +617,28 @@ struct RsTeam {
                     }
                     ++repl;
                     record(k, rr, nb);
-                    rec = rr;
+                    rec = keep(rr);
                     stop = any(!positive(q[0])) ? STOP_BREAKDOWN : k >= run.maxit ? STOP_MAXIT : RUNNING;
                     if (stop != RUNNING) continue;
-                    beta = q[0] / rho;
-                    rho = q[0];
+                    beta = keep(q[0] / rho);
+                    rho = keep(q[0]);
                 }
                 // At or below this ||r||^2 the iteration is left for a test.
-                drop = run.drop2 * rr;
-                bound = fmax(threshold(thr), drop);
+                drop = rs_uniform(run.drop2 * rr);
+                bound = rs_uniform(fmax(threshold(thr), drop));
             }
             begin = false;
             while (true) {
                 // p = z + beta p for the row and, by the same operation as in
                 // its owner, for the halo.
                 p = __builtin_fma(beta, p, z);
+                if constexpr (kHaloInLds) {
+                    each_halo([&](int j, int h) { hs[h] = hv[j] = __builtin_fma(beta, hs[h], hv[j]); });
+                } else {
 #pragma unroll
-                for (int j = 0; j < NH; ++j) ph[j] = __builtin_fma(beta, ph[j], hv[j]);
-                place(p, ph);
+                    for (int j = 0; j < NH; ++j) hv[j] = ph[j] = __builtin_fma(beta, ph[j], hv[j]);
+                }
+                place(p, hv);
                 double ap;
                 if constexpr (M32) ap = product_diff(p);
                 else ap = product();
@@ -623,7 +659,7 @@ struct RsTeam {
                 ++k;
                 double q[2] = {r * z, r * r};
                 if (!round<true>(q, hv)) return false;
-                rec = q[1];
+                rec = keep(q[1]);
                 if (s.hist) record(k, q[1], nb);
                 const bool go = q[1] > bound && positive(q[0]);
                 if (any(!go) || k >= run.maxit) {
@@ -632,8 +668,8 @@ struct RsTeam {
                     stop = any(!positive(q[0])) ? STOP_BREAKDOWN : k >= run.maxit ? STOP_MAXIT : RUNNING;
                     if (stop != RUNNING) break;
                 }
-                beta = q[0] / rho;
-                rho = q[0];
+                beta = keep(q[0] / rho);
+                rho = keep(q[0]);
             }
         }
     }
@@ -676,10 +712,10 @@ struct RsTeam {
                     if (!round<true>(q, hv)) return false;
                     if (pass == 1) {
                         if (begin) {
-                            rec = q[0];
-                            nb = sqrt(q[1]);
-                            thr = run.tol * nb;
-                            bound = threshold(thr);
+                            rec = keep(q[0]);
+                            nb = rs_uniform(sqrt(q[1]));
+                            thr = rs_uniform(run.tol * nb);
+                            bound = rs_uniform(threshold(thr));
                             record(0, rec, nb);
                             if (any(nb == 0.0)) {
                                 finish(STOP_ZERO_RHS, 0, 0, nb, rec, 0.0);
@@ -727,7 +763,7 @@ struct RsTeam {
                 publish(w);
                 if (!round<true>(q, hv)) return false;
                 const double gam = q[0];
-                rec = q[2];
+                rec = keep(q[2]);
                 if (s.hist) record(k, rec, nb);
                 double beta = 0.0, sigma = q[1];
                 if (k > 0) {
@@ -745,7 +781,7 @@ struct RsTeam {
                     if (stop != RUNNING) break;
                 }
                 const double alpha = gam / sigma;
-                gam_old = gam;
+                gam_old = keep(gam);
                 p = __builtin_fma(beta, p, d * r);
                 sv = __builtin_fma(beta, sv, w);
                 r = __builtin_fma(-alpha, sv, r);

@@ -14,7 +14,8 @@ constexpr int kRsMaxRow = 28;         // nonzeros of a row at most
 constexpr int kRsMaxWgRows = 1024;    // rows of a workgroup at most
 // Halo columns per thread at most.
 constexpr int rs_halo(int bs) { return bs == 256 ? 4 : 3; }
-constexpr int kRsMaxLds = 128 * 1024;
+// Dynamic LDS of a workgroup at most (160 KB less the kernels' static 10.3 KB).
+constexpr size_t kRsMaxLds = 149 * 1024;
 constexpr int kRsMinRows = 64;        // rows of a workgroup at least
 constexpr int kRsMaxRows = kRsGroups * kRsGroup * kRsMaxWgRows;  // rows of a system at most (bitmap of the index kernel)
 
