@@ -279,6 +279,10 @@ int cg_solve_block(cg_ctx *ctx, const double *B, double *X, int32_t s, double to
  * solved by a team of workgroups sized in proportion to its expected work,
  * with cg_solve's algorithm and stopping rules; its rows are cut into
  * product tiles and each workgroup of the team owns an equal run of them.
+ * Where every system has at most 262144 rows of at most 28 nonzeros and opts
+ * gives no tile width and no blocks_per_cu, the solve holds the matrices in
+ * registers instead, system after system on teams that come free, in the same
+ * algorithm; cg_batch_teams reports the teams of the general path either way.
  * opts->precond applies to every system; opts->nnz_per_lane picks the tile
  * width (4, 8 or 16 nonzeros per lane, 0 = 16); opts->blocks_per_cu bounds the
  * workgroups per compute unit (0 = the occupancy limit, the most that can be

@@ -1,4 +1,6 @@
 // Batched Jacobi-PCG: many independent SPD systems in one persistent launch.
+// Batches whose systems all fit the card's registers go to resident_batch.hip;
+// what follows serves the others.
 //
 // The systems are concatenated into one block-diagonal CSR (global row and
 // column indices, int32) and each system's rows are cut into product tiles
@@ -137,6 +139,8 @@ struct cg_batch {
     hipEvent_t ev0 = nullptr, ev1 = nullptr;
     jpcg::BatchArgs args{};
     long long limit = 0;
+    jpcg::cg_batch_resident* resident = nullptr;  // the systems on chip, where all of them fit
+    bool general = false;  // solve by streaming the matrices all the same (while timing tile widths)
     std::string err;
 };
 
@@ -146,6 +150,7 @@ static void free_batch(cg_batch* b)
 {
     if (!b) return;
     if (b->exec) (void)hipGraphExecDestroy(b->exec);
+    destroy_batch_resident(b->resident);
     void* ptrs[] = {b->rowptr, b->col, b->val, b->dinv, b->vec, b->block_team, b->tiles, b->col16, b->ints, b->bar,
                     b->part, b->info};
     for (void* p : ptrs)
@@ -194,13 +199,16 @@ static void capture_batch(cg_batch* b, double tol, int maxit)
     b->graph_maxit = maxit;
 }
 
-}  // namespace jpcg
+static int status_of_stop(int stop)
+{
+    if (stop == STOP_MAXIT) return CG_MAXIT;
+    if (stop == STOP_BREAKDOWN) return CG_BREAKDOWN;
+    return CG_CONVERGED;
+}
 
-using namespace jpcg;
-
-extern "C" {
-
-int cg_batch_create(int32_t nsys, const cg_csr* systems, const cg_opts* opts, void* hip_stream, cg_batch** out)
+// on_chip: solve on chip if every system fits (the caller gave no shape).
+static int create_batch(int32_t nsys, const cg_csr* systems, const cg_opts* opts, void* hip_stream, cg_batch** out,
+                        bool on_chip)
 {
     if (!out) return CG_EINVAL;
     *out = nullptr;
@@ -221,11 +229,12 @@ int cg_batch_create(int32_t nsys, const cg_csr* systems, const cg_opts* opts, vo
             o2.autotune = 0;
             o2.nnz_per_lane = npl;
             cg_batch* cand = nullptr;
-            last_rc = cg_batch_create(nsys, systems, &o2, hip_stream, &cand);
+            last_rc = create_batch(nsys, systems, &o2, hip_stream, &cand, on_chip);
             if (last_rc != 0) {
                 if (last_rc == CG_EINVAL || last_rc == CG_EDIAG) return last_rc;  // input errors
                 continue;
             }
+            cand->general = true;  // it is the tile width that is timed
             double t = 1e300;
             double *bv = nullptr, *xv = nullptr;
             std::vector<cg_info> info(nsys);
@@ -242,6 +251,7 @@ int cg_batch_create(int32_t nsys, const cg_csr* systems, const cg_opts* opts, vo
             }
             if (bv) (void)hipFree(bv);
             if (xv) (void)hipFree(xv);
+            cand->general = false;
             if (t < best_s) {
                 cg_batch_destroy(best);
                 best = cand;
@@ -453,6 +463,13 @@ int cg_batch_create(int32_t nsys, const cg_csr* systems, const cg_opts* opts, vo
         a.part = b->part;
         a.info = b->info;
         a.limit = b->limit;
+        if (on_chip) {
+            std::vector<int> rows(nsys);
+            for (int s = 0; s < nsys; ++s) rows[s] = systems[s].n;
+            b->resident = make_batch_resident(RsBatchMatrix{nsys, rows.data(), b->row_off.data(), rowptr.data(),
+                                                            b->rowptr, b->col, b->val, b->dinv},
+                                              cus, st);
+        }
         *out = b;
         return 0;
     } catch (const HipError& e) {
@@ -464,14 +481,57 @@ int cg_batch_create(int32_t nsys, const cg_csr* systems, const cg_opts* opts, vo
     }
 }
 
+}  // namespace jpcg
+
+using namespace jpcg;
+
+extern "C" {
+
+int cg_batch_create(int32_t nsys, const cg_csr* systems, const cg_opts* opts, void* hip_stream, cg_batch** out)
+{
+    // A caller who gives a tile width or a grid asks for the kernels they shape.
+    return create_batch(nsys, systems, opts, hip_stream, out,
+                        !opts || (!opts->nnz_per_lane && !opts->blocks_per_cu));
+}
+
 int cg_batch_solve(cg_batch* b, const double* b_cat, double* x_cat, double tol, int32_t maxit, cg_info* info)
 {
     if (!b) return CG_EINVAL;
     if (!b_cat || !x_cat || b_cat == x_cat || !(tol >= 0.0) || !std::isfinite(tol)) return CG_EINVAL;
     try {
-        if (!b->exec || b->graph_tol != tol || b->graph_maxit != maxit) capture_batch(b, tol, maxit);
         hipStream_t st = b->stream;
         const size_t vb = sizeof(double) * (size_t)b->n_total;
+        const RsOut* r = nullptr;
+        if (b->resident && !b->general) {
+            // On the batch's own x: should the launch be given up, the caller's
+            // is as it was.
+            JPCG_HIP(hipEventRecord(b->ev0, st));
+            JPCG_HIP(hipMemcpyAsync(b->args.x, x_cat, vb, hipMemcpyDeviceToDevice, st));
+            if (!run_batch_resident(b->resident, b->device, st, b_cat, b->args.x, tol, maxit, b->limit, r)) r = nullptr;
+        }
+        if (r) {
+            JPCG_HIP(hipMemcpyAsync(x_cat, b->args.x, vb, hipMemcpyDeviceToDevice, st));
+            JPCG_HIP(hipEventRecord(b->ev1, st));
+            JPCG_HIP(hipStreamSynchronize(st));
+            float ms = 0.f;
+            JPCG_HIP(hipEventElapsedTime(&ms, b->ev0, b->ev1));
+            int worst = CG_CONVERGED;
+            for (int s = 0; s < b->nsys; ++s) {
+                const int status = status_of_stop(r[s].stop);
+                worst = std::max(worst, status);
+                if (info) {
+                    info[s].iters = r[s].iters;
+                    info[s].status = status;
+                    info[s].replacements = r[s].replacements;
+                    info[s].outer = 0;
+                    info[s].relres_recur = r[s].nb > 0 ? std::sqrt(r[s].rr) / r[s].nb : 0.0;
+                    info[s].relres_true = r[s].nb > 0 ? std::sqrt(r[s].rr_true) / r[s].nb : 0.0;
+                    info[s].seconds = ms * 1e-3;
+                }
+            }
+            return worst;
+        }
+        if (!b->exec || b->graph_tol != tol || b->graph_maxit != maxit) capture_batch(b, tol, maxit);
         JPCG_HIP(hipEventRecord(b->ev0, st));
         JPCG_HIP(hipMemcpyAsync((void*)b->args.b, b_cat, vb, hipMemcpyDeviceToDevice, st));
         JPCG_HIP(hipMemcpyAsync(b->args.x, x_cat, vb, hipMemcpyDeviceToDevice, st));

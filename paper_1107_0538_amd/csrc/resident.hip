@@ -89,12 +89,19 @@ __global__ void k_rs_clear(ulonglong2* words, int64_t pairs)
         words[i] = ulonglong2{0ull, 0ull};
 }
 
-template <int BS>
-struct RsLds {
-    double red[kRsSums * BS / 4];
-    double tot[kRsSums];
-    int fail;
-};
+void launch_rs_index(hipStream_t st, const RsIndexJob* jobs, int njobs, const int* rowptr, const int* col, int hcap,
+                     int* hcol, int* hcount, unsigned short* lidx, unsigned* exported, int* flag)
+{
+    k_rs_index<<<njobs, kIndexBS, 0, st>>>(jobs, rowptr, col, hcap, hcol, hcount, lidx, exported, flag);
+    JPCG_HIP(hipGetLastError());
+}
+
+void launch_rs_clear(hipStream_t st, u64* words, size_t nwords)
+{
+    const int64_t pairs = (int64_t)(nwords / 2);
+    k_rs_clear<<<(int)std::min<int64_t>(4096, (pairs + 255) / 256), 256, 0, st>>>((ulonglong2*)words, pairs);
+    JPCG_HIP(hipGetLastError());
+}
 
 template <int K, int BS, int FORM>
 __global__ __launch_bounds__(BS) void k_rs_solve(RsSys s, RsRun run)
@@ -102,7 +109,7 @@ __global__ __launch_bounds__(BS) void k_rs_solve(RsSys s, RsRun run)
     extern __shared__ double pl[];
     __shared__ RsLds<BS> sh;
     // Blocks are dealt to the XCDs in turn: block b belongs to group b mod 8.
-    const int group = (int)blockIdx.x % kRsGroups, member = (int)blockIdx.x / kRsGroups;
+    const int group = (int)blockIdx.x % kRsXcds, member = (int)blockIdx.x / kRsXcds;
     if (group >= s.groups) return;
     RsTeam<K, BS, rs_halo(BS), FORM == RS_FP32_MATRIX> team(s, run, group * s.members + member, pl, sh.red, sh.tot,
                                                             &sh.fail);
@@ -139,14 +146,14 @@ static const void* rs_kernel(int form, int K, int bs)
 // a thread, so that part of the row moves to LDS.
 static bool rs_geometry(int n, int cus, int& groups, int& members, int& rpw)
 {
-    const int per_group = std::min(cus / kRsGroups, kRsGroup);
+    const int per_group = std::min(cus / kRsXcds, kRsGroup);
     if (per_group < 1) return false;
     auto rows = [&](int wgs) { return std::max(kRsMinRows, (((n + wgs - 1) / wgs) + 7) / 8 * 8); };
     groups = 1;
     rpw = rows(per_group);
     if (rpw > 640) {
-        groups = kRsGroups;
-        rpw = rows(kRsGroups * per_group);
+        groups = kRsXcds;
+        rpw = rows(kRsXcds * per_group);
     }
     members = std::min(per_group, (n + groups * rpw - 1) / (groups * rpw));
     return rpw <= kRsMaxWgRows;
@@ -198,9 +205,8 @@ cg_resident* make_resident(cg_ctx* c)
         JPCG_HIP(hipMalloc(&dflag, sizeof(int)));
         JPCG_HIP(hipMemcpyAsync(djobs, jobs.data(), sizeof(RsIndexJob) * r->G, hipMemcpyHostToDevice, c->stream));
         JPCG_HIP(hipMemsetAsync(dflag, 0, sizeof(int), c->stream));
-        k_rs_index<<<r->G, kIndexBS, 0, c->stream>>>(djobs, c->rowptr, c->col, hcap, r->hcol, r->hcount, r->lidx,
-                                                   r->exported, dflag);
-        JPCG_HIP(hipGetLastError());
+        launch_rs_index(c->stream, djobs, r->G, c->rowptr, c->col, hcap, r->hcol, r->hcount, r->lidx, r->exported,
+                        dflag);
         int flag = 0;
         std::vector<int> hcount(r->G);
         JPCG_HIP(hipMemcpyAsync(hcount.data(), r->hcount, sizeof(int) * r->G, hipMemcpyDeviceToHost, c->stream));
@@ -231,11 +237,10 @@ cg_resident* make_resident(cg_ctx* c)
         s.hcol = r->hcol;
         s.hcount = r->hcount;
         s.hcap = hcap;
-        s.sums[0] = (char*)r->words;
-        s.sums[1] = s.sums[0] + kRsSumBytes;
-        s.xch[0] = r->words + 2 * pw;
-        s.xch[1] = s.xch[0] + xw;
-        r->abort = (unsigned*)(s.xch[1] + xw);
+        s.sums = (char*)r->words;
+        s.xch = r->words + 2 * pw;
+        s.xch_step = xw;
+        r->abort = (unsigned*)(s.xch + 2 * xw);
         s.out = r->out;
         return r;
     } catch (...) {
@@ -247,11 +252,11 @@ cg_resident* make_resident(cg_ctx* c)
 }
 
 // LDS of a workgroup: the vector and what an iteration keeps of the halo, and
-// (blocks of 1024 threads) the columns' offsets from double `slots` on.
-static size_t rs_lds(int form, int K, int bs, int rows, int halo, int& slots)
+// (rs_tight) the columns' offsets from double `slots` on.
+size_t rs_lds(int form, int K, int bs, int rows, int halo, int& slots)
 {
     slots = (rows + 1 + (1 + (form == RS_SINGLE ? kRsHaloState : 1)) * halo + 1) / 2 * 2;
-    return sizeof(double) * (size_t)slots + (bs == 1024 ? sizeof(unsigned) * (size_t)(K / 2) * bs : 0);
+    return sizeof(double) * (size_t)slots + (rs_tight(bs) ? sizeof(unsigned) * (size_t)(K / 2) * bs : 0);
 }
 
 bool run_resident(cg_ctx* c, cg_resident* r, int form, const double* b, double* x, double tol, int maxit, double drop,
@@ -272,10 +277,8 @@ bool run_resident(cg_ctx* c, cg_resident* r, int form, const double* b, double* 
     // the card, would wait for each other.
     std::lock_guard<std::mutex> lock(resident_mutex(c->device));
     r->out->stop = RS_ABORTED;
-    const int64_t pairs = (int64_t)(r->nwords / 2);
-    k_rs_clear<<<(int)std::min<int64_t>(1024, (pairs + 255) / 256), 256, 0, st>>>((ulonglong2*)r->words, pairs);
-    JPCG_HIP(hipGetLastError());
-    JPCG_HIP(hipLaunchKernel(fn, dim3(kRsGroups * r->sys.members), dim3(r->bs), args, lds, st));
+    launch_rs_clear(st, r->words, r->nwords);
+    JPCG_HIP(hipLaunchKernel(fn, dim3(kRsXcds * r->sys.members), dim3(r->bs), args, lds, st));
     JPCG_HIP(hipStreamSynchronize(st));
     res = *r->out;
     return res.stop != RS_ABORTED;

@@ -57,10 +57,12 @@ namespace jpcg {
 
 using u64 = unsigned long long;
 
-// The most sums exchanged in a round, workgroups of a group and groups.
+// The most sums exchanged in a round, workgroups of a group, XCDs, and groups
+// of a team (two on an XCD where workgroups run two to a compute unit).
 constexpr int kRsSums = 5;
 constexpr int kRsGroup = 32;
-constexpr int kRsGroups = 8;
+constexpr int kRsXcds = 8;
+constexpr int kRsGroups = 16;
 // Bytes of a team's sums for one parity: [group][sum][member] of 16 bytes, and
 // a line of 128 bytes per group with its sums.
 constexpr unsigned kRsSumBytes = kRsGroups * (16u * kRsSums * kRsGroup + 128u);
@@ -75,6 +77,9 @@ __device__ __forceinline__ unsigned rs_group_sum(int sum, int group)
 // Vectors kept for the halo columns: p, or d, r and s (single-reduction form).
 constexpr int kRsHaloState = 3;
 constexpr int kRsMaxSlot = 0x7fffffff;
+// Blocks whose threads have 128 registers: 1024 threads, or 512 two to a
+// compute unit.
+constexpr bool rs_tight(int bs) { return bs == 1024 || bs == 512; }
 
 struct RsOut {
     int stop, iters, replacements, pad;
@@ -101,8 +106,9 @@ struct RsSys {
     int lds_slots;          // where the columns' offsets start in LDS, in doubles
     const double* b;
     double* x;
-    u64* xch[2];            // two words per row of the system, by the round's parity
-    char* sums[2];          // kRsSumBytes each, by the round's parity
+    u64* xch;               // two words per row of the system; odd rounds' xch_step words on
+    size_t xch_step;
+    char* sums;             // kRsSumBytes; odd rounds' as many bytes on
     RsOut* out;
     double* hist;
 };
@@ -148,22 +154,26 @@ __device__ __forceinline__ double rs_value(rs_words w)
 }
 __device__ __forceinline__ bool rs_tagged(rs_words w, unsigned tag) { return w.y == tag && w.w == tag; }
 
-// A bounded wait: true while it may go on.
+// A bounded wait: true while it may go on.  Past its limit it allows one more
+// look, so that a workgroup gives up only if what it awaits is missing then;
+// what everyone else has seen is not missing, so a solve that some workgroup
+// finished is finished by all.
 struct RsWait {
     unsigned* abort;
     long long limit, t0;
     int spins;
-    __device__ __forceinline__ RsWait(unsigned* a, long long l) : abort(a), limit(l), t0(0), spins(0) {}
+    bool last;
+    __device__ __forceinline__ RsWait(unsigned* a, long long l) : abort(a), limit(l), t0(0), spins(0), last(false) {}
     __device__ __forceinline__ bool more()
     {
-        if ((++spins & 31) != 0) return true;
-        if (__hip_atomic_load(abort, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) return false;
-        const long long now = wall_clock64();
-        if (spins == 32) t0 = now;
-        if (now - t0 > limit) {
+        if (last) {
             __hip_atomic_store(abort, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             return false;
         }
+        if ((++spins & 31) != 0) return true;
+        const long long now = wall_clock64();
+        if (spins == 32) t0 = now;
+        last = now - t0 > limit || __hip_atomic_load(abort, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0u;
         return true;
     }
 };
@@ -192,10 +202,12 @@ __device__ __forceinline__ double rs_half_sum(double v)
 // (its longest row, rounded up); NH: halo entries per thread at most.
 template <int K, int BS, int NH, bool M32>
 struct RsTeam {
-    static constexpr int kSlotWords = BS == 1024 ? 2 : K / 2;
-    // Blocks of 1024 threads have 128 registers a thread: there the columns'
-    // offsets and the halo's p stay in LDS, and a product reads fewer entries ahead.
-    static constexpr bool kSlotsInLds = BS == 1024, kHaloInLds = BS == 1024;
+    static constexpr bool kTight = rs_tight(BS);
+    static constexpr int kSlotWords = kTight ? 2 : K / 2;
+    // With 128 registers a thread the columns' offsets and the halo's p stay in
+    // LDS, and a product reads fewer entries ahead.  Held in registers they
+    // spilled (90 of them): 8.6 us per iteration at 60^3 against 6.2, 6.8
+    // against 5.7 in the single-reduction form.
     using VT = std::conditional_t<M32, float, double>;
 
     const RsSys& s;
@@ -252,7 +264,7 @@ struct RsTeam {
             v[j] = j < len ? va : VT(0);
             v[j + 1] = j + 1 < len ? vb : VT(0);
             c[j / 2 % kSlotWords] = (j < len ? ca : zero) | ((j + 1 < len ? cb : zero) << 16);
-            if (kSlotsInLds && j % 4 == 2) *(uint2*)(lc + 2 * (j / 4 * BS + tid)) = make_uint2(c[0], c[1]);
+            if (kTight && j % 4 == 2) *(uint2*)(lc + 2 * (j / 4 * BS + tid)) = make_uint2(c[0], c[1]);
             if (j % 4 == 2) __builtin_amdgcn_sched_barrier(0);  // few addresses in registers at a time
         }
 #pragma unroll
@@ -283,7 +295,7 @@ struct RsTeam {
 
     __device__ __forceinline__ void publish(double value)
     {
-        if (has()) rs_publish(rs_buffer(s.xch[tag & 1]), 16u * (unsigned)(row - s.row0), value, tag,
+        if (has()) rs_publish(rs_buffer(s.xch + (tag & 1u) * s.xch_step), 16u * (unsigned)(row - s.row0), value, tag,
                               local && near);
     }
 
@@ -291,7 +303,7 @@ struct RsTeam {
     __device__ __forceinline__ bool gather(double (&hv)[NH])
     {
         if (nh == 0) return true;
-        const auto buf = rs_buffer(s.xch[tag & 1]);
+        const auto buf = rs_buffer(s.xch + (tag & 1u) * s.xch_step);
         unsigned need = 0;
 #pragma unroll
         for (int j = 0; j < NH; ++j) need |= halo_slot(j) < H ? 1u << j : 0u;
@@ -337,7 +349,7 @@ struct RsTeam {
         ++tag;
         const int lane = tid & (kWave - 1);
         if (tid < kWave) {
-            char* const base = s.sums[tag & 1];
+            char* const base = s.sums + (tag & 1u) * kRsSumBytes;
             if (lane == 0) rs_publish(rs_buffer(base), rs_member_sum(group, 0, member), (double)xcc, tag, false);
             double id;
             const bool use = lane < s.members;
@@ -381,7 +393,7 @@ struct RsTeam {
             for (int j = 0; j < BS / 4; j += 32) v += red[k * (BS / 4) + j + l];
             v = rs_half_sum(v);
             if (s.groups * s.members > 1) {
-                char* const base = s.sums[tag & 1];
+                char* const base = s.sums + (tag & 1u) * kRsSumBytes;
                 if (l == 31) rs_publish(rs_buffer(base), rs_member_sum(group, k, member), v, tag, local);
                 const bool use = l < s.members;
                 ok = await(base, rs_member_sum(group, k, use ? l : 0), use, v);
@@ -427,12 +439,12 @@ struct RsTeam {
         return t;
     }
     // Entries of the LDS vector read ahead of their use.
-    static constexpr int kGroup = kSlotsInLds ? 4 : 14;
+    static constexpr int kGroup = kTight ? 4 : 14;
     // The LDS vector's entries for the columns g .. g + kGroup of the row.
     __device__ __forceinline__ void entries(int g, double (&e)[kGroup])
     {
         unsigned o[kGroup / 2];
-        if constexpr (kSlotsInLds) {
+        if constexpr (kTight) {
             const uint2 two = *(const uint2*)(lc + 2 * (g / 4 * BS + tid));
             o[0] = two.x;
             o[1] = two.y;
@@ -548,7 +560,7 @@ struct RsTeam {
     // registers are short.
     static __device__ __forceinline__ double keep(double v)
     {
-        if constexpr (kSlotsInLds) return rs_uniform(v);
+        if constexpr (kTight) return rs_uniform(v);
         else return v;
     }
 
@@ -564,13 +576,13 @@ struct RsTeam {
     __device__ __forceinline__ bool solve_standard()
     {
         double hv[NH] = {};
-        double ph[kHaloInLds ? 1 : NH] = {};  // the halo's p
+        double ph[kTight ? 1 : NH] = {};  // the halo's p
         double r, z, p = 0.0, rho = 0.0, beta = 0.0, nb = 0.0, thr = 0.0, rec = 0.0, drop = 0.0, bound = 0.0;
         int k = 0, repl = 0, stop = RUNNING;
         bool begin = true;
         if (!start()) return false;
         caller_halo(hv);
-        if constexpr (kHaloInLds) each_halo([&](int, int h) { hs[h] = 0.0; });
+        if constexpr (kTight) each_halo([&](int, int h) { hs[h] = 0.0; });
         while (true) {
             if (!begin) {
                 double none[1] = {0.0};
@@ -632,7 +644,7 @@ struct RsTeam {
                 // p = z + beta p for the row and, by the same operation as in
                 // its owner, for the halo.
                 p = __builtin_fma(beta, p, z);
-                if constexpr (kHaloInLds) {
+                if constexpr (kTight) {
                     each_halo([&](int j, int h) { hs[h] = hv[j] = __builtin_fma(beta, hs[h], hv[j]); });
                 } else {
 #pragma unroll

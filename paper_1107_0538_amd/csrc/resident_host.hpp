@@ -17,7 +17,7 @@ constexpr int rs_halo(int bs) { return bs == 256 ? 4 : 3; }
 // Dynamic LDS of a workgroup at most (160 KB less the kernels' static 10.3 KB).
 constexpr size_t kRsMaxLds = 149 * 1024;
 constexpr int kRsMinRows = 64;        // rows of a workgroup at least
-constexpr int kRsMaxRows = kRsGroups * kRsGroup * kRsMaxWgRows;  // rows of a system at most (bitmap of the index kernel)
+constexpr int kRsMaxRows = kRsXcds * kRsGroup * kRsMaxWgRows;  // rows of a system at most (bitmap of the index kernel)
 
 // Rows [first, first + rows) of the system with rows [row0, row0 + n): one
 // workgroup's share, whose halo list goes to entry `slot`.
@@ -26,6 +26,18 @@ struct RsIndexJob {
     int group_first, group_end;  // rows of the workgroup's group
     int bits0;                   // first word of the system's `exported` bits
 };
+
+template <int BS>
+struct RsLds {
+    double red[kRsSums * BS / 4];
+    double tot[kRsSums];
+    int fail;
+};
+
+void launch_rs_index(hipStream_t st, const RsIndexJob* jobs, int njobs, const int* rowptr, const int* col, int hcap,
+                     int* hcol, int* hcount, unsigned short* lidx, unsigned* exported, int* flag);
+void launch_rs_clear(hipStream_t st, u64* words, size_t nwords);
+size_t rs_lds(int form, int K, int bs, int rows, int halo, int& slots);
 
 // Held by every launch whose workgroups wait for each other, until it ends.
 std::mutex& resident_mutex(int device);
@@ -56,5 +68,25 @@ void destroy_resident(cg_resident* r);
 // it was.
 bool run_resident(cg_ctx* c, cg_resident* r, int form, const double* b, double* x, double tol, int maxit, double drop,
                   double* hist, RsOut& res);
+
+// The batch's systems by teams of the same solver (resident_batch.hip).
+struct RsBatchMatrix {
+    int nsys;
+    const int* rows;         // per system
+    const int64_t* row_off;  // per system, and the total
+    const int* h_rowptr;     // of the concatenated matrix, on the host and the device
+    const int* rowptr;
+    const int* col;
+    const double* val;
+    const double* dinv;
+};
+struct cg_batch_resident;
+// Null when some system does not fit.
+cg_batch_resident* make_batch_resident(const RsBatchMatrix& m, int cus, hipStream_t st);
+void destroy_batch_resident(cg_batch_resident* r);
+// Solves on the batch's own b and x (maxit <= 0: each system's rows) and fills
+// out[nsys].  False if the workgroups could not all be on the card in time.
+bool run_batch_resident(cg_batch_resident* r, int device, hipStream_t st, const double* b, double* x, double tol,
+                        int maxit, long long limit, const RsOut*& out);
 
 }  // namespace jpcg

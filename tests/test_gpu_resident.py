@@ -140,3 +140,28 @@ def test_resident_solves_from_several_threads(cuda):
     for t in threads:
         t.join()
     assert not bad
+
+
+@pytest.mark.parametrize("sizes,long_row", [
+    ((1, 64, 65, 700, 3000), False),           # small: all systems on the card at once
+    ((100,) * 40 + (33000, 5, 20000), False),  # more than one XCD, many teams
+    ((60000,) * 5 + (130000, 1000), False),    # systems that queue for the card
+    ((500, 600), True),                        # a row that is too long: the general path
+])
+def test_resident_batches(cuda, sizes, long_row):
+    from paper_1107_0538_amd import Batch
+
+    mats = [banded(n, (1, 30), seed=i) for i, n in enumerate(sizes)]
+    if long_row:
+        mats[1] = banded(sizes[1], tuple(range(1, 16)), seed=9)
+    rng = np.random.default_rng(len(sizes))
+    bs = [rng.uniform(-1, 1, a.n) for a in mats]
+    bt = Batch(mats)
+    x, infos = bt.solve(_t(np.concatenate(bs), cuda))
+    y, infos2 = bt.solve(_t(np.concatenate(bs), cuda))
+    assert np.array_equal(x.cpu().numpy(), y.cpu().numpy())
+    x = x.cpu().numpy()
+    for s, a in enumerate(mats):
+        check(a, bs[s], x[bt.offsets[s]:bt.offsets[s + 1]], infos[s], "standard")
+    x, infos = bt.solve(_t(np.concatenate(bs), cuda), maxit=2)
+    assert all(i["iters"] <= 2 for i in infos) and all(i["status"] == (0 if a.n <= 2 else 1) for i, a in zip(infos, mats))
