@@ -157,7 +157,10 @@ int cg_create(const cg_csr *A, const cg_opts *opts, void *hip_stream, cg_ctx **o
  * at most 262144 rows of at most 28 nonzeros, created without a launch shape in
  * its options, is solved by one kernel that holds the matrix in registers (such
  * solves on one device, and batched ones, wait for each other); otherwise
- * iterations run as kernels launched in hipGraph chunks.  The call synchronises
+ * iterations run as kernels launched in hipGraph chunks, in the standard form
+ * over a second copy of the matrix in slices of 64 rows where its rows are of
+ * about equal length (at most 64), no launch shape or column width was given
+ * and there is memory for it.  The call synchronises
  * the context's stream.
  * info may be NULL.  Returns the status (>= 0) or an API error (< 0).
  */
@@ -203,8 +206,8 @@ int cg_solve_mixed_matrix(cg_ctx *ctx, const double *b, double *x, double tol, i
 
 /* y = A x (the paper's "DGEMV(sparse)").  Device pointers to float64[n], x != y.
  * Rows are summed in stored order (bitwise the sequential CSR product), with
- * the product's own tiling and grid (cg_config.spmv_*).  Asynchronous on the
- * context's stream.  Returns 0 or an API error. */
+ * the product's own tiling and grid (cg_config.spmv_*) or over cg_solve's slices
+ * where the context has them.  Asynchronous on the context's stream.  Returns 0 or an API error. */
 int spmv(cg_ctx *ctx, const double *x, double *y);
 
 /*

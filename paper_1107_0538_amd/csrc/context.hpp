@@ -47,6 +47,9 @@ struct cg_ctx {
     struct cg_graphs* graphs_m32 = nullptr;  // standard form FP64 with the FP32 matrix stream
     void* mixed_dev = nullptr;
     void* mixed_host = nullptr;
+    struct cg_ell* ell = nullptr;            // the matrix in slices, where its rows suit them
+    struct cg_graphs* graphs_ell = nullptr;  // standard form over slices
+    struct cg_graphs* graphs_ell32 = nullptr;  // the same streaming FP32 values
     struct cg_resident* resident = nullptr;  // the on-chip solver, where the system fits it
     struct cg_spmv_plan* spmv = nullptr;     // the standalone product's tiling and grid
     struct cg_multi* multi = nullptr;        // multi-RHS solver for one block width
