@@ -4,7 +4,7 @@
 // orthonormalised with rank revelation by shifted Cholesky QR (Fukaya et al.).
 //
 // Per iteration, on N x 64 row-major FP64 blocks (columns >= s are zero):
-//   Q = A P                                  k_bc_spmm (row products, lane = column)
+//   Q = A P                                  k_bc_spmm (row products, four rows a wave)
 //   Gamma = P'Q, Psi = P'R                   k_bc_gram<2> + k_bc_sum
 //   alpha = Gamma^-1 Psi                     k_bc_alpha (one wave: Cholesky over
 //                                            the live columns, inverse factor)
@@ -308,23 +308,13 @@ __global__ __launch_bounds__(kGemmBS, 2) void k_bc_gemm(BcGemmArgs g, BcState* s
 // ---------------------------------------------------------------------------
 // Row products and residuals.
 // ---------------------------------------------------------------------------
-constexpr int kBcSpmmBS = 512;
 
-// Y = A X over N x 64 blocks (two nonzeros per gather, see mr_row_x2).
-__global__ __launch_bounds__(kBcSpmmBS) void k_bc_spmm(int n, const int* __restrict__ rowptr,
-                                                       const int* __restrict__ col, const double* __restrict__ val,
-                                                       const double* __restrict__ X, double* __restrict__ Y,
-                                                       int rows_per_block, int G, const BcState* st, int gate)
+// Y = A X over N x 64 blocks (spmm.hpp).
+__global__ __launch_bounds__(kSpmmBS, 6) void k_bc_spmm(RunMap<double> m, const double* __restrict__ X,
+                                                     double* __restrict__ Y, int G, const BcState* st, int gate)
 {
     if (bc_stopped(st, gate)) return;
-    const int L = xcd_logical_block((int)blockIdx.x, G);
-    const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
-    const int rs = min(L * rows_per_block, n), re = min(rs + rows_per_block, n);
-    const int cp = 2 * (lane & 31);
-    for (int i = rs + w; i < re; i += kBcSpmmBS / kWave) {
-        const double2 y = mr_row_x2(rowptr, col, val, i, [&](int j) { return *(const double2*)(X + (size_t)j * kB + cp); });
-        if (lane < 32) *(double2*)(Y + (size_t)i * kB + cp) = y;
-    }
+    spmm_block(m, X, Y, kB, G);
 }
 
 // R = B - AX (AX given), Z = M^-1 R, per-workgroup partials of r'r and b'b
@@ -736,7 +726,7 @@ __global__ void k_bc_scalars(BcState* st, const double* __restrict__ part, int G
 
 // Block solver state hanging off a context.
 struct cg_block {
-    int gram_G = 0, gemm_G = 0, spmm_G = 0, spmm_rpb = 0, gram_rpw = 0, res_G = 0, chunk = 4;
+    int gram_G = 0, gemm_G = 0, spmm_G = 0, gram_rpw = 0, res_G = 0, chunk = 4;
     double* work = nullptr;  // B, X, R, Z, P, Q, W: 7 n x 64 blocks
     double* part = nullptr;  // Gram partials [gram_G][2][4096]
     double* part2 = nullptr; // norm / residual partials [max(gemm_G, res_G)][2][64]
@@ -788,9 +778,9 @@ struct BcOps {
 
     void spmm(const double* X, double* Y, int gate)
     {
-        int n = c->n;
-        void* a[] = {&n, &c->rowptr, &c->col, &c->val, &X, &Y, &b->spmm_rpb, &b->spmm_G, &b->st, &gate};
-        launch((const void*)k_bc_spmm, b->spmm_G, kBcSpmmBS, st, a);
+        RunMap<double> m = run_map(c);
+        void* a[] = {&m, &X, &Y, &b->spmm_G, &b->st, &gate};
+        launch((const void*)k_bc_spmm, b->spmm_G, kSpmmBS, st, a);
     }
     void gram(const double* U, const double* V0, const double* V1, int gate)
     {
@@ -875,9 +865,7 @@ static cg_block* make_block(cg_ctx* c)
         b->gram_rpw = (c->n + b->gram_G - 1) / b->gram_G;
         const int tiles = (c->n + 15) / 16;
         b->gemm_G = std::max(8, std::min(c->cus * 2, (tiles + 3) / 4) / 8 * 8);
-        const int wpc = c->opts.autotune ? spmm_blocks_per_cu(c) : 4;
-        b->spmm_G = std::max(8, std::min(c->cus * wpc, (c->n + 15) / 16) / 8 * 8);
-        b->spmm_rpb = (c->n + b->spmm_G - 1) / b->spmm_G;
+        b->spmm_G = spmm_grid(c, spmm_blocks_per_cu(c));
         b->res_G = std::min(1024, (c->n + 3) / 4);
         JPCG_HIP(hipMalloc(&b->work, sizeof(double) * nb * 7));
         JPCG_HIP(hipMalloc(&b->part, sizeof(double) * (size_t)b->gram_G * 2 * kBB));

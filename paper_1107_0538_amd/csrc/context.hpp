@@ -9,7 +9,7 @@
 
 namespace jpcg {
 // Zero entries after the last nonzero of the context's col and val arrays
-// (the multi-RHS row products read batches of up to 32 past a row's start).
+// (the multi-RHS row products read batches of up to 9 past a row's start).
 constexpr int kCsrPad = 32;
 }  // namespace jpcg
 
@@ -29,6 +29,7 @@ struct cg_ctx {
     float* dinv32 = nullptr;  // fp32_copy
     float* rowsum32 = nullptr;  // fp32_copy: row sums of A (FP64 sums, FP32 storage)
     double* rowsum64 = nullptr; // fp32_copy: the same row sums in FP64 (FP32-matrix form)
+    int* runs = nullptr;      // which fours of rows the row-block products take together (spmm.hpp)
     std::vector<int> h_rowptr;
 
     // Work vectors for single-RHS solves (one allocation, each vector at a
@@ -84,6 +85,9 @@ namespace jpcg {
 void partition_rows(const std::vector<int>& rowptr, int G, std::vector<int>& out);
 
 int set_error(cg_ctx* c, int code, const std::string& msg);
+
+// Find c->runs, on the context's stream (multi.hip).
+void make_runs(cg_ctx* c);
 
 // Free the multi-RHS solver state of a context (multi.hip).
 void free_multi(cg_ctx* c);

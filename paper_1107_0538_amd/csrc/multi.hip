@@ -2,22 +2,23 @@
 // a row-major N x s block) sharing one sparse product per iteration.
 //
 // Each column follows the FP64 oracle's loop exactly; the columns only share
-// launches.  Layout: lane j of a wave owns column j, so a gathered row of X is
-// one coalesced s * 8-byte load and a CSR value/index is a wave-uniform
-// (scalar) load.  Every column's row sum runs in stored order with separate
-// multiply and add, so spmm's column j equals the sequential CSR product.
+// launches.  spmm's column j equals the sequential CSR product (spmm.hpp).
 //
-// Per iteration (parity P), all captured in hipGraph chunks:
-//   k_mr_pnew       p_j = z_j + beta_j p_j (active), z_j (first step) or p_j
-//                   carried forward (frozen), elementwise
-//   k_mr_direction  q = A p, partials of p_j'q_j (one gathered row of p per
-//                   nonzero)
+// Per iteration, all captured in hipGraph chunks:
+//   k_mr_direction  x_j += alpha_j p_j of the iteration before, then
+//                   p_j = z_j + beta_j p_j (active) or z_j (first step), with
+//                   z = M^-1 r formed here; frozen columns keep their p
+//   k_mr_product    q = A p, partials of p_j'q_j
 //   k_mr_scalars    one workgroup per column: sigma_j, alpha_j, breakdown
-//   k_mr_update     x += alpha p, r -= alpha q, z = M^-1 r, partials of r'z, r'r
+//   k_mr_update     r -= alpha q, partials of r'z, r'r
 //   k_mr_scalars    one workgroup per column: continue-condition, breakdown,
 //                   limit, beta
-// A column whose recurrence residual passes is frozen (its p is carried
-// forward unchanged) and waits; when no column is active the host runs one
+// An iteration moves ten blocks of N x s besides the matrix (x waits for the
+// pass that reads p anyway, z is not stored); 51^3 with 64 columns takes 169 us
+// an iteration (direction 51, product 74, update 31, scalars 5 each) where
+// twelve and a product of 204 us took 354.
+// A column whose recurrence residual passes is frozen and waits; when no
+// column is active the host brings x up to date (k_mr_flush), runs one
 // true-residual check for all waiting columns, exactly the oracle's check,
 // and resumes replaced ones.  Each column's per-workgroup partials are
 // reduced by that column's own workgroup of the scalar kernel, in a fixed
@@ -46,12 +47,14 @@ enum ColStatus : int {
 constexpr int kCols = 64;
 
 struct MrState {
-    int kk;            // iterations completed (the next one is kk + 1, parity (kk + 1) & 1)
-    int pad[3];
+    int kk;            // iterations completed
+    int ran;           // the last direction kernel found an active column
+    int pad[2];
     int status[kCols];
     int iters[kCols];
     int repl[kCols];
     int first[kCols];  // next direction step is the first for this column (p = z)
+    int pend[kCols];   // x += alpha p is still to be done
     double rho[kCols];
     double alpha[kCols];
     double beta[kCols];
@@ -63,48 +66,113 @@ struct MrState {
 
 template <typename T>
 struct MrArgs {
+    RunMap<T> m;
     int n, s;
-    const int* __restrict__ rowptr;
-    const int* __restrict__ col;
-    const T* __restrict__ val;
     const T* __restrict__ dinv;
     const T* B;
     T* X;
     T* R;
-    T* Z;
-    T* P[2];
+    T* P;
     T* Q;
-    int G;
-    int rows_per_block;
-    double* part;  // [G][3][64]
+    int G;         // workgroups of the product kernels
+    int Gv;        // of the elementwise kernels
+    int rows;      // rows per workgroup of the elementwise kernels
+    double* part;  // [3][64][G or Gv]
     MrState* st;
     int maxit;
     double tol;
-    const T* rowsum;  // FP32 solves: row sums of A (FP64 sums) for the row-sum-preserving product
-    int confirm;      // 1: a passed recurrence test is confirmed on b - A x; 0: it ends the column
+    int confirm;   // 1: a passed recurrence test is confirmed on b - A x; 0: it ends the column
 };
 
-// Block-reduce K per-lane quantities over the waves (lane = column) and write
-// them to part[L][k][lane].
-template <int BS, int K>
-__device__ __forceinline__ void mr_block_partials(double (&v)[K], double* part, int L)
+constexpr int kMrBS = 256;
+static_assert(kMrBS == kSpmmBS, "the product kernels share the blocks' reduction");
+
+// The block's sums of K quantities per column, given per wave in lds, to
+// part[k][column][L of G].
+template <int K>
+__device__ __forceinline__ void mr_write_partials(const double (&lds)[kMrBS / kWave][K][kWave], int s, double* part,
+                                                  int L, int G)
 {
-    constexpr int NW = BS / kWave;
-    __shared__ double lds[NW][K][kWave];
-    const int w = threadIdx.x / kWave, lane = threadIdx.x & (kWave - 1);
-#pragma unroll
-    for (int k = 0; k < K; ++k) lds[w][k][lane] = v[k];
     __syncthreads();
-    if (w == 0) {
+    for (int e = threadIdx.x; e < K * kWave; e += kMrBS) {
+        const int k = e / kWave, j = e % kWave;
+        if (j >= s) continue;
+        double t = 0.0;
 #pragma unroll
-        for (int k = 0; k < K; ++k) {
-            double t = 0.0;
-#pragma unroll
-            for (int j = 0; j < NW; ++j) t += lds[j][k][lane];
-            part[((size_t)L * K + k) * kWave + lane] = t;
-        }
+        for (int w = 0; w < kMrBS / kWave; ++w) t += lds[w][k][j];
+        part[(size_t)(k * kWave + j) * G + L] = t;
     }
 }
+
+// From the product's lanes (v[k][0]: the lane's first column, v[k][1]: its second).
+template <int K>
+__device__ __forceinline__ void mr_product_partials(double (&v)[K][2], const SpmmLane& l, double* part, int G)
+{
+    __shared__ double lds[kMrBS / kWave][K][kWave];
+    const int w = threadIdx.x / kWave;
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        const double a = v[k][0] + __shfl_xor(v[k][0], 32), b = v[k][1] + __shfl_xor(v[k][1], 32);
+        if (l.half == 0) {
+            if (l.own1) lds[w][k][l.c] = a;
+            if (l.own2) lds[w][k][l.c + 1] = b;
+        }
+    }
+    mr_write_partials<K>(lds, l.s, part, (int)blockIdx.x, G);
+}
+
+// The elementwise kernels' lanes: V neighbouring columns of a row (2 where s is
+// even, 16-byte accesses; else 1), the least power of two of lanes that holds
+// a row.
+template <int V>
+struct MrLane {
+    int s, P, c, row;  // columns, lanes per row, first column, row of the workgroup's step
+    bool used;
+    __device__ explicit MrLane(int s_) : s(s_), P(1)
+    {
+        while (P * V < s) P *= 2;
+        const int t = threadIdx.x & (P - 1);
+        c = t * V;
+        used = c < s;
+        row = threadIdx.x / P;
+    }
+    __device__ int step() const { return kMrBS / P; }
+    template <bool STREAM = false, typename T>
+    __device__ void load(const T* p, size_t i, T (&x)[V]) const
+    {
+        typedef T vec __attribute__((ext_vector_type(V)));
+        vec v;
+        if constexpr (STREAM) v = __builtin_nontemporal_load((const vec*)(p + i * s + c));
+        else v = *(const vec*)(p + i * s + c);
+#pragma unroll
+        for (int u = 0; u < V; ++u) x[u] = v[u];
+    }
+    template <bool STREAM = false, typename T>
+    __device__ void store(T* p, size_t i, const T (&x)[V]) const
+    {
+        typedef T vec __attribute__((ext_vector_type(V)));
+        vec v;
+#pragma unroll
+        for (int u = 0; u < V; ++u) v[u] = x[u];
+        if constexpr (STREAM) __builtin_nontemporal_store(v, (vec*)(p + i * s + c));
+        else *(vec*)(p + i * s + c) = v;
+    }
+    template <int K>
+    __device__ void partials(double (&v)[K][V], double* part, int L, int G) const
+    {
+        __shared__ double lds[kMrBS / kWave][K][kWave];
+        const int w = threadIdx.x / kWave, lane = threadIdx.x & (kWave - 1);
+#pragma unroll
+        for (int k = 0; k < K; ++k)
+#pragma unroll
+            for (int u = 0; u < V; ++u) {
+                double t = v[k][u];
+                for (int off = P; off < kWave; off *= 2) t += __shfl_xor(t, off);
+                if (lane < P && used) lds[w][k][c + u] = t;
+            }
+        mr_write_partials<K>(lds, s, part, L, G);
+    }
+};
 
 // True in every thread if some column is active (each wave reads the 64
 // statuses once).
@@ -114,180 +182,166 @@ __device__ __forceinline__ bool mr_any_active(const MrState* st)
     return __ballot(st->status[lane] == COL_ACTIVE) != 0ull;
 }
 
-// Row-sum-preserving form of the same row product for the FP32 inner solve:
-// y_i = sum_k a_ik (x_j - x_i) + s_i x_i with s_i the row sum (summed in
-// FP64), so the near-constant modes of A are not lost to FP32 cancellation.
-template <typename T, typename Gather>
-__device__ __forceinline__ T mr_row_diff(const int* __restrict__ rowptr, const int* __restrict__ col,
-                                         const T* __restrict__ val, const T* __restrict__ rowsum, int i, T xi,
-                                         Gather gather)
+// Residual R = B - A X and partials (r'r, r'z, b'b) per column.  mode 0: setup
+// (every column), 1: check (only pending columns are rewritten), 2: report
+// (nothing is written but the partials).
+template <typename T>
+__global__ __launch_bounds__(kMrBS) void k_mr_residual(MrArgs<T> a, int mode)
 {
-    constexpr int B = kMrBatch;
-    static_assert(B <= kCsrPad, "batch reads must stay within the padded arrays");
-    i = __builtin_amdgcn_readfirstlane(i);
-    const int k0 = __builtin_amdgcn_readfirstlane(rowptr[i]), k1 = __builtin_amdgcn_readfirstlane(rowptr[i + 1]);
-    T acc = T(0);
-    for (int k = k0; k < k1; k += B) {
-        T v[B], g[B];
+    const SpmmLane l(a.s);
+    auto write = [&](int j) { return mode == 0 || (mode == 1 && a.st->status[j] == COL_PENDING); };
+    const bool w1 = l.own1 && write(l.c), w2 = l.own2 && write(l.c + 1);
+    double v[3][2] = {};
+    auto take = [&](size_t i, int u, bool wr, T bi, T ax) {
+        const T ri = bi - ax, zi = a.dinv[i] * ri;
+        if (wr) a.R[i * a.s + l.c + u] = ri;
+        v[0][u] += (double)ri * (double)ri;
+        v[1][u] += (double)ri * (double)zi;
+        v[2][u] += (double)bi * (double)bi;
+    };
+    spmm_rows<false, T>(
+        a.m, a.X, l, a.G, [&](int i) { return l.load(a.B, i); },
+        [&](int i, T y1, T y2, Pair<T> b) {
+            take(i + l.half, 0, w1, b.x, y1);
+            take(i + l.half, 1, w2, b.y, y2);
+        },
+        [&](int i, T y) {
+            const T b = a.B[(size_t)i * a.s + l.column()];
+            if (l.half == 0) take(i, 0, w1, b, y);
+            else if (a.s > 1) take(i, 1, w2, b, y);
+        });
+    mr_product_partials<3>(v, l, a.part, a.G);
+}
+
+// x += alpha p where the last iteration left it; p = z + beta p (active), z
+// (first step), unchanged (frozen).  Bound by memory: five blocks, 340 MB at
+// 51^3 with 64 columns in 51 us.
+template <int V, bool S, typename T>
+__global__ __launch_bounds__(kMrBS) void k_mr_direction(MrArgs<T> a)
+{
+    MrState* st = a.st;
+    const bool any = mr_any_active(st);
+    const int L = xcd_logical_block((int)blockIdx.x, a.Gv);
+    if (L == 0 && threadIdx.x == 0) st->ran = any;
+    if (!any) return;
+    const MrLane<V> l(a.s);
+    if (!l.used) return;
+    bool active[V], first[V], pend[V], work = false, late = false;
+    T alpha[V], beta[V];
 #pragma unroll
-        for (int u = 0; u < B; ++u) {
-            v[u] = val[k + u];
-            g[u] = gather(col[k + u]);
+    for (int u = 0; u < V; ++u) {
+        const int j = l.c + u;
+        active[u] = st->status[j] == COL_ACTIVE;
+        first[u] = st->first[j] != 0;
+        pend[u] = st->pend[j] != 0;
+        alpha[u] = (T)st->alpha[j];
+        beta[u] = (T)st->beta[j];
+        work = work || active[u] || pend[u];
+        late = late || pend[u];
+    }
+    if (!work) return;
+    const int rs = min(L * a.rows, a.n), re = min(rs + a.rows, a.n);
+    for (int i = rs + l.row; i < re; i += l.step()) {
+        T r[V], p[V];
+        l.template load<S>(a.R, i, r);
+        l.load(a.P, i, p);
+        const T d = a.dinv[i];
+        if (late) {
+            T x[V];
+            l.template load<S>(a.X, i, x);
+#pragma unroll
+            for (int u = 0; u < V; ++u) x[u] = pend[u] ? fma_t(alpha[u], p[u], x[u]) : x[u];
+            l.template store<S>(a.X, i, x);
         }
 #pragma unroll
-        for (int u = 0; u < B; ++u)
-            if (k + u < k1) acc = fma_t(v[u], g[u] - xi, acc);
+        for (int u = 0; u < V; ++u) {
+            const T z = d * r[u];
+            p[u] = active[u] ? (first[u] ? z : fma_t(beta[u], p[u], z)) : p[u];
+        }
+        l.store(a.P, i, p);
     }
-    return fma_t(rowsum[i], xi, acc);
 }
 
-// Residual R = B - A X with Z = M^-1 R and partials (r'r, r'z, b'b) per column.
-// mode 0: setup (every column; clears both P buffers), 1: check (only pending
-// columns are rewritten), 2: report (nothing is written but the partials).
-template <int BS, typename T>
-__global__ __launch_bounds__(BS) void k_mr_residual(MrArgs<T> a, int mode)
+// x += alpha p where the iterations stopped before their next direction.
+template <typename T>
+__global__ __launch_bounds__(kMrBS) void k_mr_flush(MrArgs<T> a)
 {
-    const int L = mr_logical(a.G);
-    const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
-    const int rs = min(L * a.rows_per_block, a.n), re = min(rs + a.rows_per_block, a.n);
-    const int s = a.s;
-    const bool used = lane < s;
-    const int cl = used ? lane : 0;
-    const bool write = used && (mode == 0 || (mode == 1 && a.st->status[lane] == COL_PENDING));
-    double v[3] = {0.0, 0.0, 0.0};
-    const T* __restrict__ X = a.X;
-    for (int i = rs + w; i < re; i += BS / kWave) {
-        const T ax = mr_row<T>(a.rowptr, a.col, a.val, i, [&](int j) { return X[(size_t)j * s + cl]; });
-        const size_t o = (size_t)i * s + cl;
-        const T bi = a.B[o];
-        const T ri = bi - ax;
-        const T zi = a.dinv[i] * ri;
-        if (write) {
-            a.R[o] = ri;
-            a.Z[o] = zi;
-        }
-        if (mode == 0 && used) {
-            a.P[0][o] = T(0);
-            a.P[1][o] = T(0);
-        }
-        if (used) {
-            v[0] += (double)ri * (double)ri;
-            v[1] += (double)ri * (double)zi;
-            v[2] += (double)bi * (double)bi;
-        }
+    const MrLane<1> l(a.s);
+    if (!l.used || !a.st->pend[l.c]) return;
+    const T alpha = (T)a.st->alpha[l.c];
+    const int L = xcd_logical_block((int)blockIdx.x, a.Gv), rs = min(L * a.rows, a.n), re = min(rs + a.rows, a.n);
+    for (int i = rs + l.row; i < re; i += l.step()) {
+        T x[1], p[1];
+        l.load(a.X, i, x);
+        l.load(a.P, i, p);
+        x[0] = fma_t(alpha, p[0], x[0]);
+        l.store(a.X, i, x);
     }
-    mr_block_partials<BS, 3>(v, a.part, L);
 }
+static __global__ void k_mr_flushed(MrState* st) { st->pend[threadIdx.x] = 0; }
 
-// p_new = z + beta p_old (active), z (first step) or p_old (frozen: carried
-// forward), elementwise over the block's rows.
-template <int BS, typename T>
-__global__ __launch_bounds__(BS) void k_mr_pnew(MrArgs<T> a, int P)
+// q = A p; partials of p'q.
+template <typename T>
+__global__ __launch_bounds__(kMrBS, 5) void k_mr_product(MrArgs<T> a)
 {
-    const MrState* st = a.st;
-    if (!mr_any_active(st)) return;
-    const int L = mr_logical(a.G);
-    const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
-    const int rs = min(L * a.rows_per_block, a.n), re = min(rs + a.rows_per_block, a.n);
-    const int s = a.s;
-    if (lane >= s) return;
-    const int status = st->status[lane];
-    const bool active = status == COL_ACTIVE;
-    const bool first = active && st->first[lane];
-    const T beta = (T)st->beta[lane];
-    const T* __restrict__ Z = a.Z;
-    const T* __restrict__ pold = a.P[P ^ 1];
-    T* __restrict__ pnew = a.P[P];
-    for (int i = rs + w; i < re; i += BS / kWave) {
-        const size_t o = (size_t)i * s + lane;
-        const T po = pold[o];
-        pnew[o] = active ? (first ? Z[o] : fma_t(beta, po, Z[o])) : po;
-    }
+    if (!mr_any_active(a.st)) return;
+    const SpmmLane l(a.s);
+    double v[1][2] = {};
+    spmm_rows<sizeof(T) == 4, T>(
+        a.m, a.P, l, a.G, [&](int i) { return l.load(a.P, i); },
+        [&](int i, T q1, T q2, Pair<T> p) {
+            l.store(a.Q, i, q1, q2);
+            v[0][0] += (double)p.x * (double)q1;
+            v[0][1] += (double)p.y * (double)q2;
+        },
+        [&](int i, T q) {
+            const size_t o = (size_t)i * a.s + l.column();
+            const double pq = (double)a.P[o] * (double)q;
+            if (l.own()) a.Q[o] = q;
+            if (l.half == 0) v[0][0] += pq;
+            else v[0][1] += pq;
+        });
+    mr_product_partials<1>(v, l, a.part, a.G);
 }
 
-// q = A p_new (p_new from k_mr_pnew); partials of p_new'q for active columns.
-template <int BS, typename T>
-__global__ __launch_bounds__(BS) void k_mr_direction(MrArgs<T> a, int P)
-{
-    const MrState* st = a.st;
-    if (!mr_any_active(st)) return;
-    const int L = mr_logical(a.G);
-    const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
-    const int rs = min(L * a.rows_per_block, a.n), re = min(rs + a.rows_per_block, a.n);
-    const int s = a.s;
-    const bool used = lane < s;
-    const int cl = used ? lane : 0;
-    const bool active = used && st->status[lane] == COL_ACTIVE;
-    const T* __restrict__ pnew = a.P[P];
-    double v[1] = {0.0};
-    if constexpr (sizeof(T) == 8) {
-        if (s % 2 == 0) {  // two nonzeros per gather; lane = column pair in the lower half
-            const int c2 = 2 * (lane & 31);
-            const bool pair = lane < 32 && c2 < s;
-            const int cp = c2 < s ? c2 : 0;
-            const bool act0 = pair && st->status[cp] == COL_ACTIVE, act1 = pair && st->status[cp + 1] == COL_ACTIVE;
-            double v0 = 0.0, v1 = 0.0;
-            for (int i = rs + w; i < re; i += BS / kWave) {
-                const size_t o = (size_t)i * s + cp;
-                const double2 qi = mr_row_x2(a.rowptr, a.col, a.val, i, [&](int j) {
-                    return *(const double2*)(pnew + (size_t)j * s + cp);
-                });
-                if (pair) {
-                    *(double2*)(a.Q + o) = qi;
-                    const double2 pi = *(const double2*)(pnew + o);
-                    if (act0) v0 += pi.x * qi.x;
-                    if (act1) v1 += pi.y * qi.y;
-                }
-            }
-            // Back to lane = column for the block partials.
-            const double w0 = __shfl(v0, lane >> 1), w1 = __shfl(v1, lane >> 1);
-            v[0] = (lane & 1) ? w1 : w0;
-            mr_block_partials<BS, 1>(v, a.part, L);
-            return;
-        }
-    }
-    for (int i = rs + w; i < re; i += BS / kWave) {
-        const size_t o = (size_t)i * s + cl;
-        auto gather = [&](int j) { return pnew[(size_t)j * s + cl]; };
-        T qi;
-        if constexpr (sizeof(T) == 4) qi = mr_row_diff<T>(a.rowptr, a.col, a.val, a.rowsum, i, pnew[o], gather);
-        else qi = mr_row<T>(a.rowptr, a.col, a.val, i, gather);
-        if (used) {
-            a.Q[o] = qi;
-            if (active) v[0] += (double)pnew[o] * (double)qi;
-        }
-    }
-    mr_block_partials<BS, 1>(v, a.part, L);
-}
-
-// x += alpha p, r -= alpha q, z = M^-1 r for active columns; partials of r'z, r'r.
-template <int BS, typename T>
-__global__ __launch_bounds__(BS) void k_mr_update(MrArgs<T> a, int P)
+// r -= alpha q for active columns; partials of r'z, r'r.  Three blocks, 204 MB in
+// 31 us.
+template <int V, bool S, typename T>
+__global__ __launch_bounds__(kMrBS) void k_mr_update(MrArgs<T> a)
 {
     MrState* st = a.st;
     if (!mr_any_active(st)) return;
-    const int L = mr_logical(a.G);
-    const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
-    const int rs = min(L * a.rows_per_block, a.n), re = min(rs + a.rows_per_block, a.n);
-    const int s = a.s;
-    const bool active = lane < s && st->status[lane] == COL_ACTIVE;
+    const int L = xcd_logical_block((int)blockIdx.x, a.Gv);
     if (L == 0 && threadIdx.x == 0) st->kk += 1;  // this iteration is being done
-    const T alpha = (T)st->alpha[lane < s ? lane : 0];
-    const T* __restrict__ p = a.P[P];
-    double v[2] = {0.0, 0.0};
-    if (active) {
-        for (int i = rs + w; i < re; i += BS / kWave) {
-            const size_t o = (size_t)i * s + lane;
-            a.X[o] = fma_t(alpha, p[o], a.X[o]);
-            const T ri = fma_t(-alpha, a.Q[o], a.R[o]);
-            a.R[o] = ri;
-            const T zi = a.dinv[i] * ri;
-            a.Z[o] = zi;
-            v[0] += (double)ri * (double)zi;
-            v[1] += (double)ri * (double)ri;
+    const MrLane<V> l(a.s);
+    bool active[V], work = false;
+    T alpha[V];
+#pragma unroll
+    for (int u = 0; u < V; ++u) {
+        const int j = l.used ? l.c + u : 0;
+        active[u] = l.used && st->status[j] == COL_ACTIVE;
+        alpha[u] = (T)st->alpha[j];
+        work = work || active[u];
+    }
+    double v[2][V] = {};
+    if (work) {
+        const int rs = min(L * a.rows, a.n), re = min(rs + a.rows, a.n);
+        for (int i = rs + l.row; i < re; i += l.step()) {
+            T r[V], q[V];
+            l.template load<S>(a.R, i, r);
+            l.load(a.Q, i, q);
+            const T d = a.dinv[i];
+#pragma unroll
+            for (int u = 0; u < V; ++u) {
+                r[u] = active[u] ? fma_t(-alpha[u], q[u], r[u]) : r[u];
+                const T z = d * r[u];
+                v[0][u] += (double)r[u] * (double)z;
+                v[1][u] += (double)r[u] * (double)r[u];
+            }
+            l.template store<S>(a.R, i, r);
         }
     }
-    mr_block_partials<BS, 2>(v, a.part, L);
+    l.partials(v, a.part, L, a.Gv);
 }
 
 enum MrPhase : int { MR_SETUP = 0, MR_SIGMA = 1, MR_ITER = 2, MR_CHECK = 3, MR_REPORT = 4 };
@@ -301,7 +355,7 @@ __device__ __forceinline__ void mr_column_sum(const double* part, int G, int j, 
     for (int k = 0; k < K; ++k) out[k] = 0.0;
     for (int g = threadIdx.x; g < G; g += BS) {
 #pragma unroll
-        for (int k = 0; k < K; ++k) out[k] += part[((size_t)g * K + k) * kWave + j];
+        for (int k = 0; k < K; ++k) out[k] += part[(size_t)(k * kWave + j) * G + g];
     }
     block_sum<BS, K>(out, lds);
 }
@@ -319,6 +373,7 @@ __global__ __launch_bounds__(256) void k_mr_scalars(MrArgs<T> a, int phase)
         return;
     }
     int status = st->status[j];
+    if (phase == MR_SIGMA && status != COL_ACTIVE && st->ran && threadIdx.x == 0) st->pend[j] = 0;
     if ((phase == MR_SIGMA || phase == MR_ITER) && status != COL_ACTIVE) return;
     if (phase == MR_CHECK && status != COL_PENDING) return;
     double g[3] = {0.0, 0.0, 0.0};
@@ -328,7 +383,7 @@ __global__ __launch_bounds__(256) void k_mr_scalars(MrArgs<T> a, int phase)
         g[0] = t[0];
     } else if (phase == MR_ITER) {
         double t[2];
-        mr_column_sum<256, 2>(a.part, a.G, j, t, lds);
+        mr_column_sum<256, 2>(a.part, a.Gv, j, t, lds);
         g[0] = t[0];
         g[1] = t[1];
     } else {
@@ -342,6 +397,7 @@ __global__ __launch_bounds__(256) void k_mr_scalars(MrArgs<T> a, int phase)
         st->first[j] = 1;
         st->beta[j] = 0.0;
         st->alpha[j] = 0.0;
+        st->pend[j] = 0;
         const double nb = sqrt(g[2]);
         st->nb[j] = nb;
         st->thr[j] = a.tol * nb;
@@ -359,8 +415,10 @@ __global__ __launch_bounds__(256) void k_mr_scalars(MrArgs<T> a, int phase)
         }
     } else if (phase == MR_SIGMA) {
         const double sigma = g[0];
-        if (!(sigma > 0.0) || !isfinite(sigma)) status = COL_BREAKDOWN;
-        else st->alpha[j] = st->rho[j] / sigma;
+        const bool ok = sigma > 0.0 && isfinite(sigma);
+        if (ok) st->alpha[j] = st->rho[j] / sigma;
+        else status = COL_BREAKDOWN;
+        st->pend[j] = ok;  // the direction kernel has done the last one
     } else if (phase == MR_ITER) {
         // g = (r'z, r'r) after the update: the oracle's order of tests.
         st->iters[j] += 1;
@@ -438,20 +496,19 @@ __global__ void k_mr_zero_cols(MrArgs<T> a)
         a.X[(size_t)i * a.s + lane] = T(0);
 }
 
-constexpr int kMrBS = 512;
-
 }  // namespace jpcg
 
 // Multi-RHS solver state hanging off a context, for one block width s and
 // one precision (FP64, or the FP32 inner solver of the mixed form).
 struct cg_multi {
-    int s = 0, G = 0, chunk = 0;
+    int s = 0, chunk = 0;
+    bool stream = false;   // R and X pass the last-level cache by
     bool fp32 = false;
-    void* work = nullptr;  // R, Z, P0, P1, Q, and the solver's own B, X: 7 N s values
+    void* work = nullptr;  // R, P, Q, and the solver's own B, X: 5 N s values
     double* part = nullptr;
     jpcg::MrState* st = nullptr;
     jpcg::MrState* hst = nullptr;
-    hipGraphExec_t exec[2] = {nullptr, nullptr};
+    hipGraphExec_t exec = nullptr;
     hipEvent_t ev = nullptr;
     jpcg::MrArgs<double> args{};
     jpcg::MrArgs<float> args32{};
@@ -462,8 +519,7 @@ namespace jpcg {
 static void destroy_multi(cg_multi* m)
 {
     if (!m) return;
-    for (auto& e : m->exec)
-        if (e) (void)hipGraphExecDestroy(e);
+    if (m->exec) (void)hipGraphExecDestroy(m->exec);
     if (m->ev) (void)hipEventDestroy(m->ev);
     if (m->work) (void)hipFree(m->work);
     if (m->part) (void)hipFree(m->part);
@@ -484,11 +540,47 @@ MrArgs<double>& margs<double>(cg_multi* m) { return m->args; }
 template <>
 MrArgs<float>& margs<float>(cg_multi* m) { return m->args32; }
 
+// The words of spmm.hpp's fours of rows.
+static __global__ __launch_bounds__(256) void k_find_runs(int n, const int* __restrict__ rowptr,
+                                                          const int* __restrict__ col, int* __restrict__ runs)
+{
+    const int g = blockIdx.x * 256 + threadIdx.x, i0 = g * kRunRows;
+    if (i0 >= n) return;
+    const int rows = min(kRunRows, n - i0), k0 = rowptr[i0], len = rowptr[i0 + 1] - k0;
+    int most = len;
+    for (int r = 1; r < rows; ++r) most = max(most, rowptr[i0 + r + 1] - rowptr[i0 + r]);
+    bool ok = rows == kRunRows && len % 3 == 0 && len <= kSpmmShort;
+    for (int r = 1; ok && r < kRunRows; ++r) ok = rowptr[i0 + r + 1] - rowptr[i0 + r] == len;
+    for (int e = 0; ok && e < len; ++e) {
+        const int c = col[k0 + e / 3 * 3] + e % 3;
+        for (int r = 0; ok && r < kRunRows; ++r) ok = col[k0 + r * len + e] == c + r;
+    }
+    runs[g] = ok && len ? len : most <= kSpmmShort ? SPMM_SHORT : SPMM_LONG;
+}
+
+void make_runs(cg_ctx* c)
+{
+    const int fours = (c->n + kRunRows - 1) / kRunRows;
+    JPCG_HIP(hipMalloc(&c->runs, sizeof(int) * fours));
+    k_find_runs<<<(fours + 255) / 256, 256, 0, c->stream>>>(c->n, c->rowptr, c->col, c->runs);
+    JPCG_HIP(hipGetLastError());
+}
+
+RunMap<double> run_map(const cg_ctx* c) { return {c->n, c->runs, c->rowptr, c->col, c->val, nullptr}; }
+
+// Y = A X (row-major N x s).
+__global__ __launch_bounds__(kSpmmBS, 6) void k_spmm(RunMap<double> m, const double* __restrict__ X,
+                                                  double* __restrict__ Y, int s, int G)
+{
+    spmm_block(m, X, Y, s, G);
+}
+
 // The multi-column product's grid: workgroups per CU.  Without autotune the
-// default (2); with it, the first use times the 64-column product at 1, 2, 3,
-// 4, 6 and 8 workgroups per CU (rows split evenly, XCD-aware order) and keeps
-// the fastest.
-constexpr int kSpmmDefaultWpc = 2;
+// default, 5, what the solver's product has registers for (51^3, 64 columns: 169
+// us an iteration with 5, 173 with 4, 175 with 6, 170 with 10); with it, the first
+// use times the 64-column product at 1, 2, 3, 4, 6 and 8 workgroups per CU and
+// keeps the fastest.
+constexpr int kSpmmDefaultWpc = 5;
 
 int spmm_blocks_per_cu(cg_ctx* c)
 {
@@ -506,16 +598,14 @@ int spmm_blocks_per_cu(cg_ctx* c)
         JPCG_HIP(hipMemsetAsync(X, 0, nb, c->stream));
         JPCG_HIP(hipEventCreate(&e0));
         JPCG_HIP(hipEventCreate(&e1));
-        int n = c->n;
         for (int w : {1, 2, 3, 4, 6, 8}) {
-            int G = std::max(8, std::min(c->cus * w, (c->n + 15) / 16) / 8 * 8);
-            int rpb = (c->n + G - 1) / G;
-            void* args[] = {&n, (void*)&s, &c->rowptr, &c->col, &c->val, &X, &Y, &rpb, &G};
-            JPCG_HIP(hipLaunchKernel((const void*)k_spmm<512, double>, dim3(G), dim3(512), args, 0, c->stream));
+            const int G = spmm_grid(c, w);
+            k_spmm<<<G, kSpmmBS, 0, c->stream>>>(run_map(c), X, Y, s, G);
             JPCG_HIP(hipEventRecord(e0, c->stream));
             constexpr int kReps = 8;
             for (int r = 0; r < kReps; ++r)
-                JPCG_HIP(hipLaunchKernel((const void*)k_spmm<512, double>, dim3(G), dim3(512), args, 0, c->stream));
+                k_spmm<<<G, kSpmmBS, 0, c->stream>>>(run_map(c), X, Y, s, G);
+            JPCG_HIP(hipGetLastError());
             JPCG_HIP(hipEventRecord(e1, c->stream));
             JPCG_HIP(hipEventSynchronize(e1));
             float ms = 0.f;
@@ -541,6 +631,14 @@ int spmm_blocks_per_cu(cg_ctx* c)
     return c->spmm_wpc = best_w;
 }
 
+// Workgroups per CU of the elementwise kernels.
+constexpr int kMrVectorWpc = 4;
+// Blocks and matrix together from which on R and X are read and written past
+// the 256 MB last-level cache, which then keeps the matrix, P and Q: at 51^3
+// with 44, 48, 52 and 64 columns (268, 298, 319 and 383 MB) 146, 149, 155 and
+// 169 us per iteration against 139, 149, 168 and 205 through the cache.
+constexpr double kMrStreamBytes = 300e6;
+
 template <typename T>
 static cg_multi* make_multi(cg_ctx* c, int s)
 {
@@ -550,39 +648,34 @@ static cg_multi* make_multi(cg_ctx* c, int s)
         m->s = s;
         m->fp32 = sizeof(T) == 4;
         m->chunk = 8;
-        m->G = std::max(8, std::min(c->cus * wpc, (c->n + 63) / 64) / 8 * 8);
         const size_t ns = (size_t)c->n * s;
-        JPCG_HIP(hipMalloc(&m->work, sizeof(T) * ns * 7));
-        JPCG_HIP(hipMalloc(&m->part, sizeof(double) * (size_t)m->G * 3 * kWave));
+        m->stream = sizeof(T) * 5.0 * (double)ns + (sizeof(T) + 4.0) * (double)c->nnz > kMrStreamBytes;
+        MrArgs<T>& a = margs<T>(m);
+        a.G = spmm_grid(c, wpc);
+        a.Gv = std::max(8, std::min(c->cus * kMrVectorWpc, (c->n + 63) / 64) / 8 * 8);
+        a.rows = (c->n + a.Gv - 1) / a.Gv;
+        JPCG_HIP(hipMalloc(&m->work, sizeof(T) * ns * 5));
+        JPCG_HIP(hipMalloc(&m->part, sizeof(double) * (size_t)std::max(a.G, a.Gv) * 3 * kWave));
         JPCG_HIP(hipMalloc(&m->st, sizeof(MrState)));
         JPCG_HIP(hipHostMalloc(&m->hst, sizeof(MrState), hipHostMallocDefault));
         JPCG_HIP(hipEventCreateWithFlags(&m->ev, hipEventDisableTiming));
-        JPCG_HIP(hipMemsetAsync(m->work, 0, sizeof(T) * ns * 7, c->stream));
+        JPCG_HIP(hipMemsetAsync(m->work, 0, sizeof(T) * ns * 5, c->stream));
         JPCG_HIP(hipMemsetAsync(m->st, 0, sizeof(MrState), c->stream));
-        MrArgs<T>& a = margs<T>(m);
         T* w = (T*)m->work;
         a.n = c->n;
         a.s = s;
-        a.rowptr = c->rowptr;
-        a.col = c->col;
         if constexpr (sizeof(T) == 4) {
-            a.val = c->val32;
+            a.m = {c->n, c->runs, c->rowptr, c->col, c->val32, c->rowsum32};
             a.dinv = c->dinv32;
-            a.rowsum = c->rowsum32;
         } else {
-            a.val = c->val;
+            a.m = run_map(c);
             a.dinv = c->dinv;
-            a.rowsum = nullptr;
         }
         a.R = w;
-        a.Z = w + ns;
-        a.P[0] = w + 2 * ns;
-        a.P[1] = w + 3 * ns;
-        a.Q = w + 4 * ns;
-        a.B = w + 5 * ns;
-        a.X = w + 6 * ns;
-        a.G = m->G;
-        a.rows_per_block = (c->n + m->G - 1) / m->G;
+        a.P = w + ns;
+        a.Q = w + 2 * ns;
+        a.B = w + 3 * ns;
+        a.X = w + 4 * ns;
         a.part = m->part;
         a.st = m->st;
         a.maxit = c->n;
@@ -596,37 +689,40 @@ static cg_multi* make_multi(cg_ctx* c, int s)
     }
 }
 
-// (Re)capture the chunk graphs; tol, maxit and confirm are kernel arguments.
+// (Re)capture the chunk graph; tol, maxit and confirm are kernel arguments.
 template <typename T>
 static void capture_multi(cg_multi* m)
 {
-    for (auto& e : m->exec)
-        if (e) {
-            (void)hipGraphExecDestroy(e);
-            e = nullptr;
-        }
+    if (m->exec) (void)hipGraphExecDestroy(m->exec);
+    m->exec = nullptr;
     MrArgs<T>& args = margs<T>(m);
+    const bool pairs = args.s % 2 == 0;
+    const void* const directions[2][2] = {
+        {(const void*)k_mr_direction<1, false, T>, (const void*)k_mr_direction<1, true, T>},
+        {(const void*)k_mr_direction<2, false, T>, (const void*)k_mr_direction<2, true, T>}};
+    const void* const updates[2][2] = {
+        {(const void*)k_mr_update<1, false, T>, (const void*)k_mr_update<1, true, T>},
+        {(const void*)k_mr_update<2, false, T>, (const void*)k_mr_update<2, true, T>}};
+    const void *direction = directions[pairs][m->stream], *update = updates[pairs][m->stream];
     hipStream_t cap;
     JPCG_HIP(hipStreamCreateWithFlags(&cap, hipStreamNonBlocking));
-    for (int par = 0; par < 2; ++par) {
-        hipGraph_t graph;
-        JPCG_HIP(hipStreamBeginCapture(cap, hipStreamCaptureModeThreadLocal));
-        for (int it = 0; it < m->chunk; ++it) {
-            int P = (par + it) & 1, ph_sig = MR_SIGMA, ph_it = MR_ITER;
-            void* a0[] = {&args, &P};
-            mr_launch((const void*)k_mr_pnew<kMrBS, T>, m->G, kMrBS, cap, a0);
-            mr_launch((const void*)k_mr_direction<kMrBS, T>, m->G, kMrBS, cap, a0);
-            void* a1[] = {&args, &ph_sig};
-            mr_launch((const void*)k_mr_scalars<T>, kCols, 256, cap, a1);
-            mr_launch((const void*)k_mr_update<kMrBS, T>, m->G, kMrBS, cap, a0);
-            void* a2[] = {&args, &ph_it};
-            mr_launch((const void*)k_mr_scalars<T>, kCols, 256, cap, a2);
-        }
-        JPCG_HIP(hipStreamEndCapture(cap, &graph));
-        hipError_t e = hipGraphInstantiate(&m->exec[par], graph, nullptr, nullptr, 0);
-        (void)hipGraphDestroy(graph);
-        JPCG_HIP(e);
+    hipGraph_t graph;
+    JPCG_HIP(hipStreamBeginCapture(cap, hipStreamCaptureModeThreadLocal));
+    for (int it = 0; it < m->chunk; ++it) {
+        int ph_sig = MR_SIGMA, ph_it = MR_ITER;
+        void* a0[] = {&args};
+        mr_launch(direction, args.Gv, kMrBS, cap, a0);
+        mr_launch((const void*)k_mr_product<T>, args.G, kMrBS, cap, a0);
+        void* a1[] = {&args, &ph_sig};
+        mr_launch((const void*)k_mr_scalars<T>, kCols, 256, cap, a1);
+        mr_launch(update, args.Gv, kMrBS, cap, a0);
+        void* a2[] = {&args, &ph_it};
+        mr_launch((const void*)k_mr_scalars<T>, kCols, 256, cap, a2);
     }
+    JPCG_HIP(hipStreamEndCapture(cap, &graph));
+    hipError_t e = hipGraphInstantiate(&m->exec, graph, nullptr, nullptr, 0);
+    (void)hipGraphDestroy(graph);
+    JPCG_HIP(e);
     JPCG_HIP(hipStreamDestroy(cap));
 }
 
@@ -657,7 +753,7 @@ static cg_multi* multi_for(cg_ctx* c, int s, double tol, int maxit, int confirm)
         slot = make_multi<T>(c, s);
     }
     MrArgs<T>& a = margs<T>(slot);
-    if (!slot->exec[0] || a.tol != tol || a.maxit != maxit || a.confirm != confirm) {
+    if (!slot->exec || a.tol != tol || a.maxit != maxit || a.confirm != confirm) {
         a.tol = tol;
         a.maxit = maxit;
         a.confirm = confirm;
@@ -677,45 +773,45 @@ static MrState run_multi(cg_ctx* c, cg_multi* m)
     const int s = m->s;
     int mode = 0, ph = MR_SETUP;
     void* ra[] = {&args, &mode};
-    mr_launch((const void*)k_mr_residual<kMrBS, T>, m->G, kMrBS, st, ra);
+    mr_launch((const void*)k_mr_residual<T>, args.G, kMrBS, st, ra);
     void* sa[] = {&args, &ph};
     mr_launch((const void*)k_mr_scalars<T>, kCols, 256, st, sa);
     void* za[] = {&args};
     mr_launch((const void*)k_mr_zero_cols<T>, 256, 256, st, za);
-    int next = 1;
+    auto flush = [&] {
+        void* fa[] = {&args};
+        mr_launch((const void*)k_mr_flush<T>, args.Gv, kMrBS, st, fa);
+        k_mr_flushed<<<1, kCols, 0, st>>>(m->st);
+        JPCG_HIP(hipGetLastError());
+    };
     const long long guard = 4LL * args.maxit + 64;
     long long launched = 0;
     while (true) {
         MrState h = mr_read(c, m);
-        // Iterations after the last column stopped returned early, so the
-        // next iteration's parity comes from the device's count, not from
-        // the number of iterations launched.
-        next = h.kk + 1;
         bool active = false, pending = false;
         for (int j = 0; j < s; ++j) {
             active = active || h.status[j] == COL_ACTIVE;
             pending = pending || h.status[j] == COL_PENDING;
         }
         if (!active) {
+            flush();
             if (!pending) break;
             mode = 1;
             ph = MR_CHECK;
-            mr_launch((const void*)k_mr_residual<kMrBS, T>, m->G, kMrBS, st, ra);
+            mr_launch((const void*)k_mr_residual<T>, args.G, kMrBS, st, ra);
             mr_launch((const void*)k_mr_scalars<T>, kCols, 256, st, sa);
             continue;
         }
         if (launched > guard) throw HipError{hipErrorUnknown, "multi-RHS solver did not stop"};
         // Two chunks per poll keep the device busy while the host reads.
-        JPCG_HIP(hipGraphLaunch(m->exec[next & 1], st));
-        next += m->chunk;
-        JPCG_HIP(hipGraphLaunch(m->exec[next & 1], st));
-        next += m->chunk;
+        JPCG_HIP(hipGraphLaunch(m->exec, st));
+        JPCG_HIP(hipGraphLaunch(m->exec, st));
         launched += 2 * m->chunk;
     }
     if (args.confirm) {
         mode = 2;
         ph = MR_REPORT;
-        mr_launch((const void*)k_mr_residual<kMrBS, T>, m->G, kMrBS, st, ra);
+        mr_launch((const void*)k_mr_residual<T>, args.G, kMrBS, st, ra);
         mr_launch((const void*)k_mr_scalars<T>, kCols, 256, st, sa);
     }
     return mr_read(c, m);
@@ -739,12 +835,9 @@ int spmm(cg_ctx* c, const double* X, double* Y, int32_t s)
     if (!c) return CG_EINVAL;
     if (!X || !Y || X == Y || s < 1 || s > kCols) return set_error(c, CG_EINVAL, "spmm: bad arguments");
     try {
-        const int wpc = c->opts.autotune ? spmm_blocks_per_cu(c) : 4;
-        const int G = std::max(8, std::min(c->cus * wpc, (c->n + 15) / 16) / 8 * 8);
-        const int rpb = (c->n + G - 1) / G;
-        int n = c->n;
-        void* args[] = {&n, &s, &c->rowptr, &c->col, &c->val, &X, &Y, (void*)&rpb, (void*)&G};
-        mr_launch((const void*)k_spmm<kMrBS, double>, G, kMrBS, c->stream, args);
+        const int G = spmm_grid(c, spmm_blocks_per_cu(c));
+        k_spmm<<<G, kSpmmBS, 0, c->stream>>>(run_map(c), X, Y, s, G);
+        JPCG_HIP(hipGetLastError());
         return 0;
     } catch (const HipError& e) {
         return set_error(c, CG_EHIP, std::string("spmm: ") + e.what + ": " + hipGetErrorString(e.code));
@@ -823,7 +916,7 @@ int cg_solve_multi_mixed(cg_ctx* c, const double* B, double* X, int32_t s, doubl
             // r = b - A x in FP64 and the per-column tests.
             int mode = 0, ph = MR_SETUP;
             void* ra[] = {&m64->args, &mode};
-            mr_launch((const void*)k_mr_residual<kMrBS, double>, m64->G, kMrBS, st, ra);
+            mr_launch((const void*)k_mr_residual<double>, m64->args.G, kMrBS, st, ra);
             void* sa[] = {&m64->args, &ph};
             mr_launch((const void*)k_mr_scalars<double>, kCols, 256, st, sa);
             if (outer == 0) {  // x_j = 0 for b_j = 0

@@ -1024,7 +1024,7 @@ static void free_ctx(cg_ctx* c)
     free_block(c);
     if (c->mixed_dev) (void)hipFree(c->mixed_dev);
     if (c->mixed_host) (void)hipHostFree(c->mixed_host);
-    void* ptrs[] = {c->rowptr, c->col, c->val, c->dinv, c->val32, c->dinv32, c->rowsum32, c->rowsum64, c->work[0],
+    void* ptrs[] = {c->rowptr, c->col, c->val, c->dinv, c->val32, c->dinv32, c->rowsum32, c->rowsum64, c->runs, c->work[0],
                     c->hist};
     for (void* p : ptrs)
         if (p) (void)hipFree(p);
@@ -1147,6 +1147,7 @@ int cg_create(const cg_csr* A, const cg_opts* opts, void* hip_stream, cg_ctx** o
             rowsum_kernel<<<(n + 255) / 256, 256, 0, c->stream>>>(n, c->rowptr, c->val, c->rowsum32, c->rowsum64);
             JPCG_HIP(hipGetLastError());
         }
+        make_runs(c);
         int* bad = nullptr;
         JPCG_HIP(hipMalloc(&bad, sizeof(int)));
         JPCG_HIP(hipMemsetAsync(bad, 0, sizeof(int), c->stream));

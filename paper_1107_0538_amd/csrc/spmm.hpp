@@ -1,132 +1,339 @@
 // Row-block sparse products over row-major N x s blocks (s <= 64), shared by
-// the multi-RHS and block forms: lane j of a wave owns column j, so a
-// gathered row of X is one coalesced s * 8-byte load and a CSR value/index is
-// a wave-uniform (scalar) load.  Every column's row sum runs in stored order
+// the multi-RHS and block forms.  Every column's row sum runs in stored order
 // with separate multiply and add, so column j equals the sequential CSR
 // product.
+//
+// A wave takes four rows at a time.  Rows of a structured matrix next to each
+// other read runs of neighbouring columns: where the four rows' entries are
+// runs of three, each row's run one column further than the row's before
+// (c, c+1, c+2 in the first, c+1, c+2, c+3 in the second ...), the four rows'
+// twelve entries read six rows of X, and are added from registers.  Which fours
+// are such is found once per matrix (k_find_runs, a word per four rows); other
+// rows of up to 32 entries are added side by side, four at a time, with a
+// gather per entry, and longer ones one after the other.
+//
+// What bounds it: the vector-memory address path (16 clocks per instruction,
+// whatever its width) and the latency of the matrix, about equally.  A gather
+// therefore fetches two rows of X with 16 bytes per lane, which
+// v_permlane32_swap turns into a lane per column; and four rows' values and
+// columns are loaded at once, across the lanes and a step ahead, and broadcast
+// by v_readlane.  Product at 51^3, 64 columns (41 MB matrix, 68 MB in, 68 MB
+// out), all in the last-level cache: 204 us with a row per wave and two of the
+// row's entries per gather; 121 with a row per wave in the order below and
+// values through the scalar cache; 77 with four rows, 8 bytes per lane; 59 with
+// 16 bytes per lane and the matrix still through the scalar cache, but 107 when
+// the matrix comes from memory, one miss after the other; as it is 66, and 83
+// from memory.
+//
+// Order: the waves of one XCD walk its share of the rows side by side, so the
+// rows of X between a row's first and last entry (two planes of a lattice, 2.7
+// MB at 51^3) stay in that XCD's 4 MB L2 while they are needed.
 #pragma once
+
+#include <algorithm>
 
 #include "context.hpp"
 
 namespace jpcg {
 
-__device__ __forceinline__ int mr_logical(int G) { return xcd_logical_block((int)blockIdx.x, G); }
+constexpr int kRunRows = 4;   // rows of a wave's step
+constexpr int kSpmmBS = 256;
+constexpr int kSpmmXcds = 8;
 
+template <typename T>
+struct alignas(sizeof(T)) Pair {  // two neighbouring columns; s may be odd
+    T x, y;
+};
 
-// Nonzeros of a row whose gathers a wave issues together: 16 with one
-// column per lane, 32 (16 per half-wave) with two (mr_row_x2).
-constexpr int kMrBatch = 16;
-constexpr int kMrBatch2 = 32;
+// a's upper half of the wave against b's lower half.
+__device__ __forceinline__ void swap_halves(double& a, double& b)
+{
+    const auto lo = __builtin_amdgcn_permlane32_swap(__double2loint(a), __double2loint(b), false, false);
+    const auto hi = __builtin_amdgcn_permlane32_swap(__double2hiint(a), __double2hiint(b), false, false);
+    a = __hiloint2double((int)hi[0], (int)lo[0]);
+    b = __hiloint2double((int)hi[1], (int)lo[1]);
+}
+__device__ __forceinline__ void swap_halves(float& a, float& b)
+{
+    const auto w = __builtin_amdgcn_permlane32_swap(__float_as_int(a), __float_as_int(b), false, false);
+    a = __int_as_float((int)w[0]);
+    b = __int_as_float((int)w[1]);
+}
 
-// One wave: y_lane = sum_k a_ik x[col_k][lane] for row i in stored order,
-// without contraction, so each column is the sequential CSR row sum.
-template <typename T, typename Gather>
-__device__ __forceinline__ T mr_row(const int* __restrict__ rowptr, const int* __restrict__ col,
-                                    const T* __restrict__ val, int i, Gather gather)
+// A lane's columns.  In pairs, lane l of either half holds columns c and c + 1
+// of the half's row; in the form for sums it holds column c + half.  Lanes past
+// the last column repeat it, and in a block of odd width the last pair repeats
+// one column: first() and second() say which of a lane's columns are its own.
+struct SpmmLane {
+    int s, half, c;
+    bool own1, own2;
+    __device__ explicit SpmmLane(int s_) : s(s_)
+    {
+        const int l = threadIdx.x & 31;
+        half = (threadIdx.x >> 5) & 1;
+        c = s > 1 ? min(2 * l, s - 2) : 0;
+        own1 = 2 * l == c && (s > 1 || half == 0);
+        own2 = s > 1 && 2 * l < s;
+    }
+    __device__ bool own() const { return half ? own2 : own1; }  // of the form for sums
+    __device__ int column() const { return s > 1 ? c + half : 0; }
+    // Pairs of rows i and i + 1.
+    template <typename T>
+    __device__ Pair<T> load(const T* p, size_t i) const
+    {
+        return *(const Pair<T>*)(p + (i + half) * s + c);
+    }
+    template <typename T>
+    __device__ void store(T* p, size_t i, T a, T b) const
+    {
+        T* q = p + (i + half) * s + c;
+        if (own2) *(Pair<T>*)q = Pair<T>{a, b};
+    }
+};
+
+template <typename T>
+struct RunMap {
+    int n;
+    const int* __restrict__ runs;  // per four rows: entries of each if they are runs, else SPMM_SHORT or SPMM_LONG
+    const int* __restrict__ rowptr;
+    const int* __restrict__ col;
+    const T* __restrict__ val;
+    const T* __restrict__ rowsum;  // row-sum-preserving form
+};
+// Fours of rows that are not runs: no row longer than a half wave, or some.
+constexpr int SPMM_SHORT = 0, SPMM_LONG = -1;
+constexpr int kSpmmShort = 32;
+
+template <bool DIFF, typename T>
+__device__ __forceinline__ T spmm_add(T acc, T v, T y, T xi)
 {
 #pragma clang fp contract(off)
-    // Batches of kMrBatch nonzeros: the (wave-uniform) indices and values
-    // are loaded, then all the batch's gathers are in flight together; the
-    // tail batch reads past the row's end (into the next row or the arrays'
-    // zero pad of kCsrPad entries) and skips those slots, so a 27-entry row
-    // takes two gather round trips.
-    constexpr int B = kMrBatch;
-    static_assert(B <= kCsrPad, "batch reads must stay within the padded arrays");
-    // The row is the same in every lane: make that explicit so that the
-    // row's indices and values come through the scalar cache.
-    i = __builtin_amdgcn_readfirstlane(i);
-    const int k0 = __builtin_amdgcn_readfirstlane(rowptr[i]), k1 = __builtin_amdgcn_readfirstlane(rowptr[i + 1]);
-    T acc = T(0);
-    for (int k = k0; k < k1; k += B) {
-        T v[B], g[B];
-#pragma unroll
-        for (int u = 0; u < B; ++u) {
-            v[u] = val[k + u];
-            g[u] = gather(col[k + u]);
-        }
-#pragma unroll
-        for (int u = 0; u < B; ++u)
-            if (k + u < k1) acc = acc + v[u] * g[u];
-    }
-    return acc;
+    if constexpr (DIFF) return fma_t(v, y - xi, acc);
+    else return acc + v * y;
 }
 
-// The same row product with two nonzeros per gather instruction (FP64, s
-// even): lane l takes columns 2 (l mod 32) and 2 (l mod 32) + 1 of the
-// nonzeros at even (lower half) or odd (upper half) positions of each batch,
-// so one 16-byte load per lane fetches two nonzeros' rows of X.  This
-// gather-heavy product is limited by the per-CU address path, which handles a
-// 16-byte lane as fast as an 8-byte one, not by bytes.  Products are rounded
-// on their own; the upper half hands its products to the lower half, which
-// adds them in stored order, so both columns are the sequential CSR row sums
-// bitwise (as mr_row).  The sums are valid in the lower half's lanes.
-template <typename Gather2>
-__device__ __forceinline__ double2 mr_row_x2(const int* __restrict__ rowptr, const int* __restrict__ col,
-                                             const double* __restrict__ val, int i, Gather2 gather2)
+__device__ __forceinline__ int lane_value(int v, int l) { return __builtin_amdgcn_readlane(v, l); }
+__device__ __forceinline__ float lane_value(float v, int l)
 {
-#pragma clang fp contract(off)
-    constexpr int B = kMrBatch2;  // nonzeros per batch, half of them per half-wave
-    static_assert(B <= kCsrPad, "batch reads must stay within the padded arrays");
-    i = __builtin_amdgcn_readfirstlane(i);
-    const int k0 = __builtin_amdgcn_readfirstlane(rowptr[i]), k1 = __builtin_amdgcn_readfirstlane(rowptr[i + 1]);
-    const bool upper = (threadIdx.x & 32) != 0;
-    double a0 = 0.0, a1 = 0.0;
-    for (int k = k0; k < k1; k += B) {
-        double v[B / 2];
-        double2 g[B / 2];
-#pragma unroll
-        for (int u = 0; u < B / 2; ++u) {
-            const int ke = k + 2 * u;
-            const double ve = val[ke], vo = val[ke + 1];
-            const int ce = col[ke], co = col[ke + 1];
-            v[u] = upper ? vo : ve;
-            g[u] = gather2(upper ? co : ce);
-        }
-#pragma unroll
-        for (int u = 0; u < B / 2; ++u) {
-            const double p0 = v[u] * g[u].x, p1 = v[u] * g[u].y;
-            const double q0 = __shfl_xor(p0, 32), q1 = __shfl_xor(p1, 32);  // the other half's products
-            if (k + 2 * u < k1) {
-                a0 = a0 + p0;
-                a1 = a1 + p1;
-            }
-            if (k + 2 * u + 1 < k1) {
-                a0 = a0 + q0;
-                a1 = a1 + q1;
-            }
-        }
-    }
-    return make_double2(a0, a1);
+    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), l));
+}
+__device__ __forceinline__ double lane_value(double v, int l)
+{
+    return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), l),
+                            __builtin_amdgcn_readlane(__double2loint(v), l));
 }
 
-// Y = A X (row-major N x s), lane = column.
-template <int BS, typename T>
-__global__ __launch_bounds__(BS) void k_spmm(int n, int s, const int* __restrict__ rowptr,
-                                             const int* __restrict__ col, const T* __restrict__ val,
-                                             const T* __restrict__ X, T* __restrict__ Y, int rows_per_block, int G)
-{
-    const int L = mr_logical(G);
-    const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
-    const int rs = min(L * rows_per_block, n), re = min(rs + rows_per_block, n);
-    const int cl = lane < s ? lane : 0;
-    if constexpr (sizeof(T) == 8) {
-        if (s % 2 == 0) {  // two nonzeros per gather (see mr_row_x2)
-            const int c2 = 2 * (lane & 31);
-            const bool pair = lane < 32 && c2 < s;
-            const int cp = c2 < s ? c2 : 0;
-            for (int i = rs + w; i < re; i += BS / kWave) {
-                const double2 y = mr_row_x2(rowptr, col, val, i, [&](int j) {
-                    return *(const double2*)(X + (size_t)j * s + cp);
-                });
-                if (pair) *(double2*)(Y + (size_t)i * s + cp) = y;
+// Four rows' values and columns across the lanes: rows 0 and 1 in the halves of
+// v[0] and c[0], 2 and 3 in those of v[1] and c[1].
+template <typename T>
+struct SpmmFour {
+    T v[2];
+    int c[2];
+    int k[kRunRows + 1];  // first entries of the rows
+    int word;
+
+    __device__ void find(const RunMap<T>& m, int g)
+    {
+        word = m.runs[g];
+#pragma unroll
+        for (int r = 0; r <= kRunRows; ++r) k[r] = m.rowptr[min(g * kRunRows + r, m.n)];
+    }
+    __device__ void fetch(const RunMap<T>& m)
+    {
+        const int l = threadIdx.x & 31;
+        const bool up = (threadIdx.x & 32) != 0;
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int ka = up ? k[2 * h + 1] : k[2 * h], kb = up ? k[2 * h + 2] : k[2 * h + 1];
+            v[h] = T(0);
+            c[h] = 0;
+            if (ka + l < kb) {
+                v[h] = m.val[ka + l];
+                if (h == 0 || word <= 0) c[h] = m.col[ka + l];
             }
-            return;
         }
     }
-    for (int i = rs + w; i < re; i += BS / kWave) {
-        const T y = mr_row<T>(rowptr, col, val, i, [&](int j) { return X[(size_t)j * s + cl]; });
-        if (lane < s) Y[(size_t)i * s + lane] = y;
+    __device__ T value(int r, int e) const { return lane_value(v[r / 2], 32 * (r & 1) + e); }
+    __device__ int column(int r, int e) const { return lane_value(c[r / 2], 32 * (r & 1) + e); }
+};
+
+// The six rows of X that a run of three in each of four rows reads, from the
+// first one's column on.
+template <typename T>
+__device__ __forceinline__ void spmm_gather(const T* __restrict__ X, int s, int column, unsigned lane_at,
+                                            T (&y)[kRunRows + 2])
+{
+    const T* p = X + (size_t)column * s;
+#pragma unroll
+    for (int j = 0; j < kRunRows + 2; j += 2) {
+        const Pair<T> d = *(const Pair<T>*)(p + (size_t)j * s + lane_at);
+        y[j] = d.x;
+        y[j + 1] = d.y;
     }
 }
+
+// A X over all rows.  own(i) is asked for what the caller needs of rows i and
+// i + 1 (of the half's row) while the rows' last gathers are in flight;
+// two(i, u, w, o) gets rows i and i + 1 in pairs (u of the lane's first column,
+// w of its second, in the half's row) with it, one(i, a) a row by itself in the
+// form for sums.  DIFF: the row-sum-preserving form, sum of a_ij (x_j - x_i) +
+// s_i x_i with s_i the row sum, so the near-constant modes of A are not lost to
+// FP32 cancellation.
+template <bool DIFF, typename T, typename Own, typename Two, typename One>
+__device__ __forceinline__ void spmm_rows(const RunMap<T>& m, const T* __restrict__ X, const SpmmLane& L, int G,
+                                          Own own, Two two, One one)
+{
+    constexpr int R = kRunRows, NW = kSpmmBS / kWave, B = 3;  // B: runs in flight together
+    const int s = L.s;
+    const unsigned lane_at = (unsigned)(L.c + L.half * s);
+    const int column = L.column();
+    const int fours = (m.n + R - 1) / R, per = (fours + kSpmmXcds - 1) / kSpmmXcds, stride = G / kSpmmXcds * NW;
+    const int xcd = (int)blockIdx.x % kSpmmXcds;
+    const int g1 = min((xcd + 1) * per, fours);
+    int g = xcd * per + __builtin_amdgcn_readfirstlane(((int)blockIdx.x / kSpmmXcds) * NW + (int)threadIdx.x / kWave);
+    if (g >= g1) return;
+    SpmmFour<T> four, next;
+    next.find(m, g);
+    next.fetch(m);
+    for (; g < g1; g += stride) {
+        const int i0 = g * R;
+        four = next;
+        next.find(m, min(g + stride, fours - 1));
+        // The next rows' entries are asked for behind this step's last
+        // gathers: loads come back in the order in which they were sent, so
+        // sent before they would hold the gathers back (51^3, 64 columns, matrix
+        // in the last-level cache: 137 us instead of 66).
+        auto ahead = [&] {
+            __builtin_amdgcn_sched_barrier(0);
+            next.fetch(m);
+            __builtin_amdgcn_sched_barrier(0);
+        };
+        if (four.word > 0 && s > 1) {
+            const int len = four.word;
+            T acc[R] = {}, xi[R] = {};
+            if constexpr (DIFF) {
+#pragma unroll
+                for (int r = 0; r < R; r += 2) {
+                    const Pair<T> d = L.load(X, i0 + r);
+                    xi[r] = d.x;
+                    xi[r + 1] = d.y;
+                    swap_halves(xi[r], xi[r + 1]);
+                }
+            }
+            auto add = [&](T(&y)[R + 2], int b) {
+#pragma unroll
+                for (int j = 0; j < R + 2; j += 2) swap_halves(y[j], y[j + 1]);
+#pragma unroll
+                for (int r = 0; r < R; ++r)
+#pragma unroll
+                    for (int j = 0; j < 3; ++j) acc[r] = spmm_add<DIFF>(acc[r], four.value(r, b + j), y[r + j], xi[r]);
+            };
+            int b = 0;
+#pragma unroll 1
+            for (; b + 3 * B < len; b += 3 * B) {
+                T y[B][R + 2];
+#pragma unroll
+                for (int q = 0; q < B; ++q) spmm_gather(X, s, four.column(0, b + 3 * q), lane_at, y[q]);
+#pragma unroll
+                for (int q = 0; q < B; ++q) add(y[q], b + 3 * q);
+            }
+            // The last one to B runs; what the rows do not have is gathered again and not added.
+            T y[B][R + 2];
+#pragma unroll
+            for (int q = 0; q < B; ++q) spmm_gather(X, s, four.column(0, min(b + 3 * q, len - 3)), lane_at, y[q]);
+            const auto o0 = own(i0), o2 = own(i0 + 2);
+            ahead();
+#pragma unroll
+            for (int q = 0; q < B; ++q)
+                if (b + 3 * q < len) add(y[q], b + 3 * q);
+            if constexpr (DIFF) {
+#pragma unroll
+                for (int r = 0; r < R; ++r) acc[r] = fma_t(m.rowsum[i0 + r], xi[r], acc[r]);
+            }
+#pragma unroll
+            for (int r = 0; r < R; r += 2) swap_halves(acc[r], acc[r + 1]);
+            two(i0, acc[0], acc[1], o0);
+            two(i0 + 2, acc[2], acc[3], o2);
+        } else if (four.word != SPMM_LONG) {
+            constexpr int N = 4;  // entries of each row in flight together
+            T acc[R] = {}, xi[R] = {};
+            int len[R], most = 0;
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                len[r] = four.k[r + 1] - four.k[r];
+                most = max(most, len[r]);
+                if constexpr (DIFF) xi[r] = X[(size_t)min(i0 + r, m.n - 1) * s + column];
+            }
+            if (four.word > 0) four.c[1] = four.c[0] + 2;  // runs, whose later columns were not fetched
+#pragma unroll 1
+            for (int k = 0; k < most; k += N) {
+                T y[R][N];
+#pragma unroll
+                for (int r = 0; r < R; ++r)
+#pragma unroll
+                    for (int u = 0; u < N; ++u)
+                        y[r][u] = X[(size_t)four.column(r, k + u) * s + column];  // past its end: X's row 0
+#pragma unroll
+                for (int r = 0; r < R; ++r)
+#pragma unroll
+                    for (int u = 0; u < N; ++u)
+                        if (k + u < len[r]) acc[r] = spmm_add<DIFF>(acc[r], four.value(r, k + u), y[r][u], xi[r]);
+            }
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                if (i0 + r >= m.n) break;
+                if constexpr (DIFF) acc[r] = fma_t(m.rowsum[i0 + r], xi[r], acc[r]);
+                one(i0 + r, acc[r]);
+            }
+            ahead();
+        } else {
+#pragma unroll 1
+            for (int i = i0; i < min(i0 + R, m.n); ++i) {
+                // Batches of entries whose gathers are in flight together; the
+                // last one reads past the row's end, into the next row or the
+                // arrays' zero pad, and skips those slots.
+                constexpr int N = 9;
+                static_assert(N <= kCsrPad, "batch reads must stay within the padded arrays");
+                const int k0 = m.rowptr[i], k1 = m.rowptr[i + 1];
+                T acc = T(0), xi = T(0);
+                if constexpr (DIFF) xi = X[(size_t)i * s + column];
+#pragma unroll 1
+                for (int k = k0; k < k1; k += N) {
+                    T y[N];
+#pragma unroll
+                    for (int u = 0; u < N; ++u) y[u] = X[(size_t)m.col[k + u] * s + column];
+#pragma unroll
+                    for (int u = 0; u < N; ++u)
+                        if (k + u < k1) acc = spmm_add<DIFF>(acc, m.val[k + u], y[u], xi);
+                }
+                if constexpr (DIFF) acc = fma_t(m.rowsum[i], xi, acc);
+                one(i, acc);
+            }
+            ahead();
+        }
+    }
+}
+
+// Y = A X.
+template <typename T>
+__device__ __forceinline__ void spmm_block(const RunMap<T>& m, const T* __restrict__ X, T* __restrict__ Y, int s,
+                                           int G)
+{
+    const SpmmLane L(s);
+    spmm_rows<false>(
+        m, X, L, G, [](int) { return 0; }, [&](int i, T u, T w, int) { L.store(Y, i, u, w); },
+        [&](int i, T a) {
+            if (L.own()) Y[(size_t)i * s + L.column()] = a;
+        });
+}
+
+// Workgroups of a product over n rows at wpc per CU: a multiple of the XCDs,
+// no more than the fours of rows have waves for.
+inline int spmm_grid(const cg_ctx* c, int wpc)
+{
+    return std::max(kSpmmXcds, std::min(c->cus * wpc, (c->n + 15) / 16) / kSpmmXcds * kSpmmXcds);
+}
+
+RunMap<double> run_map(const cg_ctx* c);
 
 }  // namespace jpcg
