@@ -8,7 +8,9 @@
 //   BF16  weights and hidden activations held as BF16 copies (FP32 master
 //         weights updated by Adam), products accumulated in FP32, gradients
 //         FP32.
-// The products are one tiled GEMM kernel (64 x 64 output tiles, 16-deep LDS
+// Where 64 x 64 output tiles would not fill the chip, a layer is one launch in
+// either direction (the small-network kernels below).  Otherwise the products
+// are one tiled GEMM kernel (64 x 64 output tiles, 16-deep LDS
 // stages, 4 x 4 outputs per thread, FP32 accumulation) with optional
 // transposed operands and a split of the reduction dimension whose partials
 // are summed in fixed order (weight gradients reduce over the batch).
@@ -44,6 +46,7 @@ template <>
 __device__ __forceinline__ bf16 from_f<bf16>(float v) { return f2bf(v); }
 
 constexpr int GT = 64, GK = 16;
+constexpr int kSmallTiles = 256;  // see small_net
 
 // C_z (M x N, row-major, ldc) = sum over k in split z of A(m,k) B(k,n).
 // A(m,k) = TA ? A[k*lda + m] : A[m*lda + k];  B(k,n) = TB ? B[n*ldb + k] : B[k*ldb + n].
@@ -164,26 +167,254 @@ __global__ void k_colsum(int Bn, int N, const float* __restrict__ D, float* __re
 }
 
 // Adam on the FP32 master parameters; refresh the BF16 copies.
-__global__ void k_adam(int64_t n, float* __restrict__ p, const float* __restrict__ g, float* __restrict__ m,
-                       float* __restrict__ v, float lr, float b1, float b2, float eps, float c1, float c2,
-                       bf16* __restrict__ pb)
+struct AdamArgs {
+    float *p, *g, *m, *v;
+    bf16* pb;
+    float lr, b1, b2, eps, c1, c2;
+    int update;  // 0: the gradient is stored, 1: Adam's step is taken
+};
+__device__ __forceinline__ void adam_step(const AdamArgs& a, int64_t i, float gi)
 {
-    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
-        const float gi = g[i];
-        const float mi = b1 * m[i] + (1.f - b1) * gi;
-        const float vi = b2 * v[i] + (1.f - b2) * gi * gi;
-        m[i] = mi;
-        v[i] = vi;
-        const float pi = p[i] - lr * (mi / c1) / (sqrtf(vi / c2) + eps);
-        p[i] = pi;
-        if (pb) pb[i] = f2bf(pi);
-    }
+    const float mi = a.b1 * a.m[i] + (1.f - a.b1) * gi;
+    const float vi = a.b2 * a.v[i] + (1.f - a.b2) * gi * gi;
+    a.m[i] = mi;
+    a.v[i] = vi;
+    const float pi = a.p[i] - a.lr * (mi / a.c1) / (sqrtf(vi / a.c2) + a.eps);
+    a.p[i] = pi;
+    if (a.pb) a.pb[i] = f2bf(pi);
+}
+__global__ void k_adam(int64_t n, AdamArgs a)
+{
+    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
+        adam_step(a, i, a.g[i]);
 }
 
 __global__ void k_to_bf16(int64_t n, const float* __restrict__ in, bf16* __restrict__ out)
 {
     for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
         out[i] = f2bf(in[i]);
+}
+
+// ---------------------------------------------------------------------------
+// Small networks: one launch per layer and direction.
+//
+// A 64 x 64 output tile gives a 256 x 256 layer 16 workgroups, each walking the
+// whole reduction in stages of 16, and the sums over the batch, the bias, the
+// activation and its derivative, the splits' sum and Adam were launches of their
+// own: 22 a step, 410 us with a batch and hidden layers of 256 (24 inputs, 64
+// outputs); 82 as it is, in six launches.  Here a workgroup forms 16 x 16 outputs, an output per thread, from
+// panels of 256 along the reduction held in LDS, and applies what follows in
+// registers.  What bounds it is latency: a panel's loads, the chain of
+// additions, the launch.
+//
+// Every sum keeps the order of the kernels above: k ascending, the weight
+// gradients' reduction over the batch in the same chunks, which are added in
+// order, the bias gradients in batch order.
+// ---------------------------------------------------------------------------
+constexpr int ST = 16, SK = 256, SP = SK + 4;  // pitch: 16 rows' 16-byte reads fall on different banks
+
+struct SmallPanels {
+    float a[ST][SP];
+    float b[ST][SP];
+};
+
+// p[r][k] = f(r, k) for k < kn, 0 from there to a multiple of 16; neighbouring
+// threads take neighbouring k (ALONG) or neighbouring rows, whichever lie
+// together in memory.
+template <bool ALONG, typename F>
+__device__ __forceinline__ void small_panel(float (&p)[ST][SP], int kn, F f)
+{
+    const int t = threadIdx.x;
+    if (ALONG) {
+        if (t < (kn + 15) / 16 * 16) {
+            float v[ST];
+#pragma unroll
+            for (int r = 0; r < ST; ++r) v[r] = t < kn ? f(r, t) : 0.f;
+#pragma unroll
+            for (int r = 0; r < ST; ++r) p[r][t] = v[r];
+        }
+    } else {
+        const int r = t % ST, kk = t / ST;
+        float v[SK / ST];
+#pragma unroll
+        for (int j = 0; j < SK / ST; ++j) v[j] = kk + ST * j < kn ? f(r, kk + ST * j) : 0.f;
+#pragma unroll
+        for (int j = 0; j < SK / ST; ++j) p[r][kk + ST * j] = v[j];
+    }
+}
+
+// acc += sum over k < kn of a[m][k] b[n][k], k ascending.
+__device__ __forceinline__ float small_dot(const SmallPanels& s, int m, int n, int kn, float acc)
+{
+    for (int k = 0; k < kn; k += 16) {
+        float4 av[4], bv[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            av[u] = *(const float4*)&s.a[m][k + 4 * u];
+            bv[u] = *(const float4*)&s.b[n][k + 4 * u];
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            acc = __builtin_fmaf(av[u].x, bv[u].x, acc);
+            acc = __builtin_fmaf(av[u].y, bv[u].y, acc);
+            acc = __builtin_fmaf(av[u].z, bv[u].z, acc);
+            acc = __builtin_fmaf(av[u].w, bv[u].w, acc);
+        }
+    }
+    return acc;
+}
+
+// One layer forward: U = H W' + b, the activation; for the last layer with
+// targets also D = 2 (U - T) scale and the workgroup's sum of (U - T)^2.
+template <typename TW>
+struct SmallForward {
+    int M, N, K;
+    const float* X;  // the first layer: the caller's batch, kept in H0 as the network keeps activations
+    TW* H0;
+    const TW* in;    // other layers
+    const TW* W;
+    const float* bias;
+    float* U;
+    TW* H;         // hidden layers: silu(U)
+    float* Y;      // the last layer's output
+    const float* T;
+    float scale;
+    float* D;
+    double* loss;
+};
+template <typename TW>
+__global__ __launch_bounds__(256) void k_small_forward(SmallForward<TW> f)
+{
+    __shared__ SmallPanels s;
+    __shared__ double red[256];
+    const int mb = blockIdx.x * ST, nb = blockIdx.y * ST;
+    const int m = threadIdx.x / ST, n = threadIdx.x % ST;
+    float acc = 0.f;
+    for (int k0 = 0; k0 < f.K; k0 += SK) {
+        const int kn = min(SK, f.K - k0);
+        if (k0) __syncthreads();
+        small_panel<true>(s.a, kn, [&](int r, int k) {
+            if (mb + r >= f.M) return 0.f;
+            const int64_t e = (int64_t)(mb + r) * f.K + k0 + k;
+            if (!f.X) return to_f(f.in[e]);
+            const TW v = from_f<TW>(f.X[e]);
+            if (nb == 0) f.H0[e] = v;
+            return to_f(v);
+        });
+        small_panel<true>(s.b, kn, [&](int r, int k) {
+            return nb + r < f.N ? to_f(f.W[(int64_t)(nb + r) * f.K + k0 + k]) : 0.f;
+        });
+        __syncthreads();
+        acc = small_dot(s, m, n, kn, acc);
+    }
+    double l = 0.0;
+    if (mb + m < f.M && nb + n < f.N) {
+        const int64_t e = (int64_t)(mb + m) * f.N + nb + n;
+        const float u = acc + f.bias[nb + n];
+        f.U[e] = u;
+        if (f.H) f.H[e] = from_f<TW>(u * sigmoidf_(u));
+        if (f.Y) f.Y[e] = u;
+        if (f.T) {
+            const float d = u - f.T[e];
+            f.D[e] = 2.f * d * f.scale;
+            l = (double)d * (double)d;
+        }
+    }
+    if (!f.T) return;
+    red[threadIdx.x] = l;
+    for (int w = 128; w > 0; w /= 2) {
+        __syncthreads();
+        if (threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
+    }
+    if (threadIdx.x == 0) f.loss[blockIdx.y * gridDim.x + blockIdx.x] = red[0];
+}
+
+// Dn = (D W) silu'(U): the gradient through a layer and the activation before it.
+template <typename TW>
+struct SmallThrough {
+    int M, N, K;  // batch, inputs, outputs of the layer
+    int tiles;    // 0: none
+    const float* D;
+    const TW* W;
+    const float* U;
+    float* Dn;
+};
+// dW = D' H and db over the batch in chunks, and what is done with them.
+template <typename TW>
+struct SmallWeights {
+    int M, N, K;  // outputs, inputs, batch
+    int tiles;
+    int chunk, splits;
+    const float* D;
+    const TW* in;
+    int64_t at;  // of the layer's weights in the parameters, its biases behind them
+};
+// Several at once where none waits for another: a layer's gradient through its
+// weights, and the weights of up to two layers whose gradients are known and
+// whose weights nothing reads any more.
+template <typename TW>
+struct SmallBackward {
+    SmallThrough<TW> through;
+    SmallWeights<TW> w[2];
+    AdamArgs adam;
+};
+template <typename TW>
+__global__ __launch_bounds__(256) void k_small_backward(SmallBackward<TW> f)
+{
+    __shared__ SmallPanels s;
+    const int m = threadIdx.x / ST, n = threadIdx.x % ST;
+    int tile = blockIdx.x;
+    if (tile < f.through.tiles) {
+        const SmallThrough<TW>& t = f.through;
+        const int across = (t.N + ST - 1) / ST, mb = tile / across * ST, nb = tile % across * ST;
+        float acc = 0.f;
+        for (int k0 = 0; k0 < t.K; k0 += SK) {
+            const int kn = min(SK, t.K - k0);
+            if (k0) __syncthreads();
+            small_panel<true>(s.a, kn, [&](int r, int k) { return mb + r < t.M ? t.D[(int64_t)(mb + r) * t.K + k0 + k] : 0.f; });
+            small_panel<false>(s.b, kn, [&](int r, int k) {
+                return nb + r < t.N ? to_f(t.W[(int64_t)(k0 + k) * t.N + nb + r]) : 0.f;
+            });
+            __syncthreads();
+            acc = small_dot(s, m, n, kn, acc);
+        }
+        if (mb + m < t.M && nb + n < t.N) {
+            const int64_t e = (int64_t)(mb + m) * t.N + nb + n;
+            const float u = t.U[e], sg = sigmoidf_(u);
+            t.Dn[e] = acc * (sg * (1.f + u * (1.f - sg)));
+        }
+        return;
+    }
+    tile -= f.through.tiles;
+    const bool second = tile >= f.w[0].tiles;
+    if (second) tile -= f.w[0].tiles;
+    const SmallWeights<TW>& t = second ? f.w[1] : f.w[0];
+    const int across = (t.N + ST - 1) / ST, mb = tile / across * ST, nb = tile % across * ST;
+    const bool biases = nb == 0 && threadIdx.x < ST;
+    float sum = 0.f, db = 0.f;
+    for (int z = 0; z < t.splits; ++z) {
+        const int k1 = min(t.K, (z + 1) * t.chunk);
+        float acc = 0.f;
+        for (int k0 = z * t.chunk; k0 < k1; k0 += SK) {
+            const int kn = min(SK, k1 - k0);
+            __syncthreads();
+            small_panel<false>(s.a, kn, [&](int r, int k) { return mb + r < t.M ? t.D[(int64_t)(k0 + k) * t.M + mb + r] : 0.f; });
+            small_panel<false>(s.b, kn, [&](int r, int k) {
+                return nb + r < t.N ? to_f(t.in[(int64_t)(k0 + k) * t.N + nb + r]) : 0.f;
+            });
+            __syncthreads();
+            acc = small_dot(s, m, n, kn, acc);
+            if (biases)
+                for (int k = 0; k < kn; ++k) db += s.a[threadIdx.x][k];
+        }
+        sum = t.splits > 1 ? sum + acc : acc;
+    }
+    auto take = [&](int64_t i, float g) {
+        if (f.adam.update) adam_step(f.adam, i, g);
+        else f.adam.g[i] = g;
+    };
+    if (mb + m < t.M && nb + n < t.N) take(t.at + (int64_t)(mb + m) * t.N + nb + n, sum);
+    if (biases && mb + (int)threadIdx.x < t.M) take(t.at + (int64_t)t.M * t.N + mb + threadIdx.x, db);
 }
 
 static int grid_for(int64_t count) { return (int)std::min<int64_t>(2048, std::max<int64_t>(1, (count + 255) / 256)); }
@@ -207,6 +438,7 @@ struct mlp_net {
     std::vector<float*> U;      // pre-activations per layer
     float* D0 = nullptr;        // gradient buffers (max_batch x max width)
     float* D1 = nullptr;
+    float* D2 = nullptr;
     float* C = nullptr;         // GEMM output / split partials
     size_t c_cap = 0;
     double* loss_part = nullptr;
@@ -219,7 +451,7 @@ namespace jpcg {
 static void free_mlp(mlp_net* n)
 {
     if (!n) return;
-    void* ptrs[] = {n->p, n->g, n->m, n->v, n->pb, n->D0, n->D1, n->C, n->loss_part};
+    void* ptrs[] = {n->p, n->g, n->m, n->v, n->pb, n->D0, n->D1, n->D2, n->C, n->loss_part};
     for (void* q : ptrs)
         if (q) (void)hipFree(q);
     for (void* q : n->H)
@@ -255,10 +487,112 @@ const float* weights<float>(mlp_net* n, int l) { return n->p + n->woff[l]; }
 template <>
 const bf16* weights<bf16>(mlp_net* n, int l) { return n->pb + n->woff[l]; }
 
+// Fixed chunks of the batch that the weight gradients are summed in.
+static int batch_splits(int Bn) { return std::max(1, std::min(16, Bn / 128)); }
+
+// The small-network kernels serve networks and batches no layer of which fills
+// the chip with 64 x 64 tiles: up to 256 of them per product.  24-256-256-64 in
+// BF16, a step with batches of 32, 256 and 4096: 58, 82 and 721 us against 207,
+// 410 and 2831, a forward pass 29, 25 and 95 against 90, 95 and 104; hidden
+// layers of 1024 with 1024 (256 tiles): 879 and 264 us against 1198 and 327; with
+// 2048 (512 tiles) 1697 and 497 against 1823 and 389.
+static bool small_net(const mlp_net* n, int Bn)
+{
+    auto tiles = [](int a, int b) { return (int64_t)((a + GT - 1) / GT) * ((b + GT - 1) / GT); };
+    for (int l = 0; l < n->L; ++l)
+        if (tiles(Bn, n->dims[l + 1]) > kSmallTiles || tiles(n->dims[l], n->dims[l + 1]) > kSmallTiles) return false;
+    return true;
+}
+
+// The forward pass of a small network; with targets also the last layer's
+// gradient, into n->D0, and the loss partials (their number is returned).
+template <typename TW>
+static int small_forward(mlp_net* n, const float* X, int Bn, float* Y, const float* T)
+{
+    int partials = 0;
+    for (int l = 0; l < n->L; ++l) {
+        const int in = n->dims[l], out = n->dims[l + 1];
+        const bool last = l == n->L - 1;
+        SmallForward<TW> f{};
+        f.M = Bn;
+        f.N = out;
+        f.K = in;
+        f.X = l == 0 ? X : nullptr;
+        f.H0 = (TW*)n->H[0];
+        f.in = (const TW*)n->H[l];
+        f.W = weights<TW>(n, l);
+        f.bias = n->p + n->woff[l] + (int64_t)out * in;
+        f.U = n->U[l];
+        f.H = last ? nullptr : (TW*)n->H[l + 1];
+        f.Y = last ? (Y ? Y : (float*)n->H[l + 1]) : nullptr;
+        f.T = last ? T : nullptr;
+        f.scale = 1.f / (float)((int64_t)Bn * out);
+        f.D = n->D0;
+        f.loss = n->loss_part;
+        const dim3 grid((Bn + ST - 1) / ST, (out + ST - 1) / ST);
+        k_small_forward<TW><<<grid, 256, 0, n->stream>>>(f);
+        JPCG_HIP(hipGetLastError());
+        partials = (int)(grid.x * grid.y);
+    }
+    return partials;
+}
+
+template <typename TW>
+static void small_backward(mlp_net* n, int Bn, const AdamArgs& adam)
+{
+    float* D[3] = {n->D0, n->D1, n->D2};  // layer l's gradient in D[(L - 1 - l) % 3]
+    const int L = n->L;
+    auto tiles = [](int a, int b) { return ((a + ST - 1) / ST) * ((b + ST - 1) / ST); };
+    auto weight_job = [&](int l) {
+        SmallWeights<TW> w{};
+        if (l >= L) return w;
+        const int splits = batch_splits(Bn);
+        w.M = n->dims[l + 1];
+        w.N = n->dims[l];
+        w.K = Bn;
+        w.tiles = tiles(w.M, w.N);
+        w.chunk = (Bn + splits - 1) / splits;
+        w.splits = (Bn + w.chunk - 1) / w.chunk;
+        w.D = D[(L - 1 - l) % 3];
+        w.in = (const TW*)n->H[l];
+        w.at = n->woff[l];
+        return w;
+    };
+    for (int l = L - 1; l >= 0; --l) {
+        // Layer l's weights wait for the launch after the one that reads them;
+        // the last launch takes the first two layers'.
+        SmallBackward<TW> f{};
+        f.adam = adam;
+        f.w[0] = weight_job(l + 1);
+        if (l > 0) {
+            SmallThrough<TW>& t = f.through;
+            t.M = Bn;
+            t.N = n->dims[l];
+            t.K = n->dims[l + 1];
+            t.tiles = tiles(t.M, t.N);
+            t.D = D[(L - 1 - l) % 3];
+            t.W = weights<TW>(n, l);
+            t.U = n->U[l - 1];
+            t.Dn = D[(L - l) % 3];
+        } else {
+            f.w[1] = weight_job(0);
+        }
+        k_small_backward<TW><<<f.through.tiles + f.w[0].tiles + f.w[1].tiles, 256, 0, n->stream>>>(f);
+        JPCG_HIP(hipGetLastError());
+    }
+}
+
 template <typename TW>
 static void forward_t(mlp_net* n, const float* X, int Bn, float* Y)
 {
     hipStream_t st = n->stream;
+    if (Y && small_net(n, Bn)) {
+        // A single layer reads X while it writes its output, which may be X.
+        small_forward<TW>(n, X, Bn, n->L > 1 ? Y : nullptr, nullptr);
+        if (n->L > 1) return;
+        JPCG_HIP(hipMemcpyAsync(Y, n->H[1], sizeof(float) * (int64_t)Bn * n->dims[1], hipMemcpyDeviceToDevice, st));
+        return;
+    }
     const int64_t in0 = (int64_t)Bn * n->dims[0];
     if constexpr (sizeof(TW) == 2) {
         k_to_bf16<<<grid_for(in0), 256, 0, st>>>(in0, X, (bf16*)n->H[0]);
@@ -284,11 +618,25 @@ static void forward_t(mlp_net* n, const float* X, int Bn, float* Y)
     }
 }
 
-// Forward, loss, and gradients into n->g; returns the loss (host, after sync if want_loss).
+// Forward, loss, and gradients: into n->g, or Adam's step with them.  Returns the
+// loss (host, after sync if want_loss).
 template <typename TW>
-static double backward_t(mlp_net* n, const float* X, const float* T, int Bn, bool want_loss)
+static double backward_t(mlp_net* n, const float* X, const float* T, int Bn, bool want_loss, const AdamArgs& adam)
 {
     hipStream_t st = n->stream;
+    auto loss = [&](int partials) {
+        if (!want_loss) return 0.0;
+        JPCG_HIP(hipMemcpyAsync(n->hloss, n->loss_part, sizeof(double) * partials, hipMemcpyDeviceToHost, st));
+        JPCG_HIP(hipStreamSynchronize(st));
+        double s = 0.0;
+        for (int i = 0; i < partials; ++i) s += n->hloss[i];
+        return s / (double)((int64_t)Bn * n->dims[n->L]);
+    };
+    if (small_net(n, Bn)) {
+        const int partials = small_forward<TW>(n, X, Bn, nullptr, T);
+        small_backward<TW>(n, Bn, adam);
+        return loss(partials);
+    }
     forward_t<TW>(n, X, Bn, nullptr);
     const int L = n->L;
     const int m = n->dims[L];
@@ -303,7 +651,7 @@ static double backward_t(mlp_net* n, const float* X, const float* T, int Bn, boo
         float* gW = n->g + n->woff[l];
         float* gb = gW + (int64_t)out * in;
         // dW = D' H_l (out x in), reduced over the batch in fixed chunks.
-        const int splits = std::max(1, std::min(16, Bn / 128));
+        const int splits = batch_splits(Bn);
         gemm<float, TW, true, false>(n, out, in, Bn, D, out, (const TW*)n->H[l], in, gW, splits);
         k_colsum<<<(out + 255) / 256, 256, 0, st>>>(Bn, out, D, gb);
         JPCG_HIP(hipGetLastError());
@@ -316,12 +664,11 @@ static double backward_t(mlp_net* n, const float* X, const float* T, int Bn, boo
             std::swap(D, Dn);
         }
     }
-    if (!want_loss) return 0.0;
-    JPCG_HIP(hipMemcpyAsync(n->hloss, n->loss_part, sizeof(double) * lg, hipMemcpyDeviceToHost, st));
-    JPCG_HIP(hipStreamSynchronize(st));
-    double s = 0.0;
-    for (int i = 0; i < lg; ++i) s += n->hloss[i];
-    return s / (double)cnt;
+    if (adam.update) {
+        k_adam<<<grid_for(n->nparam), 256, 0, st>>>(n->nparam, adam);
+        JPCG_HIP(hipGetLastError());
+    }
+    return loss(lg);
 }
 
 }  // namespace jpcg
@@ -372,10 +719,11 @@ int mlp_create(int32_t nlayers, const int32_t* dims, int32_t precision, int32_t 
         for (int l = 0; l < nlayers; ++l) JPCG_HIP(hipMalloc((void**)&n->U[l], sizeof(float) * (size_t)max_batch * dims[l + 1]));
         JPCG_HIP(hipMalloc((void**)&n->D0, sizeof(float) * (size_t)max_batch * wmax));
         JPCG_HIP(hipMalloc((void**)&n->D1, sizeof(float) * (size_t)max_batch * wmax));
+        JPCG_HIP(hipMalloc((void**)&n->D2, sizeof(float) * (size_t)max_batch * wmax));
         n->c_cap = std::max<size_t>((size_t)max_batch * wmax, (size_t)16 * wmax * wmax);
         JPCG_HIP(hipMalloc((void**)&n->C, sizeof(float) * n->c_cap));
-        JPCG_HIP(hipMalloc((void**)&n->loss_part, sizeof(double) * 2048));
-        JPCG_HIP(hipHostMalloc((void**)&n->hloss, sizeof(double) * 2048, hipHostMallocDefault));
+        JPCG_HIP(hipMalloc((void**)&n->loss_part, sizeof(double) * std::max(2048, 16 * kSmallTiles)));
+        JPCG_HIP(hipHostMalloc((void**)&n->hloss, sizeof(double) * std::max(2048, 16 * kSmallTiles), hipHostMallocDefault));
         JPCG_HIP(hipStreamSynchronize(n->stream));
         *out = n;
         return 0;
@@ -434,8 +782,10 @@ int mlp_gradients(mlp_net* n, const float* X, const float* T, int32_t batch, flo
 {
     if (!n || !X || !T || batch < 1 || batch > n->max_batch) return CG_EINVAL;
     try {
-        const double l = n->precision == 1 ? backward_t<bf16>(n, X, T, batch, true)
-                                           : backward_t<float>(n, X, T, batch, true);
+        AdamArgs adam{};
+        adam.g = n->g;
+        const double l = n->precision == 1 ? backward_t<bf16>(n, X, T, batch, true, adam)
+                                           : backward_t<float>(n, X, T, batch, true, adam);
         if (loss) *loss = l;
         if (grads_host) {
             JPCG_HIP(hipMemcpyAsync(grads_host, n->g, sizeof(float) * n->nparam, hipMemcpyDeviceToHost, n->stream));
@@ -452,14 +802,13 @@ int mlp_train_step(mlp_net* n, const float* X, const float* T, int32_t batch, fl
 {
     if (!n || !X || !T || batch < 1 || batch > n->max_batch || !(lr > 0.f)) return CG_EINVAL;
     try {
-        const double l = n->precision == 1 ? backward_t<bf16>(n, X, T, batch, loss != nullptr)
-                                           : backward_t<float>(n, X, T, batch, loss != nullptr);
+        const int t = n->t + 1;
+        const float c1 = 1.f - std::pow(beta1, (float)t), c2 = 1.f - std::pow(beta2, (float)t);
+        const AdamArgs adam{n->p, n->g, n->m, n->v, n->pb, lr, beta1, beta2, eps, c1, c2, 1};
+        const double l = n->precision == 1 ? backward_t<bf16>(n, X, T, batch, loss != nullptr, adam)
+                                           : backward_t<float>(n, X, T, batch, loss != nullptr, adam);
+        n->t = t;
         if (loss) *loss = l;
-        n->t += 1;
-        const float c1 = 1.f - std::pow(beta1, (float)n->t), c2 = 1.f - std::pow(beta2, (float)n->t);
-        k_adam<<<grid_for(n->nparam), 256, 0, n->stream>>>(n->nparam, n->p, n->g, n->m, n->v, lr, beta1, beta2, eps,
-                                                           c1, c2, n->pb);
-        JPCG_HIP(hipGetLastError());
         return 0;
     } catch (const HipError&) {
         return CG_EHIP;
