@@ -6,19 +6,19 @@
 // Per iteration, on N x 64 row-major FP64 blocks (columns >= s are zero):
 //   Q = A P                                  k_bc_spmm (row products, four rows a wave)
 //   Gamma = P'Q, Psi = P'R                   k_bc_gram<2> + k_bc_sum
-//   alpha = Gamma^-1 Psi                     k_bc_alpha (one wave: Cholesky over
-//                                            the live columns, inverse factor)
+//   alpha = Gamma^-1 Psi                     k_bc_alpha (Cholesky over the live
+//                                            columns, inverse factor)
 //   X += P alpha                             k_bc_gemm<XUP>
-//   R -= Q alpha, Z = M^-1 R, ||r_j||^2      k_bc_gemm<RUP> + k_bc_sum
-//   Q'Z                                      k_bc_gram<1> + k_bc_sum
+//   R -= Q alpha, ||r_j||^2                  k_bc_gemm<RUP> + k_bc_sum
+//   Q'Z, Z = M^-1 R                          k_bc_gram<1> + k_bc_sum
 //   test, beta = -Gamma^-1 Q'Z               k_bc_beta
-//   W = Z + P beta                           k_bc_gemm<DIR>
-//   three CholeskyQR passes of W -> P        (k_bc_gram<1>, k_bc_sum, k_bc_orth,
-//                                            k_bc_gemm<APPLY>) x 3
+//   W = Z + P beta, W'W                      k_bc_gemm<DIR> + k_bc_sum
+//   three CholeskyQR passes of W -> P        (k_bc_orth, k_bc_gemm<APPLY> with the
+//                                            next pass's Gram matrix, k_bc_sum) x 3
 // The Gram and block-times-64x64 products are dense contractions: they run on
 // the FP64 matrix cores (v_mfma_f64_16x16x4f64), operands straight from
 // global memory into the fragment layout.  The 64 x 64 factorisations run in
-// one wave of one workgroup, the matrix held in registers.  All kernels of an
+// one workgroup, in blocks of 16 columns.  All kernels of an
 // iteration are captured in hipGraph chunks and return at entry once the
 // state is no longer RUN; the host confirms a
 // passed recurrence test on the true residuals and restarts the block from
@@ -75,14 +75,15 @@ __device__ __forceinline__ bool bc_stopped(const BcState* st, int gate)
 // operand over its rows; waves of a workgroup are added in LDS in wave order
 // and each workgroup writes one partial per operand.
 // NOP = 2: waves 0, 1 take V0 and waves 2, 3 take V1 (U is read twice, from L2).
+// NOP = 1: V0's rows are scaled (Q'Z with Z = M^-1 R formed here).
 // ---------------------------------------------------------------------------
 constexpr int kGramBS = 256;
 
 template <int NOP>
 __global__ __launch_bounds__(kGramBS, 2) void k_bc_gram(int n, const double* __restrict__ U,
                                                      const double* __restrict__ V0, const double* __restrict__ V1,
-                                                     double* __restrict__ part, int rows_per_wg, int G,
-                                                     const BcState* st, int gate)
+                                                     const double* __restrict__ scale, double* __restrict__ part,
+                                                     int rows_per_wg, int G, const BcState* st, int gate)
 {
     if (bc_stopped(st, gate)) return;
     __shared__ double red[NOP][kBB];
@@ -99,11 +100,12 @@ __global__ __launch_bounds__(kGramBS, 2) void k_bc_gram(int n, const double* __r
         for (int jb = 0; jb < 4; ++jb) acc[ib][jb] = d4{0.0, 0.0, 0.0, 0.0};
     const int rq = lane >> 4, cq = lane & 15;
     // The loads of the next 4-row step are issued before this step's products.
-    double a[4], b[4];
+    double a[4], b[4], d = 1.0;
     auto fetch = [&](int r0) {
         const int row = r0 + rq;
         const bool ok = row < re;
         const size_t o = (size_t)(ok ? row : rs) * kB + cq;
+        if (NOP == 1) d = scale[ok ? row : rs];
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
             a[q] = ok ? U[o + 16 * q] : 0.0;
@@ -117,7 +119,7 @@ __global__ __launch_bounds__(kGramBS, 2) void k_bc_gram(int n, const double* __r
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
             ca[q] = a[q];
-            cb[q] = b[q];
+            cb[q] = NOP == 1 ? d * b[q] : b[q];
         }
         r0 += 4 * kWavesPerOp;
         if (r0 < re) fetch(r0);
@@ -187,22 +189,31 @@ __global__ __launch_bounds__(256) void k_bc_sum(const double* __restrict__ part,
 // row: step t, lane l holds A = U[r0 + l % 16][16 (l / 16) + t] and
 // B = M[16 (l / 16) + t][16 jb + l % 16] (read from LDS).
 //   BC_XUP:   Y += U M                     (X += P alpha)
-//   BC_RUP:   Y -= U M, Z = M^-1 Y, per-column partials of y'y
-//                                          (R -= Q alpha, Z, ||r_j||^2)
-//   BC_DIR:   Y = Z + U M                  (W = Z + P beta)
+//   BC_RUP:   Y -= U M, per-column partials of y'y  (R -= Q alpha, ||r_j||^2)
+//   BC_DIR:   Y = D Z + U M                (W = M^-1 R + P beta)
+//   BC_SCALE: Y = D Z                      (W = M^-1 R, the first direction)
 //   BC_APPLY: Y = U M
+// GRAM: the workgroup's share of Y'Y too.  The tile's rows are in the lanes as
+// the matrix instructions want both operands of a Gram step, so a 16-row tile
+// costs 40 more of them (the upper triangle of 16 x 16 blocks) and no memory:
+// at 51^3 46 us with the Gram matrix, where the product took 33 and a pass for
+// the Gram matrix another 33 (136 and 68 MB).  R -= Q alpha without a stored Z and
+// with R's loads ahead of the products: 39 us, 87 before; W with its Gram matrix
+// 50, 66 + 33 before.
 // ---------------------------------------------------------------------------
-enum BcGemm : int { BC_XUP = 0, BC_RUP = 1, BC_DIR = 2, BC_APPLY = 3 };
-constexpr int kGemmBS = 256;
+enum BcGemm : int { BC_XUP = 0, BC_RUP = 1, BC_DIR = 2, BC_APPLY = 3, BC_SCALE = 4 };
+constexpr int kGemmBS = 512;
+constexpr int kGemmWaves = kGemmBS / kWave;
 constexpr int kMPad = 65;  // LDS row pitch of M (doubles)
 
 struct BcGemmArgs {
     int n;
     const double* U;
     double* Y;
-    double* Z;          // BC_RUP: written; BC_DIR: read
-    const double* dinv;
-    double* part;       // BC_RUP: [G][64] partials of y'y
+    const double* Z;     // BC_DIR, BC_SCALE
+    const double* dinv;  // the same
+    double* part;        // BC_RUP: [G][64] partials of y'y
+    double* gram;        // GRAM: [G][64 * 64]
     int G;
 };
 
@@ -225,62 +236,89 @@ __device__ __forceinline__ void bc_tile_product(const double (&a)[16], const dou
     const int lane = threadIdx.x & 63, rq = lane >> 4, cq = lane & 15;
 #pragma unroll
     for (int jb = 0; jb < 4; ++jb) acc[jb] = d4{0.0, 0.0, 0.0, 0.0};
+    // Four steps' entries of M at a time: read all at once they take 128 registers.
 #pragma unroll
-    for (int t = 0; t < 16; ++t)
+    for (int t = 0; t < 16; ++t) {
+        if (t % 4 == 0) __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int jb = 0; jb < 4; ++jb)
             acc[jb] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[t], Ms[(16 * rq + t) * kMPad + 16 * jb + cq], acc[jb], 0, 0, 0);
+    }
+    __builtin_amdgcn_sched_barrier(0);
 }
 
-template <int MODE>
+template <int MODE, bool GRAM>
 __global__ __launch_bounds__(kGemmBS, 2) void k_bc_gemm(BcGemmArgs g, BcState* st, int gate)
 {
     if (bc_stopped(st, gate)) return;
     __shared__ double Ms[kB * kMPad];
-    __shared__ double red[4][kB];
-    for (int e = threadIdx.x; e < kBB; e += kGemmBS) Ms[(e / kB) * kMPad + e % kB] = st->M[e];
-    __syncthreads();
+    __shared__ double red[GRAM ? kBB : kGemmWaves * kB];
+    if (MODE != BC_SCALE) {
+        for (int e = threadIdx.x; e < kBB; e += kGemmBS) Ms[(e / kB) * kMPad + e % kB] = st->M[e];
+        __syncthreads();
+    }
     const int L = xcd_logical_block((int)blockIdx.x, g.G);
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, rq = lane >> 4, cq = lane & 15;
     const int tiles = (g.n + 15) / 16;
     const int tpw = (tiles + g.G - 1) / g.G;
     const int t0 = min(L * tpw, tiles), t1 = min(t0 + tpw, tiles);
     double nrm[4] = {0.0, 0.0, 0.0, 0.0};
+    d4 gr[GRAM ? 10 : 1];  // blocks (ib, jb), ib <= jb
+    if constexpr (GRAM) {
+#pragma unroll
+        for (int e = 0; e < 10; ++e) gr[e] = d4{0.0, 0.0, 0.0, 0.0};
+    }
     if (MODE == BC_XUP && L == 0 && threadIdx.x == 0) st->k += 1;
     // The next tile's row loads are issued before this tile's products.
     double a[16];
     int tile = t0 + w;
-    if (tile < t1) bc_tile_load(g.U, tile * 16, g.n, a);
+    if (MODE != BC_SCALE && tile < t1) bc_tile_load(g.U, tile * 16, g.n, a);
     while (tile < t1) {
         const int r0 = tile * 16;
-        double ca[16];
+        double ca[16], y[4][4];
 #pragma unroll
         for (int u = 0; u < 16; ++u) ca[u] = a[u];
-        tile += kGemmBS / 64;
-        if (tile < t1) bc_tile_load(g.U, tile * 16, g.n, a);
-        d4 acc[4];
-        bc_tile_product(ca, Ms, acc);
+        // The rows of Y or Z that the product is added to.
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
-            const int row = r0 + rq + 4 * v;
-            if (row >= g.n) continue;
-            double di = 0.0;
-            if constexpr (MODE == BC_RUP) di = g.dinv[row];
+            const int row = min(r0 + rq + 4 * v, g.n - 1);
+            double di = 1.0;
+            if constexpr (MODE == BC_DIR || MODE == BC_SCALE) di = g.dinv[row];
 #pragma unroll
             for (int jb = 0; jb < 4; ++jb) {
                 const size_t o = (size_t)row * kB + 16 * jb + cq;
-                if constexpr (MODE == BC_XUP) {
-                    g.Y[o] = g.Y[o] + acc[jb][v];
-                } else if constexpr (MODE == BC_RUP) {
-                    const double r = g.Y[o] - acc[jb][v];
-                    g.Y[o] = r;
-                    g.Z[o] = di * r;
-                    nrm[jb] += r * r;
-                } else if constexpr (MODE == BC_DIR) {
-                    g.Y[o] = g.Z[o] + acc[jb][v];
-                } else {
-                    g.Y[o] = acc[jb][v];
-                }
+                if constexpr (MODE == BC_XUP || MODE == BC_RUP) y[jb][v] = g.Y[o];
+                if constexpr (MODE == BC_DIR || MODE == BC_SCALE) y[jb][v] = di * g.Z[o];
+            }
+        }
+        tile += kGemmWaves;
+        if (MODE != BC_SCALE && tile < t1) bc_tile_load(g.U, tile * 16, g.n, a);
+        d4 acc[4];
+        if constexpr (MODE != BC_SCALE) bc_tile_product(ca, Ms, acc);
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const int row = r0 + rq + 4 * v;
+            const bool ok = row < g.n;
+#pragma unroll
+            for (int jb = 0; jb < 4; ++jb) {
+                const size_t o = (size_t)row * kB + 16 * jb + cq;
+                double x;
+                if constexpr (MODE == BC_XUP || MODE == BC_DIR) x = y[jb][v] + acc[jb][v];
+                else if constexpr (MODE == BC_RUP) x = y[jb][v] - acc[jb][v];
+                else if constexpr (MODE == BC_SCALE) x = y[jb][v];
+                else x = acc[jb][v];
+                if (ok) g.Y[o] = x;
+                else x = 0.0;
+                if constexpr (MODE == BC_RUP) nrm[jb] += x * x;
+                if constexpr (GRAM) y[jb][v] = x;
+            }
+            if constexpr (GRAM) {
+                int e = 0;
+#pragma unroll
+                for (int ib = 0; ib < 4; ++ib)
+#pragma unroll
+                    for (int jb = ib; jb < 4; ++jb, ++e)
+                        gr[e] = __builtin_amdgcn_mfma_f64_16x16x4f64(y[ib][v], y[jb][v], gr[e], 0, 0, 0);
             }
         }
     }
@@ -295,12 +333,36 @@ __global__ __launch_bounds__(kGemmBS, 2) void k_bc_gemm(BcGemmArgs g, BcState* s
         }
         if (rq == 0) {
 #pragma unroll
-            for (int jb = 0; jb < 4; ++jb) red[w][16 * jb + cq] = nrm[jb];
+            for (int jb = 0; jb < 4; ++jb) red[w * kB + 16 * jb + cq] = nrm[jb];
         }
         __syncthreads();
         if (threadIdx.x < kB) {
-            const int j = threadIdx.x;
-            g.part[(size_t)L * kB + j] = ((red[0][j] + red[1][j]) + red[2][j]) + red[3][j];
+            double x = 0.0;
+            for (int t = 0; t < kGemmWaves; ++t) x += red[t * kB + threadIdx.x];
+            g.part[(size_t)L * kB + threadIdx.x] = x;
+        }
+    }
+    if constexpr (GRAM) {
+        // The waves in order; the triangle below is the one above.
+        for (int t = 0; t < kGemmWaves; ++t) {
+            if (w == t) {
+                int e = 0;
+#pragma unroll
+                for (int ib = 0; ib < 4; ++ib)
+#pragma unroll
+                    for (int jb = ib; jb < 4; ++jb, ++e)
+#pragma unroll
+                        for (int v = 0; v < 4; ++v) {
+                            double& o = red[(16 * ib + rq + 4 * v) * kB + 16 * jb + cq];
+                            o = t == 0 ? gr[e][v] : o + gr[e][v];
+                        }
+            }
+            __syncthreads();
+        }
+        double* out = g.gram + (size_t)L * kBB;
+        for (int e = threadIdx.x; e < kBB; e += kGemmBS) {
+            const int i = e / kB, j = e % kB;
+            out[e] = i / 16 <= j / 16 ? red[e] : red[j * kB + i];
         }
     }
 }
@@ -317,11 +379,10 @@ __global__ __launch_bounds__(kSpmmBS, 6) void k_bc_spmm(RunMap<double> m, const 
     spmm_block(m, X, Y, kB, G);
 }
 
-// R = B - AX (AX given), Z = M^-1 R, per-workgroup partials of r'r and b'b
+// R = B - AX (AX given), per-workgroup partials of r'r and b'b
 // (part[g][0][64], part[g][1][64]); write = 0 only measures.
 __global__ __launch_bounds__(256) void k_bc_residual(int n, const double* __restrict__ B,
-                                                     const double* __restrict__ AX, const double* __restrict__ dinv,
-                                                     double* __restrict__ R, double* __restrict__ Z,
+                                                     const double* __restrict__ AX, double* __restrict__ R,
                                                      double* __restrict__ part, int write)
 {
     __shared__ double red[2][4][kB];
@@ -330,10 +391,7 @@ __global__ __launch_bounds__(256) void k_bc_residual(int n, const double* __rest
     for (int i = blockIdx.x * 4 + w; i < n; i += gridDim.x * 4) {
         const size_t o = (size_t)i * kB + lane;
         const double b = B[o], r = b - AX[o];
-        if (write) {
-            R[o] = r;
-            Z[o] = dinv[i] * r;
-        }
+        if (write) R[o] = r;
         rr += r * r;
         bb += b * b;
     }
@@ -359,206 +417,213 @@ __global__ void k_bc_pack(int n, int s, const double* __restrict__ src, double* 
 }
 
 // ---------------------------------------------------------------------------
-// 64 x 64 factorisations, one workgroup of 256 threads, matrices in LDS.
+// 64 x 64 factorisations, one workgroup of four waves, matrices in LDS.
+//
+// What bounds them is the chain of 64 pivots.  One wave with a column of the
+// matrix per lane took 52 us for a Cholesky factor and its inverse, about 400 ns
+// a step: a square root, a division, and the factor's column through LDS to 63
+// updates.  In blocks of 16 columns a step updates the block's later columns
+// only, from v_readlane broadcasts, with a reciprocal square root in place of
+// root and division; what is left and the blocks of the inverse are products
+// for the matrix cores: 31 us.
 // ---------------------------------------------------------------------------
 constexpr int kSmallBS = 256;
 constexpr int kSP = 65;  // LDS pitch
+constexpr int kBlk = 16;
 
-// Cholesky factorisation of the symmetric matrix in A (its lower triangle)
-// taking columns in order.  mode 0: every column in `use` must have a
-// positive pivot (bad = 1 otherwise); mode 1: a column whose pivot is <= tau
-// is dropped.  keep[k] is set for the factored columns.  On return row k of A
-// holds column k of the factor L (A = L' in its upper triangle, zeros below
-// the diagonal; zero rows for dropped or unused columns).  Called by the whole
-// workgroup; wave 0 factors alone, without workgroup barriers: lane j holds
-// column j of the trailing matrix in registers, updated in both triangles so
-// that it stays exactly symmetric (lane i's update of a_ji is the same fused
-// product as lane j's of a_ij).  Step k: the pivot is lane k's a_kk; lane i's
-// own a_ik scaled by the inverse pivot is l_ik, written to A[k][i]; every lane
-// reads that row's entries right of the diagonal as broadcasts and subtracts
-// l_ik l_jk from its column.
-template <int K>
-__device__ __forceinline__ void chol_step(double (&a)[kB], int j, unsigned long long usem, int mode, double tau,
-                                          double* A, int* keep, bool& badk)
+// 1 / sqrt(d) for d > 0: the hardware's estimate and two Newton steps.
+__device__ __forceinline__ double recip_sqrt(double d)
 {
-    const double d = read_lane(a[K], K);
-    bool kk = ((usem >> K) & 1ull) != 0;
-    if (kk) {
-        if (mode == 0) {
-            if (!(d > 0.0) || !isfinite(d)) {
-                badk = true;
+    if (d < 0x1p-900 || d > 0x1p900) return 1.0 / sqrt(d);
+    double x = __builtin_amdgcn_rsq(d);
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+        const double e = __builtin_fma(-d * x, x, 1.0);
+        x = __builtin_fma(0.5 * x, e, x);
+    }
+    return x;
+}
+
+// Fragments of the 16 x 16 x 4 FP64 product: a block's step t as left or right
+// operand, and where slot v of a product lies.
+struct Frag {
+    int r, c;  // lane / 16, lane % 16
+    __device__ Frag() : r((threadIdx.x & 63) >> 4), c(threadIdx.x & 15) {}
+    // S[row0 + c][col0 + 4 t + r]: left operand, or right operand of the transpose.
+    __device__ double rows(const double* S, int row0, int col0, int t) const
+    {
+        return S[(row0 + c) * kSP + col0 + 4 * t + r];
+    }
+    // S[row0 + 4 t + r][col0 + c]: right operand, or left operand of the transpose.
+    __device__ double cols(const double* S, int row0, int col0, int t) const
+    {
+        return S[(row0 + 4 * t + r) * kSP + col0 + c];
+    }
+};
+__device__ __forceinline__ d4 mfma4(double a, double b, d4 c)
+{
+    return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
+}
+
+// The columns 16 b ... of the trailing matrix, factored by one wave with a row
+// per lane.  keep[k] is set for the factored ones, ip[k] to the inverse of the
+// factor's diagonal (0 where not).
+__device__ __forceinline__ void chol_panel(double* A, int b, unsigned long long usem, int mode, double tau, int* keep,
+                                           double* ip, bool& bad)
+{
+    const int i = threadIdx.x, c0 = kBlk * b;
+    double p[kBlk];
+#pragma unroll
+    for (int j = 0; j < kBlk; ++j) p[j] = i >= c0 ? A[i * kSP + c0 + j] : 0.0;
+#pragma unroll
+    for (int k = 0; k < kBlk; ++k) {
+        const double d = read_lane(p[k], c0 + k);
+        bool kk = ((usem >> (c0 + k)) & 1ull) != 0;
+        if (kk) {
+            if (mode == 0) {
+                if (!(d > 0.0) || !isfinite(d)) {
+                    bad = true;
+                    kk = false;
+                }
+            } else if (!(d > tau)) {
                 kk = false;
             }
-        } else if (!(d > tau)) {
-            kk = false;
         }
-    }
-    if (j == 0) keep[K] = kk ? 1 : 0;
-    if (!kk) {
-        A[K * kSP + j] = 0.0;
-        return;
-    }
-    const double piv = sqrt(d), ip = 1.0 / piv;
-    const double l = j == K ? piv : (j > K ? a[K] * ip : 0.0);
-    A[K * kSP + j] = l;
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    // Columns j <= K are final: they subtract l_ik * 0, which leaves a_ij
-    // unchanged (the entries are finite).  The row is read in groups of 16,
-    // all loads of a group issued before its updates.
-    const double lm = j > K ? l : 0.0;
-    constexpr int I0 = K + 1, NI = kB - I0;
+        const double inv = kk ? recip_sqrt(d) : 0.0;
+        if (i == 0) {
+            keep[c0 + k] = kk ? 1 : 0;
+            ip[c0 + k] = inv;
+        }
+        const double l = kk && i >= c0 + k ? p[k] * inv : 0.0;
+        p[k] = l;
 #pragma unroll
-    for (int c = 0; c < NI; c += 16) {
-        double li[16];
-#pragma unroll
-        for (int u = 0; u < 16; ++u)
-            if (c + u < NI) li[u] = A[K * kSP + I0 + c + u];
-        __builtin_amdgcn_sched_barrier(0);  // the group's loads stay ahead of its updates
-#pragma unroll
-        for (int u = 0; u < 16; ++u)
-            if (c + u < NI) a[I0 + c + u] = __builtin_fma(-li[u], lm, a[I0 + c + u]);
+        for (int j = k + 1; j < kBlk; ++j) p[j] = __builtin_fma(-l, read_lane(l, c0 + j), p[j]);
     }
+#pragma unroll
+    for (int j = 0; j < kBlk; ++j)
+        if (i >= c0) A[i * kSP + c0 + j] = p[j];
 }
 
-template <int... K>
-__device__ __forceinline__ void chol_steps(std::integer_sequence<int, K...>, double (&a)[kB], int j,
-                                           unsigned long long usem, int mode, double tau, double* A, int* keep,
-                                           bool& badk)
+// X = L^-1 for the Cholesky factor L of the symmetric matrix in A (lower
+// triangle; overwritten), taking columns in order and restricted to the kept
+// ones (rows and columns not kept are zero in X).  mode 0: every column in `use`
+// must have a positive pivot (bad = 1 otherwise); mode 1: a column whose pivot
+// is <= tau is dropped.  Called by the whole workgroup.
+__device__ __forceinline__ void small_inverse_factor(double* A, const int* use, int mode, double tau, int* keep,
+                                                     double* ip, int* bad, double* X)
 {
-    (chol_step<K>(a, j, usem, mode, tau, A, keep, badk), ...);
-}
-
-__device__ __forceinline__ void small_cholesky(double* A, const int* use, int mode, double tau, int* keep, int* bad)
-{
-    if (threadIdx.x < kB) {
-        const int j = threadIdx.x;
-        const unsigned long long usem = __ballot(use[j] != 0);
-        double a[kB];
+    constexpr int NB = kB / kBlk;
+    const int w = threadIdx.x / kWave;
+    const Frag f;
+    unsigned long long usem = 0;
+    if (w == 0) usem = __ballot(use[threadIdx.x] != 0);
+    bool badk = false;
+    for (int b = 0; b < NB; ++b) {
+        if (w == 0) chol_panel(A, b, usem, mode, tau, keep, ip, badk);
+        __syncthreads();
+        // The trailing blocks' lower triangle, a wave per block.
+        int e = 0;
+        for (int ib = b + 1; ib < NB; ++ib)
+            for (int jb = b + 1; jb <= ib; ++jb, ++e) {
+                if (e % NB != w) continue;
+                d4 acc;
 #pragma unroll
-        for (int i = 0; i < kB; ++i) a[i] = A[i >= j ? i * kSP + j : j * kSP + i];
-        // Every lane has read its column before row 0 is overwritten.
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        bool badk = false;
-        chol_steps(std::make_integer_sequence<int, kB>{}, a, j, usem, mode, tau, A, keep, badk);
-        if (j == 0 && badk) *bad = 1;
+                for (int v = 0; v < 4; ++v) acc[v] = A[(kBlk * ib + f.r + 4 * v) * kSP + kBlk * jb + f.c];
+#pragma unroll
+                for (int t = 0; t < 4; ++t)
+                    acc = mfma4(-f.rows(A, kBlk * ib, kBlk * b, t), f.rows(A, kBlk * jb, kBlk * b, t), acc);
+#pragma unroll
+                for (int v = 0; v < 4; ++v) A[(kBlk * ib + f.r + 4 * v) * kSP + kBlk * jb + f.c] = acc[v];
+            }
+        __syncthreads();
+    }
+    if (threadIdx.x == 0 && badk) *bad = 1;
+    // The diagonal blocks of the inverse, a wave per block, a column per lane.
+    {
+        const int c0 = kBlk * w, j = f.c;
+        double x[kBlk];
+#pragma unroll
+        for (int i = 0; i < kBlk; ++i) x[i] = i == j ? 1.0 : 0.0;
+#pragma unroll
+        for (int m = 0; m < kBlk; ++m) {
+            const double xm = x[m] * ip[c0 + m];
+            x[m] = xm;
+#pragma unroll
+            for (int i = m + 1; i < kBlk; ++i) x[i] = __builtin_fma(-A[(c0 + i) * kSP + c0 + m], xm, x[i]);
+        }
+        if (f.r == 0) {
+#pragma unroll
+            for (int i = 0; i < kBlk; ++i) X[(c0 + i) * kSP + c0 + j] = keep[c0 + j] ? x[i] : 0.0;
+        }
+        for (int jb = w + 1; jb < NB; ++jb)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) X[(c0 + f.r + 4 * v) * kSP + kBlk * jb + f.c] = 0.0;
     }
     __syncthreads();
-}
-
-// Step M of the forward substitution (M a template parameter): x_M = r_M /
-// L[M][M], then r_i -= L[i][M] x_M for the rows below, L's column M read from
-// row M of U = L' as broadcasts.
-template <int M>
-__device__ __forceinline__ void inv_step(double (&r)[kB], unsigned long long km, const double* U)
-{
-    if (!((km >> M) & 1ull)) {
-        r[M] = 0.0;
-        return;
-    }
-    const double xm = r[M] / U[M * kSP + M];
-    r[M] = xm;
-    // The row is read in groups of 16, all loads of a group issued before
-    // its updates.
-    constexpr int I0 = M + 1, NI = kB - I0;
+    // Then the diagonals below: X_ij = -X_ii sum over k of L_ik X_kj.  The sum's
+    // slots are the second product's right operands as they are.
+    for (int d = 1; d < NB; ++d) {
+        const int ib = w + d, jb = w;
+        if (ib < NB) {
+            d4 sum = {0.0, 0.0, 0.0, 0.0}, x = {0.0, 0.0, 0.0, 0.0};
+            for (int kb = jb; kb < ib; ++kb)
 #pragma unroll
-    for (int c = 0; c < NI; c += 16) {
-        double ui[16];
+                for (int t = 0; t < 4; ++t)
+                    sum = mfma4(f.rows(A, kBlk * ib, kBlk * kb, t), f.cols(X, kBlk * kb, kBlk * jb, t), sum);
 #pragma unroll
-        for (int u = 0; u < 16; ++u)
-            if (c + u < NI) ui[u] = U[M * kSP + I0 + c + u];
-        __builtin_amdgcn_sched_barrier(0);
+            for (int t = 0; t < 4; ++t) x = mfma4(-f.rows(X, kBlk * ib, kBlk * ib, t), sum[t], x);
 #pragma unroll
-        for (int u = 0; u < 16; ++u)
-            if (c + u < NI) r[I0 + c + u] = __builtin_fma(-ui[u], xm, r[I0 + c + u]);
-    }
-}
-
-template <int... M>
-__device__ __forceinline__ void inv_steps(std::integer_sequence<int, M...>, double (&r)[kB], unsigned long long km,
-                                          const double* U)
-{
-    (inv_step<M>(r, km, U), ...);
-}
-
-// X = Lk^-1 for the factor left in U = L' by small_cholesky, restricted to the
-// kept columns (rows and columns not kept are zero in X).  Wave 0 alone: lane j
-// forms column j by forward substitution in column order (each x_m, once
-// known, updates every row below it, so the updates of a step are
-// independent).
-__device__ __forceinline__ void small_tri_inverse(const double* U, const int* keep, double* X)
-{
-    if (threadIdx.x < kB) {
-        const int j = threadIdx.x;
-        const unsigned long long km = __ballot(keep[j] != 0);
-        const bool mine = ((km >> j) & 1ull) != 0;
-        double r[kB];
-#pragma unroll
-        for (int i = 0; i < kB; ++i) r[i] = i == j ? 1.0 : 0.0;
-        inv_steps(std::make_integer_sequence<int, kB>{}, r, km, U);
-#pragma unroll
-        for (int i = 0; i < kB; ++i) X[i * kSP + j] = mine ? r[i] : 0.0;
-    }
-    __syncthreads();
-}
-
-// C = op(A) B for 64 x 64 LDS matrices (op = transpose if ta), written to
-// out[e] (global, row-major) scaled by `sign`.  Returns whether every entry
-// (of the whole matrix) is finite.
-__device__ bool small_matmul_out(const double* A, int ta, const double* B, double sign, double* out)
-{
-    const int t = threadIdx.x;
-    const int r0 = (t >> 4) * 4, c0 = (t & 15) * 4;
-    double c[4][4] = {};
-    for (int m = 0; m < kB; ++m) {
-        double av[4], bv[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            av[u] = ta ? A[m * kSP + r0 + u] : A[(r0 + u) * kSP + m];
-            bv[u] = B[m * kSP + c0 + u];
+            for (int v = 0; v < 4; ++v) X[(kBlk * ib + f.r + 4 * v) * kSP + kBlk * jb + f.c] = x[v];
         }
-#pragma unroll
-        for (int u = 0; u < 4; ++u)
-#pragma unroll
-            for (int v = 0; v < 4; ++v) c[u][v] += av[u] * bv[v];
+        __syncthreads();
     }
+}
+
+// op(A) B for 64 x 64 LDS matrices (op = transpose if ta): a wave takes 16 rows.
+__device__ __forceinline__ void small_matmul(const double* A, int ta, const double* B, d4 (&c)[4])
+{
+    const int w = threadIdx.x / kWave;
+    const Frag f;
+#pragma unroll
+    for (int jb = 0; jb < 4; ++jb) c[jb] = d4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll 4
+    for (int t = 0; t < kB / 4; ++t) {
+        const double a = ta ? f.cols(A, 0, kBlk * w, t) : f.rows(A, kBlk * w, 0, t);
+#pragma unroll
+        for (int jb = 0; jb < 4; ++jb) c[jb] = mfma4(a, f.cols(B, 0, kBlk * jb, t), c[jb]);
+    }
+}
+
+// The product to out[e] (global, row-major) scaled by `sign`.  Returns whether
+// every entry (of the whole matrix) is finite.
+__device__ __forceinline__ bool small_matmul_out(const double* A, int ta, const double* B, double sign, double* out)
+{
+    const int w = threadIdx.x / kWave;
+    const Frag f;
+    d4 c[4];
+    small_matmul(A, ta, B, c);
     bool finite = true;
 #pragma unroll
-    for (int u = 0; u < 4; ++u)
+    for (int jb = 0; jb < 4; ++jb)
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
-            out[(r0 + u) * kB + c0 + v] = sign * c[u][v];
-            finite = finite && isfinite(c[u][v]);
+            out[(kBlk * w + f.r + 4 * v) * kB + kBlk * jb + f.c] = sign * c[jb][v];
+            finite = finite && isfinite(c[jb][v]);
         }
     return __syncthreads_and(finite ? 1 : 0) != 0;
 }
 
-// The same product into an LDS matrix.
-__device__ void small_matmul_lds(const double* A, int ta, const double* B, double* C)
+// The product into an LDS matrix.
+__device__ __forceinline__ void small_matmul_lds(const double* A, int ta, const double* B, double* C)
 {
-    const int t = threadIdx.x;
-    const int r0 = (t >> 4) * 4, c0 = (t & 15) * 4;
-    double c[4][4] = {};
-    for (int m = 0; m < kB; ++m) {
-        double av[4], bv[4];
+    const int w = threadIdx.x / kWave;
+    const Frag f;
+    d4 c[4];
+    small_matmul(A, ta, B, c);
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            av[u] = ta ? A[m * kSP + r0 + u] : A[(r0 + u) * kSP + m];
-            bv[u] = B[m * kSP + c0 + u];
-        }
+    for (int jb = 0; jb < 4; ++jb)
 #pragma unroll
-        for (int u = 0; u < 4; ++u)
-#pragma unroll
-            for (int v = 0; v < 4; ++v) c[u][v] += av[u] * bv[v];
-    }
-    __syncthreads();
-#pragma unroll
-    for (int u = 0; u < 4; ++u)
-#pragma unroll
-        for (int v = 0; v < 4; ++v) C[(r0 + u) * kSP + c0 + v] = c[u][v];
+        for (int v = 0; v < 4; ++v) C[(kBlk * w + f.r + 4 * v) * kSP + kBlk * jb + f.c] = c[jb][v];
     __syncthreads();
 }
 
@@ -573,17 +638,16 @@ __device__ void load_small(const double* src, double* dst)
 __global__ __launch_bounds__(kSmallBS) void k_bc_alpha(BcState* st, int gate)
 {
     if (bc_stopped(st, gate)) return;
-    __shared__ double A[kB * kSP], X[kB * kSP], T[kB * kSP];
+    __shared__ double A[kB * kSP], X[kB * kSP], T[kB * kSP], ip[kB];
     __shared__ int use[kB], keep[kB], bad;
     if (threadIdx.x == 0) bad = 0;
     if (threadIdx.x < kB) use[threadIdx.x] = st->live[threadIdx.x];
     load_small(st->G0, A);
-    small_cholesky(A, use, 0, 0.0, keep, &bad);
+    small_inverse_factor(A, use, 0, 0.0, keep, ip, &bad, X);
     if (bad) {
         if (threadIdx.x == 0) st->status = BC_BREAKDOWN;
         return;
     }
-    small_tri_inverse(A, keep, X);
     for (int e = threadIdx.x; e < kBB; e += kSmallBS) st->Li[e] = X[(e / kB) * kSP + e % kB];
     load_small(st->G1, A);
     small_matmul_lds(X, 0, A, T);                             // T = Li Psi
@@ -630,9 +694,8 @@ __global__ __launch_bounds__(kSmallBS) void k_bc_beta(BcState* st, int gate)
 __global__ __launch_bounds__(kSmallBS) void k_bc_orth(BcState* st, int pass, int gate)
 {
     if (bc_stopped(st, gate)) return;
-    __shared__ double A[kB * kSP], X[kB * kSP], scale[kB];
+    __shared__ double A[kB * kSP], X[kB * kSP], scale[kB], ip[kB];
     __shared__ int use[kB], keep[kB], bad;
-    __shared__ double shift;
     const int t = threadIdx.x;
     load_small(st->G0, A);
     if (t < kB) {
@@ -648,18 +711,15 @@ __global__ __launch_bounds__(kSmallBS) void k_bc_orth(BcState* st, int pass, int
             A[i * kSP + j] *= scale[i] * scale[j];
         }
         __syncthreads();
-        if (t == 0) {
-            double tr = 0.0;
-            for (int j = 0; j < kB; ++j) tr += A[j * kSP + j];
+        if (t < kB) {
+            double tr = A[t * kSP + t];
+            for (int off = kB / 2; off > 0; off /= 2) tr += __shfl_xor(tr, off);
             const double s = (double)st->s, n = (double)st->n;
-            shift = 11.0 * (n * s + s * (s + 1.0)) * 0x1p-53 * tr;
+            A[t * kSP + t] += 11.0 * (n * s + s * (s + 1.0)) * 0x1p-53 * tr;
         }
         __syncthreads();
-        if (t < kB) A[t * kSP + t] += shift;
-        __syncthreads();
     }
-    small_cholesky(A, use, 1, pass == 0 ? 0.0 : st->tau, keep, &bad);
-    small_tri_inverse(A, keep, X);
+    small_inverse_factor(A, use, 1, pass == 0 ? 0.0 : st->tau, keep, ip, &bad, X);
     // M[i][j] = scale_i X[j][i]
     for (int e = t; e < kBB; e += kSmallBS) {
         const int i = e / kB, j = e % kB;
@@ -681,15 +741,27 @@ __global__ __launch_bounds__(kSmallBS) void k_bc_orth(BcState* st, int pass, int
 // BREAKDOWN on a non-finite value, else RUN.  mode 1 (check of a PENDING
 // state): CONVERGED if every true residual passes, else RUN and one more
 // restart.  mode 2 (report): rr = ||b - A x||^2 only.
-__global__ void k_bc_scalars(BcState* st, const double* __restrict__ part, int G, int mode)
+__global__ __launch_bounds__(1024) void k_bc_scalars(BcState* st, const double* __restrict__ part, int G, int mode)
 {
-    __shared__ double rr[kB], bb[kB];
+    __shared__ double rr[kB], bb[kB], sums[16][2][kB];
     const int t = threadIdx.x;
+    {
+        // A wave takes every 16th workgroup's partials; the waves' sums in order.
+        double a = 0.0, b = 0.0;
+        const int j = t % kB, w = t / kB;
+        for (int g = w; g < G; g += 16) {
+            a += part[((size_t)g * 2 + 0) * kB + j];
+            b += part[((size_t)g * 2 + 1) * kB + j];
+        }
+        sums[w][0][j] = a;
+        sums[w][1][j] = b;
+        __syncthreads();
+    }
     if (t < kB) {
         double a = 0.0, b = 0.0;
-        for (int g = 0; g < G; ++g) {
-            a += part[((size_t)g * 2 + 0) * kB + t];
-            b += part[((size_t)g * 2 + 1) * kB + t];
+        for (int w = 0; w < 16; ++w) {
+            a += sums[w][0][t];
+            b += sums[w][1][t];
         }
         rr[t] = a;
         bb[t] = b;
@@ -728,7 +800,7 @@ __global__ void k_bc_scalars(BcState* st, const double* __restrict__ part, int G
 struct cg_block {
     int gram_G = 0, gemm_G = 0, spmm_G = 0, gram_rpw = 0, res_G = 0, chunk = 4;
     double* work = nullptr;  // B, X, R, Z, P, Q, W: 7 n x 64 blocks
-    double* part = nullptr;  // Gram partials [gram_G][2][4096]
+    double* part = nullptr;  // Gram partials [gram_G][2][4096], [gemm_G][4096]
     double* part2 = nullptr; // norm / residual partials [max(gemm_G, res_G)][2][64]
     jpcg::BcState* st = nullptr;
     jpcg::BcState* hst = nullptr;
@@ -782,15 +854,19 @@ struct BcOps {
         void* a[] = {&m, &X, &Y, &b->spmm_G, &b->st, &gate};
         launch((const void*)k_bc_spmm, b->spmm_G, kSpmmBS, st, a);
     }
+    void sum_grams(int nop, int G, int gate)
+    {
+        int count = nop * kBB, which = 0;
+        void* r[] = {&b->part, &G, &count, &which, &b->st, &gate};
+        launch((const void*)k_bc_sum<32>, count / 32, 256, st, r);
+    }
     void gram(const double* U, const double* V0, const double* V1, int gate)
     {
         int n = c->n;
         const int nop = V1 ? 2 : 1;
-        void* a[] = {&n, &U, &V0, &V1, &b->part, &b->gram_rpw, &b->gram_G, &b->st, &gate};
+        void* a[] = {&n, &U, &V0, &V1, &c->dinv, &b->part, &b->gram_rpw, &b->gram_G, &b->st, &gate};
         launch(nop == 2 ? (const void*)k_bc_gram<2> : (const void*)k_bc_gram<1>, b->gram_G, kGramBS, st, a);
-        int count = nop * kBB, which = 0;
-        void* r[] = {&b->part, &b->gram_G, &count, &which, &b->st, &gate};
-        launch((const void*)k_bc_sum<32>, count / 32, 256, st, r);
+        sum_grams(nop, b->gram_G, gate);
     }
     void norms(int gate)
     {
@@ -798,43 +874,51 @@ struct BcOps {
         void* r[] = {&b->part2, &b->gemm_G, &count, &which, &b->st, &gate};
         launch((const void*)k_bc_sum<4>, kB / 4, 256, st, r);
     }
-    void gemm(int mode, const double* U, double* Y, double* Z, int gate)
+    // With `grams` also Y'Y.
+    void gemm(int mode, const double* U, double* Y, const double* Z, int gate, bool grams = false)
     {
-        BcGemmArgs g{c->n, U, Y, Z, c->dinv, b->part2, b->gemm_G};
+        BcGemmArgs g{c->n, U, Y, Z, c->dinv, b->part2, b->part, b->gemm_G};
         void* a[] = {&g, &b->st, &gate};
-        const void* fn = mode == BC_XUP   ? (const void*)k_bc_gemm<BC_XUP>
-                         : mode == BC_RUP ? (const void*)k_bc_gemm<BC_RUP>
-                         : mode == BC_DIR ? (const void*)k_bc_gemm<BC_DIR>
-                                          : (const void*)k_bc_gemm<BC_APPLY>;
+        const void* fn = mode == BC_XUP     ? (const void*)k_bc_gemm<BC_XUP, false>
+                         : mode == BC_RUP   ? (const void*)k_bc_gemm<BC_RUP, false>
+                         : mode == BC_DIR   ? (const void*)k_bc_gemm<BC_DIR, true>
+                         : mode == BC_SCALE ? (const void*)k_bc_gemm<BC_SCALE, true>
+                         : grams            ? (const void*)k_bc_gemm<BC_APPLY, true>
+                                            : (const void*)k_bc_gemm<BC_APPLY, false>;
         launch(fn, b->gemm_G, kGemmBS, st, a);
+        if (grams) sum_grams(1, b->gemm_G, gate);
     }
     void orth_pass(int pass, int gate)
     {
         void* a[] = {&b->st, &pass, &gate};
         launch((const void*)k_bc_orth, 1, kSmallBS, st, a);
     }
-    // P = orth(W0): three CholeskyQR passes, the blocks in W0 -> Wa -> Wb -> P.
-    void orth(double* W0, double* Wa, double* Wb, int gate)
+    // P = orth(W0): three CholeskyQR passes, the blocks in W0 -> Wa -> Wb -> P;
+    // W0's Gram matrix is there.
+    void orth(const double* W0, double* Wa, double* Wb, int gate)
     {
-        gram(W0, W0, nullptr, gate);
         orth_pass(0, gate);
-        gemm(BC_APPLY, W0, Wa, nullptr, gate);
-        gram(Wa, Wa, nullptr, gate);
+        gemm(BC_APPLY, W0, Wa, nullptr, gate, true);
         orth_pass(1, gate);
-        gemm(BC_APPLY, Wa, Wb, nullptr, gate);
-        gram(Wb, Wb, nullptr, gate);
+        gemm(BC_APPLY, Wa, Wb, nullptr, gate, true);
         orth_pass(2, gate);
         gemm(BC_APPLY, Wb, v.P, nullptr, gate);
     }
-    // R = B - A X, Z = M^-1 R (write), partials of r'r, b'b; then the scalars.
+    // P = orth(M^-1 R): the first direction.
+    void start()
+    {
+        gemm(BC_SCALE, nullptr, v.W, v.R, 0, true);
+        orth(v.W, v.Z, v.Q, 0);
+    }
+    // R = B - A X (write), partials of r'r, b'b; then the scalars.
     void residual(int write, int mode)
     {
         spmm(v.X, v.Q, 0);
         int n = c->n;
-        void* a[] = {&n, &v.B, &v.Q, &c->dinv, &v.R, &v.Z, &b->part2, &write};
+        void* a[] = {&n, &v.B, &v.Q, &v.R, &b->part2, &write};
         launch((const void*)k_bc_residual, b->res_G, 256, st, a);
         void* s[] = {&b->st, &b->part2, &b->res_G, &mode};
-        launch((const void*)k_bc_scalars, 1, 64, st, s);
+        launch((const void*)k_bc_scalars, 1, 1024, st, s);
     }
     // One gated iteration.
     void iteration()
@@ -845,12 +929,12 @@ struct BcOps {
         void* a[] = {&b->st, &gate};
         launch((const void*)k_bc_alpha, 1, kSmallBS, st, a);
         gemm(BC_XUP, v.P, v.X, nullptr, 1);
-        gemm(BC_RUP, v.Q, v.R, v.Z, 1);
+        gemm(BC_RUP, v.Q, v.R, nullptr, 1);
         norms(1);
-        gram(v.Q, v.Z, nullptr, 1);
+        gram(v.Q, v.R, nullptr, 1);
         void* bta[] = {&b->st, &gate};
         launch((const void*)k_bc_beta, 1, kSmallBS, st, bta);
-        gemm(BC_DIR, v.P, v.W, v.Z, 1);
+        gemm(BC_DIR, v.P, v.W, v.R, 1, true);
         // W -> Z -> Q -> P (Z and Q are free until the next iteration's product)
         orth(v.W, v.Z, v.Q, 1);
     }
@@ -864,11 +948,11 @@ static cg_block* make_block(cg_ctx* c)
         b->gram_G = std::max(8, std::min(c->cus, (c->n + 63) / 64) / 8 * 8);
         b->gram_rpw = (c->n + b->gram_G - 1) / b->gram_G;
         const int tiles = (c->n + 15) / 16;
-        b->gemm_G = std::max(8, std::min(c->cus * 2, (tiles + 3) / 4) / 8 * 8);
+        b->gemm_G = std::max(8, std::min(c->cus, (tiles + kGemmWaves - 1) / kGemmWaves) / 8 * 8);
         b->spmm_G = spmm_grid(c, spmm_blocks_per_cu(c));
         b->res_G = std::min(1024, (c->n + 3) / 4);
         JPCG_HIP(hipMalloc(&b->work, sizeof(double) * nb * 7));
-        JPCG_HIP(hipMalloc(&b->part, sizeof(double) * (size_t)b->gram_G * 2 * kBB));
+        JPCG_HIP(hipMalloc(&b->part, sizeof(double) * (size_t)std::max(2 * b->gram_G, b->gemm_G) * kBB));
         JPCG_HIP(hipMalloc(&b->part2, sizeof(double) * (size_t)std::max(b->gemm_G, b->res_G) * 2 * kB));
         JPCG_HIP(hipMalloc(&b->st, sizeof(BcState)));
         JPCG_HIP(hipHostMalloc(&b->hst, sizeof(BcState), hipHostMallocDefault));
@@ -956,7 +1040,7 @@ int cg_solve_block(cg_ctx* c, const double* B, double* X, int32_t s, double tol,
         ops.residual(1, 0);
         BcState h = bc_read(c, b);
         if (h.status == BC_RUN) {
-            ops.orth(ops.v.Z, ops.v.W, ops.v.Q, 0);
+            ops.start();
             const long long guard = 2LL * maxit + 64;
             long long launched = 0;
             while (true) {
@@ -975,7 +1059,7 @@ int cg_solve_block(cg_ctx* c, const double* B, double* X, int32_t s, double tol,
                         } else {
                             for (int j = 0; j < kB; ++j) b->hst->live[j] = 1;
                             JPCG_HIP(hipMemcpyAsync(b->st->live, b->hst->live, sizeof(int) * kB, hipMemcpyHostToDevice, st));
-                            ops.orth(ops.v.Z, ops.v.W, ops.v.Q, 0);
+                            ops.start();
                         }
                     }
                 }
