@@ -74,10 +74,13 @@ __device__ __forceinline__ bool bc_stopped(const BcState* st, int gate)
 // block of 16 columns.  Each wave accumulates all 16 output tiles of its
 // operand over its rows; waves of a workgroup are added in LDS in wave order
 // and each workgroup writes one partial per operand.
-// NOP = 2: waves 0, 1 take V0 and waves 2, 3 take V1 (U is read twice, from L2).
+// NOP = 2: half the waves take V0 and half V1 (U is read twice, from L2).
 // NOP = 1: V0's rows are scaled (Q'Z with Z = M^-1 R formed here).
+// Bound by the loads in flight: 8 waves a CU with 8 KB each ahead; 51^3, three
+// blocks (204 MB) 54 us against 69 with 4 waves and 4 KB, two 33 against 39.
 // ---------------------------------------------------------------------------
-constexpr int kGramBS = 256;
+constexpr int kGramBS = 512;
+constexpr int kGramStep = 8;  // rows of a wave's step
 
 template <int NOP>
 __global__ __launch_bounds__(kGramBS, 2) void k_bc_gram(int n, const double* __restrict__ U,
@@ -89,7 +92,7 @@ __global__ __launch_bounds__(kGramBS, 2) void k_bc_gram(int n, const double* __r
     __shared__ double red[NOP][kBB];
     const int L = xcd_logical_block((int)blockIdx.x, G);
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    constexpr int kWavesPerOp = 4 / NOP;
+    constexpr int kWavesPerOp = kGramBS / kWave / NOP;
     const int op = w / kWavesPerOp, sub = w % kWavesPerOp;
     const double* __restrict__ V = op == 0 ? V0 : V1;
     const int rs = min(L * rows_per_wg, n), re = min(rs + rows_per_wg, n);
@@ -99,34 +102,44 @@ __global__ __launch_bounds__(kGramBS, 2) void k_bc_gram(int n, const double* __r
 #pragma unroll
         for (int jb = 0; jb < 4; ++jb) acc[ib][jb] = d4{0.0, 0.0, 0.0, 0.0};
     const int rq = lane >> 4, cq = lane & 15;
-    // The loads of the next 4-row step are issued before this step's products.
-    double a[4], b[4], d = 1.0;
+    // The loads of the next step are issued before this step's products.
+    constexpr int Q = kGramStep / 4;
+    double a[Q][4], b[Q][4], d[Q];
     auto fetch = [&](int r0) {
-        const int row = r0 + rq;
-        const bool ok = row < re;
-        const size_t o = (size_t)(ok ? row : rs) * kB + cq;
-        if (NOP == 1) d = scale[ok ? row : rs];
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            a[q] = ok ? U[o + 16 * q] : 0.0;
-            b[q] = ok ? V[o + 16 * q] : 0.0;
+        for (int h = 0; h < Q; ++h) {
+            const int row = r0 + 4 * h + rq;
+            const bool ok = row < re;
+            const size_t o = (size_t)(ok ? row : rs) * kB + cq;
+            d[h] = 1.0;
+            if (NOP == 1) d[h] = scale[ok ? row : rs];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                a[h][q] = ok ? U[o + 16 * q] : 0.0;
+                b[h][q] = ok ? V[o + 16 * q] : 0.0;
+            }
         }
     };
-    int r0 = rs + 4 * sub;
+    int r0 = rs + kGramStep * sub;
     if (r0 < re) fetch(r0);
     while (r0 < re) {
-        double ca[4], cb[4];
+        double ca[Q][4], cb[Q][4];
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            ca[q] = a[q];
-            cb[q] = NOP == 1 ? d * b[q] : b[q];
-        }
-        r0 += 4 * kWavesPerOp;
+        for (int h = 0; h < Q; ++h)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                ca[h][q] = a[h][q];
+                cb[h][q] = NOP == 1 ? d[h] * b[h][q] : b[h][q];
+            }
+        r0 += kGramStep * kWavesPerOp;
         if (r0 < re) fetch(r0);
 #pragma unroll
-        for (int ib = 0; ib < 4; ++ib)
+        for (int h = 0; h < Q; ++h)
 #pragma unroll
-            for (int jb = 0; jb < 4; ++jb) acc[ib][jb] = __builtin_amdgcn_mfma_f64_16x16x4f64(ca[ib], cb[jb], acc[ib][jb], 0, 0, 0);
+            for (int ib = 0; ib < 4; ++ib)
+#pragma unroll
+                for (int jb = 0; jb < 4; ++jb)
+                    acc[ib][jb] = __builtin_amdgcn_mfma_f64_16x16x4f64(ca[h][ib], cb[h][jb], acc[ib][jb], 0, 0, 0);
     }
     // Add the waves of each operand in wave order.
     for (int t = 0; t < kWavesPerOp; ++t) {
@@ -425,21 +438,22 @@ __global__ void k_bc_pack(int n, int s, const double* __restrict__ src, double* 
 // updates.  In blocks of 16 columns a step updates the block's later columns
 // only, from v_readlane broadcasts, with a reciprocal square root in place of
 // root and division; what is left and the blocks of the inverse are products
-// for the matrix cores: 31 us.
+// for the matrix cores: 21 us (31 with branches in the steps and with loads that
+// each waited to be stored).
 // ---------------------------------------------------------------------------
 constexpr int kSmallBS = 256;
 constexpr int kSP = 65;  // LDS pitch
 constexpr int kBlk = 16;
 
-// 1 / sqrt(d) for d > 0: the hardware's estimate and two Newton steps.
+// 1 / sqrt(d) for a normal d > 0: the hardware's estimate and two
+// third-order Newton steps (the second one rounds).
 __device__ __forceinline__ double recip_sqrt(double d)
 {
-    if (d < 0x1p-900 || d > 0x1p900) return 1.0 / sqrt(d);
     double x = __builtin_amdgcn_rsq(d);
 #pragma unroll
     for (int u = 0; u < 2; ++u) {
         const double e = __builtin_fma(-d * x, x, 1.0);
-        x = __builtin_fma(0.5 * x, e, x);
+        x = __builtin_fma(x * e, __builtin_fma(0.375, e, 0.5), x);
     }
     return x;
 }
@@ -472,32 +486,29 @@ __device__ __forceinline__ void chol_panel(double* A, int b, unsigned long long 
                                            double* ip, bool& bad)
 {
     const int i = threadIdx.x, c0 = kBlk * b;
-    double p[kBlk];
+    double p[kBlk], mine = 0.0;
 #pragma unroll
     for (int j = 0; j < kBlk; ++j) p[j] = i >= c0 ? A[i * kSP + c0 + j] : 0.0;
+    const unsigned used = (unsigned)(usem >> c0) & 0xffffu;
+    unsigned kept = 0;
+    // Straight through: a branch costs more than what it would leave out.
 #pragma unroll
     for (int k = 0; k < kBlk; ++k) {
         const double d = read_lane(p[k], c0 + k);
-        bool kk = ((usem >> (c0 + k)) & 1ull) != 0;
-        if (kk) {
-            if (mode == 0) {
-                if (!(d > 0.0) || !isfinite(d)) {
-                    bad = true;
-                    kk = false;
-                }
-            } else if (!(d > tau)) {
-                kk = false;
-            }
-        }
-        const double inv = kk ? recip_sqrt(d) : 0.0;
-        if (i == 0) {
-            keep[c0 + k] = kk ? 1 : 0;
-            ip[c0 + k] = inv;
-        }
-        const double l = kk && i >= c0 + k ? p[k] * inv : 0.0;
+        const bool u = (used >> k) & 1u;
+        const bool kk = u & (mode == 0 ? (d > 0.0) & (d < __builtin_huge_val()) : d > tau);
+        bad |= mode == 0 && u && !kk;
+        kept |= (unsigned)kk << k;
+        const double inv = kk ? recip_sqrt(kk ? d : 1.0) : 0.0;
+        mine = i == c0 + k ? inv : mine;
+        const double l = kk & (i >= c0 + k) ? p[k] * inv : 0.0;
         p[k] = l;
 #pragma unroll
         for (int j = k + 1; j < kBlk; ++j) p[j] = __builtin_fma(-l, read_lane(l, c0 + j), p[j]);
+    }
+    if (i >= c0 && i < c0 + kBlk) {
+        keep[i] = (kept >> (i - c0)) & 1u;
+        ip[i] = mine;
     }
 #pragma unroll
     for (int j = 0; j < kBlk; ++j)
@@ -629,7 +640,14 @@ __device__ __forceinline__ void small_matmul_lds(const double* A, int ta, const 
 
 __device__ void load_small(const double* src, double* dst)
 {
-    for (int e = threadIdx.x; e < kBB; e += kSmallBS) dst[(e / kB) * kSP + e % kB] = src[e];
+    double v[kBB / kSmallBS];  // all loads in flight together
+#pragma unroll
+    for (int u = 0; u < kBB / kSmallBS; ++u) v[u] = src[threadIdx.x + u * kSmallBS];
+#pragma unroll
+    for (int u = 0; u < kBB / kSmallBS; ++u) {
+        const int e = threadIdx.x + u * kSmallBS;
+        dst[(e / kB) * kSP + e % kB] = v[u];
+    }
     __syncthreads();
 }
 
