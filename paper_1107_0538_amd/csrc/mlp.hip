@@ -173,20 +173,32 @@ struct AdamArgs {
     float lr, b1, b2, eps, c1, c2;
     int update;  // 0: the gradient is stored, 1: Adam's step is taken
 };
-__device__ __forceinline__ void adam_step(const AdamArgs& a, int64_t i, float gi)
-{
-    const float mi = a.b1 * a.m[i] + (1.f - a.b1) * gi;
-    const float vi = a.b2 * a.v[i] + (1.f - a.b2) * gi * gi;
-    a.m[i] = mi;
-    a.v[i] = vi;
-    const float pi = a.p[i] - a.lr * (mi / a.c1) / (sqrtf(vi / a.c2) + a.eps);
-    a.p[i] = pi;
-    if (a.pb) a.pb[i] = f2bf(pi);
-}
+struct AdamState {
+    float p, m, v;
+    __device__ __forceinline__ void load(const AdamArgs& a, int64_t i)
+    {
+        p = a.p[i];
+        m = a.m[i];
+        v = a.v[i];
+    }
+    __device__ __forceinline__ void step(const AdamArgs& a, int64_t i, float gi) const
+    {
+        const float mi = __builtin_fmaf(1.f - a.b1, gi, a.b1 * m);
+        const float vi = __builtin_fmaf((1.f - a.b2) * gi, gi, a.b2 * v);
+        a.m[i] = mi;
+        a.v[i] = vi;
+        const float pi = p - a.lr * (mi / a.c1) / (sqrtf(vi / a.c2) + a.eps);
+        a.p[i] = pi;
+        if (a.pb) a.pb[i] = f2bf(pi);
+    }
+};
 __global__ void k_adam(int64_t n, AdamArgs a)
 {
-    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
-        adam_step(a, i, a.g[i]);
+    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
+        AdamState w;
+        w.load(a, i);
+        w.step(a, i, a.g[i]);
+    }
 }
 
 __global__ void k_to_bf16(int64_t n, const float* __restrict__ in, bf16* __restrict__ out)
@@ -202,7 +214,7 @@ __global__ void k_to_bf16(int64_t n, const float* __restrict__ in, bf16* __restr
 // whole reduction in stages of 16, and the sums over the batch, the bias, the
 // activation and its derivative, the splits' sum and Adam were launches of their
 // own: 22 a step, 410 us with a batch and hidden layers of 256 (24 inputs, 64
-// outputs); 82 as it is, in six launches.  Here a workgroup forms 16 x 16 outputs, an output per thread, from
+// outputs); 46 as it is, in six launches.  Here a workgroup forms 16 x 16 outputs, an output per thread, from
 // panels of 256 along the reduction held in LDS, and applies what follows in
 // registers.  What bounds it is latency: a panel's loads, the chain of
 // additions, the launch.
@@ -218,35 +230,52 @@ struct SmallPanels {
     float b[ST][SP];
 };
 
-// p[r][k] = f(r, k) for k < kn, 0 from there to a multiple of 16; neighbouring
-// threads take neighbouring k (ALONG) or neighbouring rows, whichever lie
-// together in memory.
-template <bool ALONG, typename F>
-__device__ __forceinline__ void small_panel(float (&p)[ST][SP], int kn, F f)
-{
-    const int t = threadIdx.x;
-    if (ALONG) {
-        if (t < (kn + 15) / 16 * 16) {
-            float v[ST];
+// p[r][k] = f(r, k) for r < rows and k < kn, else 0 (k to a multiple of 16).
+// Neighbouring threads take neighbouring k (ALONG) or neighbouring rows,
+// whichever lie together in memory.  A panel's loads are sent one after the
+// other from addresses that are always good, and looked at when all are sent:
+// a conversion or a branch at each would wait for it (a layer of 256 forward 10.5
+// us, backward 16.5; with the loads apart from their use 6.6 and 8.4).
+template <typename T>
+struct SmallLoads {
+    T v[ST];
+    template <bool ALONG, typename F>
+    __device__ __forceinline__ void send(int rows, int kn, F f)
+    {
+        const int t = threadIdx.x;
+        if (ALONG) {
+            const int k = min(t, kn - 1);
 #pragma unroll
-            for (int r = 0; r < ST; ++r) v[r] = t < kn ? f(r, t) : 0.f;
+            for (int r = 0; r < ST; ++r) v[r] = f(min(r, rows - 1), k);
+        } else {
+            const int r = min(t % ST, rows - 1);
 #pragma unroll
-            for (int r = 0; r < ST; ++r) p[r][t] = v[r];
+            for (int j = 0; j < SK / ST; ++j) v[j] = f(r, min(t / ST + ST * j, kn - 1));
         }
-    } else {
-        const int r = t % ST, kk = t / ST;
-        float v[SK / ST];
-#pragma unroll
-        for (int j = 0; j < SK / ST; ++j) v[j] = kk + ST * j < kn ? f(r, kk + ST * j) : 0.f;
-#pragma unroll
-        for (int j = 0; j < SK / ST; ++j) p[r][kk + ST * j] = v[j];
     }
-}
+    template <bool ALONG, typename C>
+    __device__ __forceinline__ void keep(float (&p)[ST][SP], int rows, int kn, C convert) const
+    {
+        const int t = threadIdx.x;
+        if (ALONG) {
+#pragma unroll
+            for (int r = 0; r < ST; ++r) p[r][t] = r < rows && t < kn ? convert(v[r], r, t) : 0.f;
+        } else {
+            const int r = t % ST;
+#pragma unroll
+            for (int j = 0; j < SK / ST; ++j) {
+                const int k = t / ST + ST * j;
+                p[r][k] = r < rows && k < kn ? convert(v[j], r, k) : 0.f;
+            }
+        }
+    }
+};
+static_assert(SK == 256 && SK / ST == ST, "a thread holds 16 of a panel's values either way");
 
-// acc += sum over k < kn of a[m][k] b[n][k], k ascending.
-__device__ __forceinline__ float small_dot(const SmallPanels& s, int m, int n, int kn, float acc)
+// acc += sum over k_lo <= k < kn of a[m][k] b[n][k], k ascending (k_lo a multiple of 16).
+__device__ __forceinline__ float small_dot(const SmallPanels& s, int m, int n, int k_lo, int kn, float acc)
 {
-    for (int k = 0; k < kn; k += 16) {
+    for (int k = k_lo; k < kn; k += 16) {
         float4 av[4], bv[4];
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
@@ -292,20 +321,25 @@ __global__ __launch_bounds__(256) void k_small_forward(SmallForward<TW> f)
     float acc = 0.f;
     for (int k0 = 0; k0 < f.K; k0 += SK) {
         const int kn = min(SK, f.K - k0);
+        SmallLoads<TW> la, lb;
+        SmallLoads<float> lx;
+        auto at = [&](int r, int k) { return (int64_t)(mb + r) * f.K + k0 + k; };
+        if (f.X) lx.template send<true>(f.M - mb, kn, [&](int r, int k) { return f.X[at(r, k)]; });
+        else la.template send<true>(f.M - mb, kn, [&](int r, int k) { return f.in[at(r, k)]; });
+        lb.template send<true>(f.N - nb, kn, [&](int r, int k) { return f.W[(int64_t)(nb + r) * f.K + k0 + k]; });
         if (k0) __syncthreads();
-        small_panel<true>(s.a, kn, [&](int r, int k) {
-            if (mb + r >= f.M) return 0.f;
-            const int64_t e = (int64_t)(mb + r) * f.K + k0 + k;
-            if (!f.X) return to_f(f.in[e]);
-            const TW v = from_f<TW>(f.X[e]);
-            if (nb == 0) f.H0[e] = v;
-            return to_f(v);
-        });
-        small_panel<true>(s.b, kn, [&](int r, int k) {
-            return nb + r < f.N ? to_f(f.W[(int64_t)(nb + r) * f.K + k0 + k]) : 0.f;
-        });
+        if (f.X) {
+            lx.template keep<true>(s.a, f.M - mb, kn, [&](float x, int r, int k) {
+                const TW v = from_f<TW>(x);
+                if (nb == 0) f.H0[at(r, k)] = v;
+                return to_f(v);
+            });
+        } else {
+            la.template keep<true>(s.a, f.M - mb, kn, [](TW v, int, int) { return to_f(v); });
+        }
+        lb.template keep<true>(s.b, f.N - nb, kn, [](TW v, int, int) { return to_f(v); });
         __syncthreads();
-        acc = small_dot(s, m, n, kn, acc);
+        acc = small_dot(s, m, n, 0, kn, acc);
     }
     double l = 0.0;
     if (mb + m < f.M && nb + n < f.N) {
@@ -367,20 +401,23 @@ __global__ __launch_bounds__(256) void k_small_backward(SmallBackward<TW> f)
     if (tile < f.through.tiles) {
         const SmallThrough<TW>& t = f.through;
         const int across = (t.N + ST - 1) / ST, mb = tile / across * ST, nb = tile % across * ST;
+        const float u = t.U[(int64_t)min(mb + m, t.M - 1) * t.N + min(nb + n, t.N - 1)];
         float acc = 0.f;
         for (int k0 = 0; k0 < t.K; k0 += SK) {
             const int kn = min(SK, t.K - k0);
+            SmallLoads<float> la;
+            SmallLoads<TW> lb;
+            la.template send<true>(t.M - mb, kn, [&](int r, int k) { return t.D[(int64_t)(mb + r) * t.K + k0 + k]; });
+            lb.template send<false>(t.N - nb, kn, [&](int r, int k) { return t.W[(int64_t)(k0 + k) * t.N + nb + r]; });
             if (k0) __syncthreads();
-            small_panel<true>(s.a, kn, [&](int r, int k) { return mb + r < t.M ? t.D[(int64_t)(mb + r) * t.K + k0 + k] : 0.f; });
-            small_panel<false>(s.b, kn, [&](int r, int k) {
-                return nb + r < t.N ? to_f(t.W[(int64_t)(k0 + k) * t.N + nb + r]) : 0.f;
-            });
+            la.template keep<true>(s.a, t.M - mb, kn, [](float v, int, int) { return v; });
+            lb.template keep<false>(s.b, t.N - nb, kn, [](TW v, int, int) { return to_f(v); });
             __syncthreads();
-            acc = small_dot(s, m, n, kn, acc);
+            acc = small_dot(s, m, n, 0, kn, acc);
         }
         if (mb + m < t.M && nb + n < t.N) {
             const int64_t e = (int64_t)(mb + m) * t.N + nb + n;
-            const float u = t.U[e], sg = sigmoidf_(u);
+            const float sg = sigmoidf_(u);
             t.Dn[e] = acc * (sg * (1.f + u * (1.f - sg)));
         }
         return;
@@ -390,31 +427,59 @@ __global__ __launch_bounds__(256) void k_small_backward(SmallBackward<TW> f)
     if (second) tile -= f.w[0].tiles;
     const SmallWeights<TW>& t = second ? f.w[1] : f.w[0];
     const int across = (t.N + ST - 1) / ST, mb = tile / across * ST, nb = tile % across * ST;
-    const bool biases = nb == 0 && threadIdx.x < ST;
+    const bool mine = mb + m < t.M && nb + n < t.N;
+    const bool biases = nb == 0 && threadIdx.x < ST && mb + (int)threadIdx.x < t.M;
+    // The parameters' state is on its way while the sums are formed.
+    AdamState w, wb;
+    const int64_t iw = t.at + (int64_t)(mb + m) * t.N + nb + n, ib = t.at + (int64_t)t.M * t.N + mb + threadIdx.x;
+    if (f.adam.update && mine) w.load(f.adam, iw);
+    if (f.adam.update && biases) wb.load(f.adam, ib);
     float sum = 0.f, db = 0.f;
+    auto panel = [&](int k0, int kn) {
+        SmallLoads<float> la;
+        SmallLoads<TW> lb;
+        la.template send<false>(t.M - mb, kn, [&](int r, int k) { return t.D[(int64_t)(k0 + k) * t.M + mb + r]; });
+        lb.template send<false>(t.N - nb, kn, [&](int r, int k) { return t.in[(int64_t)(k0 + k) * t.N + nb + r]; });
+        __syncthreads();
+        la.template keep<false>(s.a, t.M - mb, kn, [](float v, int, int) { return v; });
+        lb.template keep<false>(s.b, t.N - nb, kn, [](TW v, int, int) { return to_f(v); });
+        __syncthreads();
+        if (biases) {
+            int k = 0;
+            for (; k + 16 <= kn; k += 16) {
+                float v[16];
+#pragma unroll
+                for (int u = 0; u < 16; ++u) v[u] = s.a[threadIdx.x][k + u];
+#pragma unroll
+                for (int u = 0; u < 16; ++u) db += v[u];
+            }
+            for (; k < kn; ++k) db += s.a[threadIdx.x][k];
+        }
+    };
+    // One panel for the whole batch where its chunks begin at multiples of 16.
+    const bool whole = t.K <= SK && t.chunk % 16 == 0;
+    if (whole) panel(0, t.K);
     for (int z = 0; z < t.splits; ++z) {
         const int k1 = min(t.K, (z + 1) * t.chunk);
         float acc = 0.f;
-        for (int k0 = z * t.chunk; k0 < k1; k0 += SK) {
-            const int kn = min(SK, k1 - k0);
-            __syncthreads();
-            small_panel<false>(s.a, kn, [&](int r, int k) { return mb + r < t.M ? t.D[(int64_t)(k0 + k) * t.M + mb + r] : 0.f; });
-            small_panel<false>(s.b, kn, [&](int r, int k) {
-                return nb + r < t.N ? to_f(t.in[(int64_t)(k0 + k) * t.N + nb + r]) : 0.f;
-            });
-            __syncthreads();
-            acc = small_dot(s, m, n, kn, acc);
-            if (biases)
-                for (int k = 0; k < kn; ++k) db += s.a[threadIdx.x][k];
+        if (whole) {
+            acc = small_dot(s, m, n, z * t.chunk, k1, acc);
+        } else {
+            for (int k0 = z * t.chunk; k0 < k1; k0 += SK) {
+                const int kn = min(SK, k1 - k0);
+                panel(k0, kn);
+                acc = small_dot(s, m, n, 0, kn, acc);
+            }
         }
         sum = t.splits > 1 ? sum + acc : acc;
     }
-    auto take = [&](int64_t i, float g) {
-        if (f.adam.update) adam_step(f.adam, i, g);
-        else f.adam.g[i] = g;
-    };
-    if (mb + m < t.M && nb + n < t.N) take(t.at + (int64_t)(mb + m) * t.N + nb + n, sum);
-    if (biases && mb + (int)threadIdx.x < t.M) take(t.at + (int64_t)t.M * t.N + mb + threadIdx.x, db);
+    if (f.adam.update) {
+        if (mine) w.step(f.adam, iw, sum);
+        if (biases) wb.step(f.adam, ib, db);
+    } else {
+        if (mine) f.adam.g[iw] = sum;
+        if (biases) f.adam.g[ib] = db;
+    }
 }
 
 static int grid_for(int64_t count) { return (int)std::min<int64_t>(2048, std::max<int64_t>(1, (count + 255) / 256)); }
@@ -492,10 +557,10 @@ static int batch_splits(int Bn) { return std::max(1, std::min(16, Bn / 128)); }
 
 // The small-network kernels serve networks and batches no layer of which fills
 // the chip with 64 x 64 tiles: up to 256 of them per product.  24-256-256-64 in
-// BF16, a step with batches of 32, 256 and 4096: 58, 82 and 721 us against 207,
-// 410 and 2831, a forward pass 29, 25 and 95 against 90, 95 and 104; hidden
-// layers of 1024 with 1024 (256 tiles): 879 and 264 us against 1198 and 327; with
-// 2048 (512 tiles) 1697 and 497 against 1823 and 389.
+// BF16, a step with batches of 32, 256 and 4096: 35, 45 and 343 us against 207,
+// 410 and 2831, a forward pass 19, 18 and 85 against 90, 95 and 104; hidden
+// layers of 1024 with 1024 (256 tiles): 674 and 223 us against 1198 and 327; with
+// 2048 (512 tiles) about equal.
 static bool small_net(const mlp_net* n, int Bn)
 {
     auto tiles = [](int a, int b) { return (int64_t)((a + GT - 1) / GT) * ((b + GT - 1) / GT); };
