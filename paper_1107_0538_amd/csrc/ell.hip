@@ -136,10 +136,11 @@ EllKernels ell_kernels(const cg_ell* e, bool mat32)
 
 void launch_ell_spmv(const cg_ell* e, hipStream_t st, const double* x, double* y)
 {
-    const int G = (e->map.S + 7) / 8 * 8;
-    if (e->map.width <= 14) k_ell_spmv<14><<<G, kEllRows, 0, st>>>(e->map, e->keep_spmv, G, x, y);
-    else k_ell_spmv<28><<<G, kEllRows, 0, st>>>(e->map, e->keep_spmv, G, x, y);
-    JPCG_HIP(hipGetLastError());
+    int G = (e->map.S + 7) / 8 * 8, keep = e->keep_spmv;
+    EllMap m = e->map;
+    void* args[] = {&m, &keep, &G, &x, &y};
+    const void* fn = m.width <= 14 ? (const void*)k_ell_spmv<14> : (const void*)k_ell_spmv<28>;
+    JPCG_HIP(hipLaunchKernel(fn, dim3(G), dim3(kEllRows), args, 0, st));
 }
 
 }  // namespace jpcg

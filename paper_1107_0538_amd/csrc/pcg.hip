@@ -529,9 +529,14 @@ static cg_spmv_plan* make_spmv_plan(cg_ctx* c, int npl, int bs, int G)
     }
 }
 
+// Rows from which on the product runs over slices: a lane walks a whole row there,
+// and below this a wave per SIMD is not enough to hide it (16^3 to 32^3 6.0 us a
+// call against 5.5 by tiles, 36^3 6.4 against 7.0, 46^3 7.1 against 8.1).
+constexpr int kEllSpmvRows = 40000;
+
 static void launch_spmv(cg_ctx* c, const double* x, double* y)
 {
-    if (c->ell) {
+    if (c->ell && c->n >= kEllSpmvRows) {
         launch_ell_spmv(c->ell, c->stream, x, y);
         return;
     }
@@ -1188,8 +1193,9 @@ int cg_create(const cg_csr* A, const cg_opts* opts, void* hip_stream, cg_ctx** o
         // for the kernels it shapes.
         if (!c->opts.nnz_per_lane && !c->opts.block_size && !c->opts.blocks_per_cu && !c->opts.chunk)
             c->resident = make_resident(c);
-        // Slices, likewise; col_bits = 32 asks for the column array.
-        if (!c->opts.nnz_per_lane && !c->opts.block_size && !c->opts.blocks_per_cu && !c->opts.col_bits)
+        // Slices, likewise; col_bits = 32 asks for the column array.  Nothing
+        // runs over them where the system is solved on chip and is small.
+        if ((!c->resident || c->n >= kEllSpmvRows) && !c->opts.nnz_per_lane && !c->opts.block_size && !c->opts.blocks_per_cu && !c->opts.col_bits)
             c->ell = make_ell(c);
         // The mixed form needs the standard FP64 graphs (outer residual) and
         // FP32 standard graphs (inner solve) with the same tile shape.

@@ -165,8 +165,9 @@ __global__ __launch_bounds__(kQ1X) void k_q1_apply(int n, Q1Coef q, const double
 //
 // What bounds it: the double-precision adds and multiplies (about 110 a node).
 // With a node per lane and 35 loads for each, the vector-memory address path
-// took 34.4 us at 128^3 (50 MB); 17.7 as it is, 6 loads of 16 bytes a plane for
-// two nodes.
+// took 34.4 us at 128^3 (50 MB); 15.7 as it is, 6 loads of 16 bytes a plane for
+// two nodes (16.9 with the mass terms formed in each plane and the ends of longer
+// lines in every case).
 struct Q1March {
     int n, lanes;   // lanes of a line
     int chunks;     // of 2 * lanes nodes per line
@@ -210,14 +211,16 @@ struct Q1Layer {
     double s[3][5];
 };
 
+// CHUNKS: a line goes on past the lanes.
+template <bool CHUNKS>
 __global__ __launch_bounds__(kQ1BS, 3) void k_q1_march(Q1March g, Q1Coef q, const double* __restrict__ sigma,
                                                     const double* __restrict__ xv, double* __restrict__ yv)
 {
 #pragma clang fp contract(off)
     const int n = g.n, m = n - 1;
     int L = xcd_logical_block((int)blockIdx.x, g.G);
-    const int chunk = L % g.chunks;
-    L /= g.chunks;
+    const int chunk = CHUNKS ? L % g.chunks : 0;
+    if (CHUNKS) L /= g.chunks;
     const int yg = L % g.ygroups, z0 = (L / g.ygroups) * g.planes, z1 = min(z0 + g.planes, n);
     const int l = threadIdx.x % g.lanes, y = yg * g.lines + (int)threadIdx.x / g.lanes;
     const int x = 2 * (chunk * g.lanes + l);
@@ -228,7 +231,7 @@ __global__ __launch_bounds__(kQ1BS, 3) void k_q1_march(Q1March g, Q1Coef q, cons
     // Loads are sent a plane ahead, from addresses inside the arrays whatever the
     // lane, and looked at when the plane's turn comes.
     const int xa = min(x, n - 2), ea = min(x, m - 2), side = first ? max(x - 1, 0) : min(x + 2, n - 1);
-    const bool beside = g.chunks > 1 && (first ? x > 0 : last && x + 2 < n);
+    const bool beside = CHUNKS && (first ? x > 0 : last && x + 2 < n);
     struct Plane {
         Q1Pair v[3];  // lines y - 1, y, y + 1
         double e[3];  // an end lane's neighbour beyond
@@ -240,7 +243,7 @@ __global__ __launch_bounds__(kQ1BS, 3) void k_q1_march(Q1March g, Q1Coef q, cons
             const unsigned line = (unsigned)min(max(y + b - 1, 0), n - 1) * (unsigned)n;
             p.v[b] = *(const Q1Pair*)(plane + line + (unsigned)xa);
             p.e[b] = 0.0;
-            if (g.chunks > 1) p.e[b] = plane[line + (unsigned)side];
+            if (CHUNKS) p.e[b] = plane[line + (unsigned)side];
         }
     };
     struct Elements {
@@ -254,7 +257,7 @@ __global__ __launch_bounds__(kQ1BS, 3) void k_q1_march(Q1March g, Q1Coef q, cons
             const unsigned line = (unsigned)min(max(y + b - 1, 0), m - 1) * (unsigned)m;
             t.v[b] = *(const Q1Pair*)(plane + line + (unsigned)ea);
             t.e[b] = 0.0;
-            if (g.chunks > 1) t.e[b] = plane[line + (unsigned)min(max(x - 1, 0), m - 1)];
+            if (CHUNKS) t.e[b] = plane[line + (unsigned)min(max(x - 1, 0), m - 1)];
         }
     };
     auto layer_of = [&](const Elements& t, int z, Q1Layer& s) {
@@ -275,21 +278,33 @@ __global__ __launch_bounds__(kQ1BS, 3) void k_q1_march(Q1March g, Q1Coef q, cons
     // one element, the others as many as there are around the node.
     const double cy = (double)((y > 0) + (y < m));
     const double cx[2] = {(double)((x > 0) + (x < m)), (double)((x + 1 > 0) + (x + 1 < m))};
+    // chm * count per plane offset and line offset: for offsets -1 and 1 in x, and
+    // for 0 at either node.
+    struct Mass {
+        double edge[2], centre[2][2];
+    };
+    auto mass_of = [&](int dz, double cz, Mass& t) {
+#pragma unroll
+        for (int dy = 0; dy < 2; ++dy) {
+            const double cyz = dy == 0 ? cz * cy : cz;
+            t.edge[dy] = q.chm[dz + dy + 1] * cyz;
+#pragma unroll
+            for (int u = 0; u < 2; ++u) t.centre[dy][u] = q.chm[dz + dy] * (cyz * cx[u]);
+        }
+    };
+    Mass beside_plane, own_plane;
+    mass_of(1, 1.0, beside_plane);
     // The nine terms of one plane for the lane's nodes: lines iy, offsets ix.
     constexpr int kSlot[3] = {0, 2, 1};
-    auto add = [&](const double (&v)[3][4], const Q1Layer& s, int dz, double cz, double (&acc)[2]) {
+    auto add = [&](const double (&v)[3][4], const Q1Layer& s, int dz, const Mass& t, double (&acc)[2]) {
 #pragma unroll
         for (int iy = 0; iy < 3; ++iy) {
             const int dy = iy != 1, by = kSlot[iy];
-            const double cyz = iy == 1 ? cz * cy : cz;
-            // chm * count for offsets -1 and 1, and for offset 0 at either node.
-            const double edge = q.chm[dz + dy + 1] * cyz;
 #pragma unroll
             for (int u = 0; u < 2; ++u) {
-                const double centre = q.chm[dz + dy] * (cyz * cx[u]);
-                const double a0 = fma(q.hk[dz + dy + 1], s.s[by][u], edge);
-                const double a1 = fma(q.hk[dz + dy], s.s[by][3 + u], centre);
-                const double a2 = fma(q.hk[dz + dy + 1], s.s[by][1 + u], edge);
+                const double a0 = fma(q.hk[dz + dy + 1], s.s[by][u], t.edge[dy]);
+                const double a1 = fma(q.hk[dz + dy], s.s[by][3 + u], t.centre[dy][u]);
+                const double a2 = fma(q.hk[dz + dy + 1], s.s[by][1 + u], t.edge[dy]);
                 acc[u] = acc[u] + a0 * v[iy][u];
                 acc[u] = acc[u] + a1 * v[iy][u + 1];
                 acc[u] = acc[u] + a2 * v[iy][u + 2];
@@ -328,7 +343,7 @@ __global__ __launch_bounds__(kQ1BS, 3) void k_q1_march(Q1March g, Q1Coef q, cons
             high[u] = 0.0;
         }
         if (p > z0) {
-            add(v, below, 1, 1.0, low);
+            add(v, below, 1, beside_plane, low);
             double* out = yv + ((size_t)(p - 1) * n + y) * n + x;
             if (in_y && x < n) out[0] = low[0];
             if (in_y && x + 1 < n) out[1] = low[1];
@@ -339,9 +354,10 @@ __global__ __launch_bounds__(kQ1BS, 3) void k_q1_march(Q1March g, Q1Coef q, cons
             for (int b = 0; b < 3; ++b)
 #pragma unroll
                 for (int k = 0; k < 5; ++k) both.s[b][k] = below.s[b][k] + above.s[b][k];
-            add(v, both, 0, (double)((p > 0) + (p < m)), mid);
+            mass_of(0, (double)((p > 0) + (p < m)), own_plane);
+            add(v, both, 0, own_plane, mid);
         }
-        if (p + 1 < z1) add(v, above, 1, 1.0, high);
+        if (p + 1 < z1) add(v, above, 1, beside_plane, high);
     }
 }
 
@@ -419,7 +435,8 @@ int q1_apply(int32_t n_edge, double c, const double* sigma, const double* x, dou
         // infinite c.
         if (n_edge >= kQ1MarchMin && std::isfinite(c)) {
             const Q1March g = q1_march(n_edge);
-            k_q1_march<<<g.G, kQ1BS, 0, (hipStream_t)stream>>>(g, q1_coef(n_edge, c), sigma, x, y);
+            const auto march = g.chunks > 1 ? k_q1_march<true> : k_q1_march<false>;
+            march<<<g.G, kQ1BS, 0, (hipStream_t)stream>>>(g, q1_coef(n_edge, c), sigma, x, y);
         } else {
             const dim3 grid((n_edge + kQ1X - 1) / kQ1X, n_edge, n_edge);
             k_q1_apply<<<grid, kQ1X, 0, (hipStream_t)stream>>>(n_edge, q1_coef(n_edge, c), sigma, x, y);

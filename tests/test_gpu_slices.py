@@ -40,6 +40,20 @@ def test_slices_product_bitwise(cuda, n, offsets):
     assert np.array_equal(s.spmv(_t(x, cuda)).cpu().numpy(), oracle.spmv(a, x))
 
 
+@pytest.mark.parametrize("n,offsets", [
+    (39999, (1, 5)), (40000, (1, 5)), (40001, ()), (40033, tuple(range(1, 7))), (40063, tuple(range(1, 8))),  # tiles, then slices
+    (40064, tuple(range(1, 14))), (40065, tuple(range(1, 15))), (41000, tuple(range(1, 32))), (41000, tuple(range(1, 33))),
+])
+def test_slices_product_from_its_smallest_size(cuda, n, offsets):
+    from paper_1107_0538_amd import Solver
+
+    a = banded(n, offsets, seed=n)
+    x = np.random.default_rng(n).uniform(-1, 1, n)
+    x[[5, n // 2, n - 1]] = [np.inf, -np.inf, np.nan]
+    y = Solver(a).spmv(_t(x, cuda)).cpu().numpy()
+    assert np.array_equal(y, oracle.spmv(a, x), equal_nan=True)
+
+
 def test_slices_product_rows_without_entries_and_infinities(cuda):
     # Empty rows sum to zero, and an infinity reaches only the rows that refer to it.
     from paper_1107_0538_amd import Solver
