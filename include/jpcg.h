@@ -157,10 +157,10 @@ int cg_create(const cg_csr *A, const cg_opts *opts, void *hip_stream, cg_ctx **o
  * at most 262144 rows of at most 28 nonzeros, created without a launch shape in
  * its options, is solved by one kernel that holds the matrix in registers (such
  * solves on one device, and batched ones, wait for each other); otherwise
- * iterations run as kernels launched in hipGraph chunks, in the standard form
- * over a second copy of the matrix in slices of 64 rows where its rows are of
- * about equal length (at most 64), no launch shape or column width was given
- * and there is memory for it.  The call synchronises
+ * iterations run as kernels launched in hipGraph chunks, over a second copy of
+ * the matrix in slices of 64 rows where its rows are of about equal length (at
+ * most 64), no launch shape or column width was given and there is memory for
+ * it.  The call synchronises
  * the context's stream.
  * info may be NULL.  Returns the status (>= 0) or an API error (< 0).
  */

@@ -5,6 +5,7 @@
 
 #include "context.hpp"
 #include "ell_kernels.hpp"
+#include "ell_sr.hpp"
 
 namespace jpcg {
 
@@ -126,6 +127,12 @@ static EllKernels ell_kernels_of(bool mat32)
     k.flushed = (const void*)k_ell_flushed;
     k.check = (const void*)k_ell_check<U>;
     k.decide = (const void*)k_ell_decide;
+    k.sr_residual = (const void*)k_ell_sr_residual<U>;
+    k.sr_begin = (const void*)k_ell_sr_begin;
+    k.sr_start = (const void*)k_ell_sr_start<U>;
+    k.sr_update = (const void*)k_ell_sr_update;
+    k.sr_product = (const void*)k_ell_sr_product<U>;
+    k.sr_decide = (const void*)k_ell_sr_decide;
     return k;
 }
 

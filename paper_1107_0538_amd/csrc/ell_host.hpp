@@ -3,6 +3,7 @@
 
 #include "context.hpp"
 #include "ell.hpp"
+#include "sr_kernels.hpp"
 #include "std_kernels.hpp"
 
 struct cg_ell {
@@ -43,11 +44,28 @@ struct EllArgs {
     double drop2;
 };
 
+// The single-reduction form (ell_sr.hpp).
+struct EllSrArgs {
+    EllMap m;
+    int keep;
+    const double* __restrict__ dinv;
+    const double* b;
+    double* x;
+    double *r, *p, *s, *w, *u;
+    int G, Gu, R;        // as above
+    double* part[2];     // [Gu][4], by parity
+    double* part_w;      // [G][2]
+    double* part_chk;    // [G][2]
+    SrState* st;
+    double* hist;
+};
+
 constexpr int kEllBS = 256;
 constexpr int kEllWaves = kEllBS / kWave;
 
 struct EllKernels {
     const void *setup, *begin, *direction, *product, *update, *flush, *flushed, *check, *decide;
+    const void *sr_residual, *sr_begin, *sr_start, *sr_update, *sr_product, *sr_decide;
 };
 EllKernels ell_kernels(const cg_ell* e, bool mat32);
 

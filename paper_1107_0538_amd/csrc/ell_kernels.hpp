@@ -23,10 +23,10 @@ namespace jpcg {
 // f(s) for the workgroup's slices: a wave takes every kEllWaves-th of the
 // workgroup's run; blocks of one XCD own neighbouring runs.
 template <typename F>
-__device__ __forceinline__ void ell_slices(const EllArgs& a, F f)
+__device__ __forceinline__ void ell_slices(const EllMap& m, int G, F f)
 {
-    const int L = logical_of(a.G), per = (a.m.S + a.G - 1) / a.G;
-    const int s1 = min((L + 1) * per, a.m.S);
+    const int L = logical_of(G), per = (m.S + G - 1) / G;
+    const int s1 = min((L + 1) * per, m.S);
     for (int s = L * per + __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave); s < s1; s += kEllWaves) f(s);
 }
 
@@ -43,7 +43,7 @@ template <int U>
 __device__ __forceinline__ void ell_residual(const EllArgs& a, double* r_out, double& rr, double& rz, double& bb)
 {
     const double* __restrict__ x = a.x;
-    ell_slices(a, [&](int s) {
+    ell_slices(a.m, a.G, [&](int s) {
         const int lane = threadIdx.x & (kWave - 1), i = s * kEllRows + lane;
         const double ax = ell_row<false, U>(a.m, a.m.val, a.keep, s, lane, x, 0.0);
         if (i < a.m.n) {
@@ -146,7 +146,7 @@ __global__ __launch_bounds__(kEllBS) void k_ell_product(EllArgs a)
     if (a.st->cg.stop != RUNNING) return;
     const double* __restrict__ p = a.p;
     double v[1] = {0.0};
-    ell_slices(a, [&](int s) {
+    ell_slices(a.m, a.G, [&](int s) {
         const int lane = threadIdx.x & (kWave - 1), i = s * kEllRows + lane;
         const double pi = p[min(i, a.m.n - 1)];
         double y;

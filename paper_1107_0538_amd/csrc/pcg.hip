@@ -259,6 +259,7 @@ struct cg_graphs {
     bool ell = false;
     jpcg::EllKernels ekern{};
     jpcg::EllArgs eargs{};
+    jpcg::EllSrArgs esargs{};
 };
 
 namespace jpcg {
@@ -437,6 +438,55 @@ static cg_graphs* make_ell_graphs(cg_ctx* c, int chunk, bool mat32, double drop)
     }
 }
 
+// The single-reduction form over the context's slices.  Every workgroup of the
+// update reduces both kernels' partials, so the grids are half of the above.
+static cg_graphs* make_ell_sr_graphs(cg_ctx* c, int chunk)
+{
+    cg_graphs* g = new cg_graphs();
+    try {
+        g->ell = true;
+        g->form = CG_FORM_SINGLE_REDUCTION;
+        g->chunk = chunk;
+        g->ekern = ell_kernels(c->ell, false);
+        g->st_bytes = sizeof(SrState);
+        EllSrArgs& a = g->esargs;
+        a.m = c->ell->map;
+        a.keep = c->ell->keep;
+        a.G = std::min(kEllMaxGrid / 2, ((a.m.S + kEllWaves - 1) / kEllWaves + 7) / 8 * 8);
+        a.Gu = std::min(kEllUpdateGrid / 2, ((c->n + kEllBS - 1) / kEllBS + 7) / 8 * 8);
+        a.R = (c->n + a.Gu - 1) / a.Gu;
+        JPCG_HIP(hipMalloc(&g->part, sizeof(double) * (4 * (size_t)a.G + 8 * (size_t)a.Gu)));
+        JPCG_HIP(hipMalloc(&g->st, g->st_bytes));
+        JPCG_HIP(hipHostMalloc(&g->hst, g->st_bytes * 4, hipHostMallocDefault));
+        JPCG_HIP(hipMalloc(&g->cb, sizeof(double) * c->n));
+        JPCG_HIP(hipMalloc(&g->cx, sizeof(double) * c->n));
+        for (auto& e : g->evs) JPCG_HIP(hipEventCreateWithFlags(&e, hipEventDisableTiming));
+        JPCG_HIP(hipMemsetAsync(g->st, 0, g->st_bytes, c->stream));
+        double* const* w = c->work;
+        a.dinv = c->dinv;
+        a.b = (double*)g->cb;
+        a.x = (double*)g->cx;
+        a.r = w[0];
+        a.p = w[1];
+        a.s = w[2];
+        a.w = w[3];
+        a.u = w[4];
+        a.part_w = g->part;
+        a.part_chk = g->part + 2 * (size_t)a.G;
+        a.part[0] = g->part + 4 * (size_t)a.G;
+        a.part[1] = a.part[0] + 4 * (size_t)a.Gu;
+        a.st = (SrState*)g->st;
+        a.hist = nullptr;
+        JPCG_HIP(hipStreamSynchronize(c->stream));
+        return g;
+    } catch (const HipError& err) {
+        destroy_graphs(g);
+        if (err.code != hipErrorOutOfMemory) throw;
+        (void)hipGetLastError();
+        return nullptr;  // the tile kernels' graphs are there
+    }
+}
+
 // The chunk graphs, captured when a solve first runs through them.
 static void capture_graphs(cg_graphs* g)
 {
@@ -449,7 +499,11 @@ static void capture_graphs(cg_graphs* g)
         JPCG_HIP(hipStreamBeginCapture(cap, hipStreamCaptureModeThreadLocal));
         for (int it = 0; it < g->chunk; ++it) {
             int P = (par + it) & 1;
-            if (g->form == CG_FORM_SINGLE_REDUCTION) {
+            if (g->ell && g->form == CG_FORM_SINGLE_REDUCTION) {
+                void* args[] = {&g->esargs, &P};
+                launch(g->ekern.sr_update, g->esargs.Gu, kEllBS, cap, args);
+                launch(g->ekern.sr_product, g->esargs.G, kEllBS, cap, args);
+            } else if (g->form == CG_FORM_SINGLE_REDUCTION) {
                 void* args[] = {&g->sargs, &P};
                 launch(g->kern.sr_iter, g->G, g->bs, cap, args);
             } else if (g->ell) {
@@ -755,6 +809,71 @@ static SolveResult run_single(cg_ctx* c, cg_graphs* g, double tol, int maxit, do
     return r;
 }
 
+// Single-reduction form over slices, on the graphs' own b and x.
+static SolveResult run_ell_single(cg_ctx* c, cg_graphs* g, double tol, int maxit, double* hist)
+{
+    hipStream_t s = c->stream;
+    EllSrArgs a = g->esargs;
+    a.hist = hist;
+    auto product = [&] {
+        void* args[] = {&a};
+        launch(g->ekern.sr_product, a.G, kEllBS, s, args);
+    };
+    // ||b - A x||^2; replace: into r; setup: with p and s cleared.
+    auto residual = [&](int replace, int setup) {
+        void* args[] = {&a, &replace, &setup};
+        launch(g->ekern.sr_residual, a.G, kEllBS, s, args);
+    };
+    auto start = [&](int P, int restart) {
+        void* args[] = {&a, &P, &restart};
+        launch(g->ekern.sr_start, a.Gu, kEllBS, s, args);
+        product();
+    };
+    auto decide = [&](int report) {
+        void* args[] = {&a, &report};
+        launch(g->ekern.sr_decide, 1, kEllBS, s, args);
+    };
+    residual(1, 1);
+    {
+        void* args[] = {&a, &tol, &maxit};
+        launch(g->ekern.sr_begin, 1, kEllBS, s, args);
+    }
+    start(0, 0);
+    auto iteration = [&](int P) {
+        void* args[] = {&a, &P};
+        launch(g->ekern.sr_update, a.Gu, kEllBS, s, args);
+        product();
+    };
+    auto stopped = [&]() -> int {
+        SrState st = read_state<SrState>(c, g);
+        if (st.stop == STOP_ZERO_RHS) JPCG_HIP(hipMemsetAsync(g->cx, 0, sizeof(double) * c->n, s));
+        if (st.stop == STOP_CHECK) {
+            residual(1, 0);
+            decide(0);
+            st = read_state<SrState>(c, g);
+            if (st.stop == RUNNING) {  // replaced residual: s = A p, w = A M^-1 r, then resume
+                start(st.k_done & 1, 1);
+                return st.k_done + 1;
+            }
+        }
+        if (st.stop == STOP_MAXIT || st.stop == STOP_BREAKDOWN) {
+            residual(0, 0);
+            decide(1);
+        }
+        return -1;
+    };
+    chunk_loop(c, g, 1, maxit, hist == nullptr, iteration, stopped);
+    const SrState st = read_state<SrState>(c, g);
+    SolveResult r;
+    r.stop = st.stop;
+    r.iters = st.k_done;
+    r.replacements = st.replacements;
+    r.nb = st.nb;
+    r.rr = st.rr;
+    r.rr_true = st.rr_true;
+    return r;
+}
+
 // One FP64 solve through the graph path.  b, x are caller device pointers.
 static SolveResult run_solve(cg_ctx* c, cg_graphs* g, const double* b, double* x, double tol, int maxit,
                              double* hist)
@@ -763,8 +882,9 @@ static SolveResult run_solve(cg_ctx* c, cg_graphs* g, const double* b, double* x
     const size_t vb = sizeof(double) * c->n;
     JPCG_HIP(hipMemcpyAsync(g->cb, b, vb, hipMemcpyDeviceToDevice, s));
     JPCG_HIP(hipMemcpyAsync(g->cx, x, vb, hipMemcpyDeviceToDevice, s));
-    const SolveResult r = g->ell ? run_ell(c, g, tol, maxit, hist)
-                          : g->form == CG_FORM_SINGLE_REDUCTION
+    const bool single = g->form == CG_FORM_SINGLE_REDUCTION;
+    const SolveResult r = g->ell ? (single ? run_ell_single : run_ell)(c, g, tol, maxit, hist)
+                          : single
                               ? run_single(c, g, tol, maxit, hist)
                               : run_standard<double>(c, g, g->args, tol, maxit, hist, true);
     JPCG_HIP(hipMemcpyAsync(x, g->cx, vb, hipMemcpyDeviceToDevice, s));
@@ -1245,8 +1365,11 @@ int cg_solve(cg_ctx* c, const double* b, double* x, double tol, int32_t maxit, c
         JPCG_HIP(hipEventRecord(c->ev0, c->stream));
         const SolveResult st = run_any(c, c->form == CG_FORM_SINGLE_REDUCTION ? RS_SINGLE : RS_STANDARD, b, x, tol,
                                        maxit, 0.0, hist, [&] {
-                                           if (!c->ell || c->form != CG_FORM_STANDARD) return c->graphs;
-                                           if (!c->graphs_ell) c->graphs_ell = make_ell_graphs(c, c->chunk, false, 0.0);
+                                           if (!c->ell) return c->graphs;
+                                           if (!c->graphs_ell)
+                                               c->graphs_ell = c->form == CG_FORM_STANDARD
+                                                                   ? make_ell_graphs(c, c->chunk, false, 0.0)
+                                                                   : make_ell_sr_graphs(c, c->chunk);
                                            return c->graphs_ell ? c->graphs_ell : c->graphs;
                                        });
         JPCG_HIP(hipEventRecord(c->ev1, c->stream));

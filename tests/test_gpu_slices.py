@@ -117,3 +117,31 @@ def test_slices_solve_breakdown(cuda):
     xo, io = oracle.pcg(a, b, precond="none")
     assert info["status"] == io["status"] == 2 and info["iters"] == io["iters"]
     assert np.linalg.norm(x.cpu().numpy() - xo) <= 1e-9 * max(np.linalg.norm(xo), 1e-300)
+
+
+@pytest.mark.parametrize("history", [False, True])
+@pytest.mark.parametrize("n,offsets", [(262145, (1, 600)), (300001, (1, 30, 900)), (6000, tuple(range(1, 16)))])
+def test_slices_single_reduction(cuda, n, offsets, history):
+    # The single-reduction form over slices: converged, stopped by the limit, by b = 0 and at once by
+    # x0, and resumed after replacements (the last one asks for more than is attainable).
+    from paper_1107_0538_amd import Solver
+
+    a = banded(n, offsets, seed=n)
+    b = np.random.default_rng(n + 1).uniform(-1, 1, n)
+    s = Solver(a, form="single", history=history)
+    x, info = s.solve(_t(b, cuda))
+    check(a, b, x.cpu().numpy(), info, "single")
+    if history:
+        h = s.history()
+        assert h.size == info["iters"] + 1 and h[-1] <= 1e-10 < h[-2]
+    x3, i3 = s.solve(_t(b, cuda), maxit=3)
+    xo, io = oracle.pcg(a, b, maxit=3)
+    assert i3["status"] == io["status"] == 1 and i3["iters"] == 3
+    assert np.linalg.norm(x3.cpu().numpy() - xo) <= 1e-9 * np.linalg.norm(xo)
+    x0, i0 = s.solve(_t(np.zeros(n), cuda), x0=x)
+    assert i0["status"] == 0 and i0["iters"] == 0 and not x0.cpu().numpy().any()
+    again, ia = s.solve(_t(b, cuda), x0=x, tol=1e-9)
+    assert ia["status"] == 0 and ia["iters"] == 0 and (again == x).all()
+    _, ir = s.solve(_t(b, cuda), tol=1e-17, maxit=2 * info["iters"] + 40)
+    assert ir["status"] in (1, 2) and ir["replacements"] >= (0 if ir["status"] == 2 else 1)
+    assert ir["relres_true"] <= 1e-12
