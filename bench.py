@@ -52,36 +52,9 @@ def solve_bytes(n, nnz, iters, checks, form="standard", vb=8, ib=4):
     return setup + iters * iter_bytes(n, nnz, form, vb, ib) + checks * (matrix + 3 * vb * n)
 
 
-# HBM bytes per iteration from rocprofv3 FETCH_SIZE / WRITE_SIZE (scaled by a
-# 512 MiB copy: fetch x2, write x1) for the 51^3 system, keyed by form and
-# launch shape (nonzeros per lane, block size, column index bits).  Each entry
-# records the profile it came from and a hash of the kernel sources it was
-# measured on; once those sources change the figure no longer applies and the
-# roofline reports traffic as null.
-# HBM bytes per iteration from rocprofv3 FETCH_SIZE and WRITE_SIZE passes (KiB per dispatch,
-# median; FETCH_SIZE x2 and WRITE_SIZE x1, the factors a streaming triad of known size reads
-# under the same counters), valid while the kernels' sources hash to `sources_sha`.
-MEASURED_TRAFFIC = {
-    ("standard", 132651, 3442951, 16, 512, 16): {  # k_direction + k_update
-        "bytes": ((18563.4 + 3146.4) * 2 + 3159.2 + 4149.4) * 1024, "sources_sha": "dde6e28c68226766"},
-    ("single", 132651, 3442951, 16, 512, 16): {  # k_sr_iter
-        "bytes": (21074.1 * 2 + 6298.4) * 1024, "sources_sha": "ecffa30fce08bee6"},
-}
-TRAFFIC_SOURCES = {
-    "standard": ("std_kernels.hpp", "tiles.hpp", "common.hpp"),
-    "single": ("sr_kernels.hpp", "tiles.hpp", "common.hpp"),
-}
-TRAFFIC_PROFILE = "profiles/pcg_iteration_kernels_51cube_hbm_counters.txt"
-
-
-def kernel_sources_sha(form):
-    import hashlib
-
-    h = hashlib.sha256()
-    for f in TRAFFIC_SOURCES[form]:
-        with open(os.path.join(ROOT, "paper_1107_0538_amd", "csrc", f), "rb") as fh:
-            h.update(fh.read())
-    return h.hexdigest()[:16]
+# Systems up to this size are solved in one kernel that reads the matrix once
+# (cg_solve's rule on sizes; the workload's rows have 27 entries).
+ON_CHIP_ROWS = 262144
 
 
 def hbm_probe(dev, stream, mib=512, reps=20):
@@ -119,32 +92,36 @@ def hbm_probe(dev, stream, mib=512, reps=20):
 
 
 def roofline(form, n, nnz, run):
-    """The iteration's kernels against the HBM roofline.
+    """The solve's kernels against the HBM roofline.
 
-    One CG iteration is the unit: k_direction + k_update (standard form) or
-    k_sr_iter (single-reduction form), launched in hipGraph chunks; its
-    duration is the event-timed device time of the solve over the iteration
-    count (setup and the final check are two products in 410 iterations).
+    A system that is solved on chip is one launch, which reads the matrix once
+    and is bound by the latency of its iterations' exchanges: the unit is the
+    whole solve, `achieved` what it has to move over its event-timed device
+    time, and `csr_equivalent_gbs` what a solver that streams the CSR bytes in
+    every iteration would have to reach.  Larger systems stream the matrix over
+    slices of 64 rows, the standard form in three kernels an iteration and the
+    single-reduction form in two, launched in hipGraph chunks: the unit is one
+    iteration, its duration the device time over the iteration count (setup
+    and the final check are two products in 410 iterations).
     """
     per_iter_s = run["device_s"] / max(run["iters"], 1)
     ib = iter_bytes(n, nnz, form)
-    launch = run["launch"]
-    entry = MEASURED_TRAFFIC.get((form, n, nnz, launch["nnz_per_lane"], launch["block_size"], launch["col_bits"]))
-    sha = kernel_sources_sha(form)
-    traffic = entry["bytes"] if entry and entry["sources_sha"] == sha else None
-    # The stored format's compulsory bytes: 16-bit column offsets save 2 per
-    # nonzero against the CSR count that `achieved` uses; the standard form's
-    # whole {z, p} pair stores and loads add 24 per row, the single-reduction
-    # form's whole {r, w, s, d} quad stores 8.
-    fb = ib - (2 * nnz if launch.get("col_bits") == 16 else 0) + (24 * n if form == "standard" else 8 * n)
+    if n <= ON_CHIP_ROWS:
+        kernel, bound = "k_rs_solve (the whole solve)", "latency"
+        nbytes, seconds = 12 * nnz + 4 * (n + 1) + 32 * n, run["device_s"]  # matrix, b, x0, dinv read, x written
+        extra = {"csr_equivalent_gbs": ib / per_iter_s / 1e9, "iteration_s": per_iter_s}
+    else:
+        kernel = "k_ell_sr_update + k_ell_sr_product" if form == "single" else \
+            "k_ell_direction + k_ell_product + k_ell_update"
+        kernel, bound, nbytes, seconds = kernel + " (one CG iteration)", "hbm", ib, per_iter_s
+        # The stored format's bytes: 16-bit column offsets save 2 per nonzero, and
+        # the single-reduction form stores u and reads u, p and w again.
+        fb = ib - 2 * nnz + (24 * n if form == "single" else 0)
+        extra = {"format_bytes_per_launch": fb, "format_frac": fb / per_iter_s / 1e9 / HBM_PEAK_GBS}
     return {
-        "kernel": ("k_sr_iter" if form == "single" else "k_direction + k_update") + " (one CG iteration)",
-        "bound": "hbm", "achieved": ib / per_iter_s / 1e9, "peak": HBM_PEAK_GBS, "unit": "GB/s",
-        "frac": ib / per_iter_s / 1e9 / HBM_PEAK_GBS, "traffic": traffic,
-        "traffic_source": TRAFFIC_PROFILE if traffic is not None else "kernel changed since the counters were taken",
-        "kernel_sources_sha": sha,
-        "bytes_per_launch": ib, "launch_s": per_iter_s,
-        "format_bytes_per_launch": fb, "format_frac": fb / per_iter_s / 1e9 / HBM_PEAK_GBS,
+        "kernel": kernel, "bound": bound, "achieved": nbytes / seconds / 1e9, "peak": HBM_PEAK_GBS, "unit": "GB/s",
+        "frac": nbytes / seconds / 1e9 / HBM_PEAK_GBS, "traffic": None, "traffic_source": "not measured",
+        "bytes_per_launch": nbytes, "launch_s": seconds, **extra,
     }
 
 
@@ -243,11 +220,11 @@ def bench_hbm128(args, dev, stream):
     ib = iter_bytes(n, nnz, "standard")
     out = {
         "workload": f"q1hex 128^3 sigma+mass, N={n}, nnz={nnz}, FP64 Jacobi-PCG standard form, tol 1e-10",
-        "kernel": "k_direction + k_update (one CG iteration)", "bound": "hbm",
+        "kernel": "k_ell_direction + k_ell_product + k_ell_update (one CG iteration)", "bound": "hbm",
         "achieved": ib / per_iter / 1e9, "peak": HBM_PEAK_GBS, "unit": "GB/s",
         "frac": ib / per_iter / 1e9 / HBM_PEAK_GBS, "bytes_per_launch": ib, "launch_s": per_iter,
         "iters": it["iters"], "relres_true": it["relres_true"],
-        "spmv": {"kernel": f"k_spmv<{cfg['spmv_nnz_per_lane']}, {cfg['spmv_block_size']}>", "bytes": sb,
+        "spmv": {"kernel": "k_ell_spmv (slices of 64 rows)", "bytes": sb,
                  "warm_us": warm * 1e6, "warm_gbs": sb / warm / 1e9, "warm_frac": sb / warm / 1e9 / HBM_PEAK_GBS,
                  "cold_us": cold * 1e6, "cold_gbs": sb / cold / 1e9, "cold_frac": sb / cold / 1e9 / HBM_PEAK_GBS},
     }
@@ -737,15 +714,13 @@ def main():
             "us": spmv_us, "gbs": sb / spmv_us / 1e3, "frac_hbm_peak": sb / spmv_us / 1e3 / HBM_PEAK_GBS,
             "cold_us_median": cold_us, "cold_gbs": sb / cold_us / 1e3,
             "bytes": sb, "format_bytes": sb - (2 * nnz if cfg["col_bits"] == 16 else 0),
-            "kernel": f"k_spmv<{cfg['spmv_nnz_per_lane']}, {cfg['spmv_block_size']}>",
-            "nnz_per_lane": cfg["spmv_nnz_per_lane"], "block_size": cfg["spmv_block_size"], "grid": cfg["spmv_grid"],
+            "kernel": "k_ell_spmv (slices of 64 rows)",
         },
         "roofline": dict(roofline(best, n, nnz, r), achievable=probe["gbs"],
                          frac_of_achievable=roofline(best, n, nnz, r)["achieved"] / probe["gbs"],
-                         cache_resident=(f"the {args.n}^3 working set ({(iter_bytes(n, nnz, best)) / 1e6:.0f} MB) "
-                                         "fits the 256 MB last-level cache (MALL), so warm iterations are served "
-                                         "partly from it; roofline_128 is the HBM-bound figure")
-                         if iter_bytes(n, nnz, best) < 256e6 else None),
+                         cache_resident=(f"the {args.n}^3 system stays in the compute units' registers for the "
+                                         "whole solve; roofline_128 is the HBM-bound figure")
+                         if n <= ON_CHIP_ROWS else None),
         "hbm_probe": probe,
         "paper_context": {"opencl_1gpu_tesla_t10_s": 0.659, "matlab_core2duo_s": 3.17,
                           "note": "different (unavailable) matrix and hardware; context only"},
