@@ -9,8 +9,8 @@
 //   alpha = Gamma^-1 Psi                     k_bc_alpha (Cholesky over the live
 //                                            columns, inverse factor)
 //   X += P alpha                             k_bc_gemm<XUP>
-//   R -= Q alpha, ||r_j||^2                  k_bc_gemm<RUP> + k_bc_sum
-//   Q'Z, Z = M^-1 R                          k_bc_gram<1> + k_bc_sum
+//   R -= Q alpha, ||r_j||^2                  k_bc_gemm<RUP>
+//   Q'Z, Z = M^-1 R                          k_bc_gram<1> + k_bc_sum (the norms too)
 //   test, beta = -Gamma^-1 Q'Z               k_bc_beta
 //   W = Z + P beta, W'W                      k_bc_gemm<DIR> + k_bc_sum
 //   three CholeskyQR passes of W -> P        (k_bc_orth, k_bc_gemm<APPLY> with the
@@ -164,19 +164,28 @@ __global__ __launch_bounds__(kGramBS, 2) void k_bc_gram(int n, const double* __r
 // dst[e] = sum over g of part[g * count + e] for e < count, in a fixed order:
 // a workgroup takes EPB consecutive entries; its 256 / EPB thread groups add
 // the partials g = q, q + groups, ... (group q), and the group sums are added
-// in group order.  which 0: Gram partials, entries [0, 4096) to st->G0 and
-// [4096, 8192) to st->G1; which 1: column norms to st->rr.
-template <int EPB>
-__global__ __launch_bounds__(256) void k_bc_sum(const double* __restrict__ part, int G, int count, int which,
-                                                BcState* st, int gate)
+// in group order.  Gram partials: entries [0, 4096) to st->G0 and [4096, 8192)
+// to st->G1.  The workgroups past those, if any, add the column norms' partials
+// (norms[g * 64 + j], g < Gn) to st->rr: a launch of their own costs 3 us an
+// iteration.
+constexpr int kSumEntries = 32;
+
+__global__ __launch_bounds__(256) void k_bc_sum(const double* __restrict__ part, int G, int count,
+                                                const double* __restrict__ norms, int Gn, BcState* st, int gate)
 {
     if (bc_stopped(st, gate)) return;
-    constexpr int kGroups = 256 / EPB;
+    constexpr int EPB = kSumEntries, kGroups = 256 / EPB;
     __shared__ double red[kGroups][EPB];
     const int j = threadIdx.x % EPB, q = threadIdx.x / EPB;
-    const int e = blockIdx.x * EPB + j;
+    const bool norm = (int)blockIdx.x * EPB >= count;
+    const int e = blockIdx.x * EPB + j - (norm ? count : 0);
+    if (norm) {
+        part = norms;
+        G = Gn;
+        count = kB;
+    }
     double s = 0.0;
-    if (e < count) {
+    {
         int g = q;
         for (; g + 3 * kGroups < G; g += 4 * kGroups) {
             const double a0 = part[(size_t)g * count + e], a1 = part[(size_t)(g + kGroups) * count + e];
@@ -187,11 +196,11 @@ __global__ __launch_bounds__(256) void k_bc_sum(const double* __restrict__ part,
     }
     red[q][j] = s;
     __syncthreads();
-    if (q == 0 && e < count) {
+    if (q == 0) {
         double t = 0.0;
         for (int k = 0; k < kGroups; ++k) t += red[k][j];
-        if (which == 0) (e < kBB ? st->G0[e] : st->G1[e - kBB]) = t;
-        else st->rr[e] = t;
+        if (norm) st->rr[e] = t;
+        else (e < kBB ? st->G0[e] : st->G1[e - kBB]) = t;
     }
 }
 
@@ -872,25 +881,20 @@ struct BcOps {
         void* a[] = {&m, &X, &Y, &b->spmm_G, &b->st, &gate};
         launch((const void*)k_bc_spmm, b->spmm_G, kSpmmBS, st, a);
     }
-    void sum_grams(int nop, int G, int gate)
+    // With `norms` the column norms of the last BC_RUP too.
+    void sum_grams(int nop, int G, int gate, bool norms = false)
     {
-        int count = nop * kBB, which = 0;
-        void* r[] = {&b->part, &G, &count, &which, &b->st, &gate};
-        launch((const void*)k_bc_sum<32>, count / 32, 256, st, r);
+        int count = nop * kBB;
+        void* r[] = {&b->part, &G, &count, &b->part2, &b->gemm_G, &b->st, &gate};
+        launch((const void*)k_bc_sum, (count + (norms ? kB : 0)) / kSumEntries, 256, st, r);
     }
-    void gram(const double* U, const double* V0, const double* V1, int gate)
+    void gram(const double* U, const double* V0, const double* V1, int gate, bool norms = false)
     {
         int n = c->n;
         const int nop = V1 ? 2 : 1;
         void* a[] = {&n, &U, &V0, &V1, &c->dinv, &b->part, &b->gram_rpw, &b->gram_G, &b->st, &gate};
         launch(nop == 2 ? (const void*)k_bc_gram<2> : (const void*)k_bc_gram<1>, b->gram_G, kGramBS, st, a);
-        sum_grams(nop, b->gram_G, gate);
-    }
-    void norms(int gate)
-    {
-        int count = kB, which = 1;
-        void* r[] = {&b->part2, &b->gemm_G, &count, &which, &b->st, &gate};
-        launch((const void*)k_bc_sum<4>, kB / 4, 256, st, r);
+        sum_grams(nop, b->gram_G, gate, norms);
     }
     // With `grams` also Y'Y.
     void gemm(int mode, const double* U, double* Y, const double* Z, int gate, bool grams = false)
@@ -948,8 +952,7 @@ struct BcOps {
         launch((const void*)k_bc_alpha, 1, kSmallBS, st, a);
         gemm(BC_XUP, v.P, v.X, nullptr, 1);
         gemm(BC_RUP, v.Q, v.R, nullptr, 1);
-        norms(1);
-        gram(v.Q, v.R, nullptr, 1);
+        gram(v.Q, v.R, nullptr, 1, true);
         void* bta[] = {&b->st, &gate};
         launch((const void*)k_bc_beta, 1, kSmallBS, st, bta);
         gemm(BC_DIR, v.P, v.W, v.R, 1, true);
