@@ -391,6 +391,16 @@ static cg_graphs* make_graphs(cg_ctx* c, int form, bool fp32, int npl, int bs, i
 // per iteration, 1024 149, 8192 150; 1024 for the vectors 146.6, 256 157.
 constexpr int kEllMaxGrid = 2048, kEllUpdateGrid = 1024;
 
+// Rows per workgroup of the elementwise kernels, whole passes of its threads,
+// and their grid: 65^3 14.51 ms a solve against 14.66 with the rows spread evenly
+// over the largest grid (a second pass for 13 rows), 84^3 31.9 and 32.2, 110^3
+// 78.8 and 79.4; 96^3 46.6 and 46.3.
+static void ell_rows(int n, int grid, int& R, int& G)
+{
+    R = ((n + grid - 1) / grid + kEllBS - 1) / kEllBS * kEllBS;
+    G = ((n + R - 1) / R + 7) / 8 * 8;
+}
+
 static cg_graphs* make_ell_graphs(cg_ctx* c, int chunk, bool mat32, double drop)
 {
     cg_graphs* g = new cg_graphs();
@@ -404,8 +414,7 @@ static cg_graphs* make_ell_graphs(cg_ctx* c, int chunk, bool mat32, double drop)
         a.m = c->ell->map;
         a.keep = mat32 ? c->ell->keep32 : c->ell->keep;
         a.G = std::min(kEllMaxGrid, ((a.m.S + kEllWaves - 1) / kEllWaves + 7) / 8 * 8);
-        a.Gu = std::min(kEllUpdateGrid, ((c->n + kEllBS - 1) / kEllBS + 7) / 8 * 8);
-        a.R = (c->n + a.Gu - 1) / a.Gu;
+        ell_rows(c->n, kEllUpdateGrid, a.R, a.Gu);
         JPCG_HIP(hipMalloc(&g->part, sizeof(double) * (6 * (size_t)a.G + 2 * (size_t)a.Gu)));
         JPCG_HIP(hipMalloc(&g->st, g->st_bytes));
         JPCG_HIP(hipHostMalloc(&g->hst, g->st_bytes * 4, hipHostMallocDefault));
@@ -453,8 +462,7 @@ static cg_graphs* make_ell_sr_graphs(cg_ctx* c, int chunk)
         a.m = c->ell->map;
         a.keep = c->ell->keep;
         a.G = std::min(kEllMaxGrid / 2, ((a.m.S + kEllWaves - 1) / kEllWaves + 7) / 8 * 8);
-        a.Gu = std::min(kEllUpdateGrid / 2, ((c->n + kEllBS - 1) / kEllBS + 7) / 8 * 8);
-        a.R = (c->n + a.Gu - 1) / a.Gu;
+        ell_rows(c->n, kEllUpdateGrid / 2, a.R, a.Gu);
         JPCG_HIP(hipMalloc(&g->part, sizeof(double) * (4 * (size_t)a.G + 8 * (size_t)a.Gu)));
         JPCG_HIP(hipMalloc(&g->st, g->st_bytes));
         JPCG_HIP(hipHostMalloc(&g->hst, g->st_bytes * 4, hipHostMallocDefault));
