@@ -140,6 +140,7 @@ struct cg_batch {
     jpcg::BatchArgs args{};
     long long limit = 0;
     jpcg::cg_batch_resident* resident = nullptr;  // the systems on chip, where all of them fit
+    int solved_on_chip = -1;  // the last solve's result came from there
     bool general = false;  // solve by streaming the matrices all the same (while timing tile widths)
     std::string err;
 };
@@ -509,6 +510,7 @@ int cg_batch_solve(cg_batch* b, const double* b_cat, double* x_cat, double tol, 
             JPCG_HIP(hipMemcpyAsync(b->args.x, x_cat, vb, hipMemcpyDeviceToDevice, st));
             if (!run_batch_resident(b->resident, b->device, st, b_cat, b->args.x, tol, maxit, b->limit, r)) r = nullptr;
         }
+        b->solved_on_chip = r != nullptr;
         if (r) {
             JPCG_HIP(hipMemcpyAsync(x_cat, b->args.x, vb, hipMemcpyDeviceToDevice, st));
             JPCG_HIP(hipEventRecord(b->ev1, st));
@@ -593,5 +595,7 @@ void cg_batch_destroy(cg_batch* b)
     (void)hipStreamSynchronize(b->stream);
     free_batch(b);
 }
+
+int jpcg_test_batch_solved_on_chip(const cg_batch* b) { return b->solved_on_chip; }
 
 }  // extern "C"

@@ -52,6 +52,7 @@ struct cg_ctx {
     struct cg_graphs* graphs_ell = nullptr;  // standard form over slices
     struct cg_graphs* graphs_ell32 = nullptr;  // the same streaming FP32 values
     struct cg_resident* resident = nullptr;  // the on-chip solver, where the system fits it
+    int solved_on_chip = -1;                 // the last solve's result came from it
     struct cg_spmv_plan* spmv = nullptr;     // the standalone product's tiling and grid
     struct cg_multi* multi = nullptr;        // multi-RHS solver for one block width
     struct cg_multi* multi32 = nullptr;      // FP32 multi-RHS inner solver (mixed form)

@@ -907,7 +907,8 @@ static SolveResult run_any(cg_ctx* c, int form, const double* b, double* x, doub
                            double* hist, Graphs graphs)
 {
     RsOut o;
-    if (c->resident && run_resident(c, c->resident, form, b, x, tol, maxit, drop, hist, o)) {
+    c->solved_on_chip = c->resident && run_resident(c, c->resident, form, b, x, tol, maxit, drop, hist, o);
+    if (c->solved_on_chip) {
         SolveResult r;
         r.stop = o.stop;
         r.iters = o.iters;

@@ -9,6 +9,12 @@
 
 namespace jpcg {
 
+TestHooks& test_hooks()
+{
+    static thread_local TestHooks h;
+    return h;
+}
+
 constexpr int kMaxDevices = 64;
 
 std::mutex& resident_mutex(int device)
@@ -82,11 +88,13 @@ __global__ __launch_bounds__(kIndexBS) void k_rs_index(const RsIndexJob* __restr
     }
 }
 
-// Clears the exchange words (a tag of 0 is never awaited).
-__global__ void k_rs_clear(ulonglong2* words, int64_t pairs)
+// Clears the exchange words (a tag of 0 is never awaited) and keeps x.
+__global__ void k_rs_clear(ulonglong2* words, int64_t pairs, const double* __restrict__ x, double* __restrict__ x0,
+                           int64_t n)
 {
-    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < pairs; i += (int64_t)gridDim.x * blockDim.x)
-        words[i] = ulonglong2{0ull, 0ull};
+    const int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x, step = (int64_t)gridDim.x * blockDim.x;
+    for (int64_t i = t; i < pairs; i += step) words[i] = ulonglong2{0ull, 0ull};
+    for (int64_t i = t; i < n; i += step) x0[i] = x[i];
 }
 
 void launch_rs_index(hipStream_t st, const RsIndexJob* jobs, int njobs, const int* rowptr, const int* col, int hcap,
@@ -96,10 +104,10 @@ void launch_rs_index(hipStream_t st, const RsIndexJob* jobs, int njobs, const in
     JPCG_HIP(hipGetLastError());
 }
 
-void launch_rs_clear(hipStream_t st, u64* words, size_t nwords)
+void launch_rs_clear(hipStream_t st, u64* words, size_t nwords, const double* x, double* x0, int64_t n)
 {
     const int64_t pairs = (int64_t)(nwords / 2);
-    k_rs_clear<<<(int)std::min<int64_t>(4096, (pairs + 255) / 256), 256, 0, st>>>((ulonglong2*)words, pairs);
+    k_rs_clear<<<(int)std::min<int64_t>(4096, (pairs + 255) / 256), 256, 0, st>>>((ulonglong2*)words, pairs, x, x0, n);
     JPCG_HIP(hipGetLastError());
 }
 
@@ -162,7 +170,7 @@ static bool rs_geometry(int n, int cus, int& groups, int& members, int& rpw)
 void destroy_resident(cg_resident* r)
 {
     if (!r) return;
-    void* ptrs[] = {r->lidx, r->hcol, r->hcount, r->exported, r->words};
+    void* ptrs[] = {r->lidx, r->hcol, r->hcount, r->exported, r->words, r->x0};
     for (void* p : ptrs)
         if (p) (void)hipFree(p);
     if (r->out) (void)hipHostFree(r->out);
@@ -200,7 +208,8 @@ cg_resident* make_resident(cg_ctx* c)
         const size_t xw = (2 * (size_t)c->n + 15) / 16 * 16, pw = kRsSumBytes / sizeof(u64);
         r->nwords = 2 * xw + 2 * pw + 16;
         JPCG_HIP(hipMalloc(&r->words, sizeof(u64) * r->nwords));
-        JPCG_HIP(hipHostMalloc(&r->out, sizeof(RsOut), hipHostMallocDefault));
+        JPCG_HIP(hipMalloc(&r->x0, sizeof(double) * c->n));
+        JPCG_HIP(hipHostMalloc(&r->out, sizeof(RsOut) * 2, hipHostMallocDefault));
         JPCG_HIP(hipMalloc(&djobs, sizeof(RsIndexJob) * r->G));
         JPCG_HIP(hipMalloc(&dflag, sizeof(int)));
         JPCG_HIP(hipMemcpyAsync(djobs, jobs.data(), sizeof(RsIndexJob) * r->G, hipMemcpyHostToDevice, c->stream));
@@ -267,7 +276,8 @@ bool run_resident(cg_ctx* c, cg_resident* r, int form, const double* b, double* 
     s.b = b;
     s.x = x;
     s.hist = hist;
-    RsRun run{tol, drop * drop, maxit, r->abort, c->limit_ticks / 80, c->limit_ticks};
+    RsRun run{tol, drop * drop, maxit, -1, -1, r->abort, &r->out[1].stop, c->limit_ticks / 80, c->limit_ticks};
+    test_hooks().apply(run);
     const void* fn = rs_kernel(form, r->K, r->bs);
     const size_t lds = rs_lds(form, r->K, r->bs, r->rpw, r->halo, s.lds_slots);
     if (lds > kRsMaxLds) return false;
@@ -277,11 +287,23 @@ bool run_resident(cg_ctx* c, cg_resident* r, int form, const double* b, double* 
     // the card, would wait for each other.
     std::lock_guard<std::mutex> lock(resident_mutex(c->device));
     r->out->stop = RS_ABORTED;
-    launch_rs_clear(st, r->words, r->nwords);
+    *run.given_up = 0;
+    launch_rs_clear(st, r->words, r->nwords, x, r->x0, c->n);
     JPCG_HIP(hipLaunchKernel(fn, dim3(kRsXcds * r->sys.members), dim3(r->bs), args, lds, st));
     JPCG_HIP(hipStreamSynchronize(st));
+    if (*run.given_up || r->out->stop == RS_ABORTED) {
+        JPCG_HIP(hipMemcpyAsync(x, r->x0, sizeof(double) * c->n, hipMemcpyDeviceToDevice, st));
+        return false;
+    }
     res = *r->out;
-    return res.stop != RS_ABORTED;
+    return true;
 }
 
 }  // namespace jpcg
+
+extern "C" void jpcg_test_on_chip(long long wait_limit, int absent, int quit)
+{
+    jpcg::test_hooks() = jpcg::TestHooks{wait_limit, absent, quit};
+}
+
+extern "C" int jpcg_test_solved_on_chip(const cg_ctx* c) { return c->solved_on_chip; }

@@ -34,9 +34,11 @@
 //
 // Every workgroup adds the same sums in the same order, so all of them reach
 // the same bits and take the same branches.  Every wait is bounded: a
-// workgroup that waits too long raises an abort word, everyone leaves, x is
-// not written, and the host falls back to the kernels of std_kernels.hpp /
-// sr_kernels.hpp.
+// workgroup that waits too long raises an abort word and leaves, and so do all
+// that wait in vain for it.  Others may have seen what it did not and finish
+// the solve, so the host takes no result of a launch in which any workgroup
+// gave up: x is put back and the kernels of std_kernels.hpp, sr_kernels.hpp or
+// ell_kernels.hpp solve the system.
 //
 // What bounds it: the latency of the rounds, two an iteration in the standard
 // form and one in the single-reduction form, each a chain of LDS, cross-lane
@@ -116,7 +118,9 @@ struct RsSys {
 struct RsRun {
     double tol, drop2;  // drop2 > 0: the FP32-matrix form's reliable updates (see CgArgsT)
     int maxit;
-    unsigned* abort;
+    int absent, quit;   // tests: this member of the team is not there, or gives up when the solve ends; else -1
+    unsigned* abort;    // raised for the other workgroups
+    int* given_up;      // and for the host (pinned)
     long long limit_first, limit;  // bounds of a wait, device wall clock ticks
 };
 
@@ -154,26 +158,33 @@ __device__ __forceinline__ double rs_value(rs_words w)
 }
 __device__ __forceinline__ bool rs_tagged(rs_words w, unsigned tag) { return w.y == tag && w.w == tag; }
 
+// The calling workgroup leaves before the end: the others and the host are told.
+__device__ __forceinline__ void rs_give_up(const RsRun& run)
+{
+    __hip_atomic_store(run.abort, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(run.given_up, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 // A bounded wait: true while it may go on.  Past its limit it allows one more
-// look, so that a workgroup gives up only if what it awaits is missing then;
-// what everyone else has seen is not missing, so a solve that some workgroup
-// finished is finished by all.
+// look.  What is missing in that look may come right after it and be seen by
+// the other workgroups, so whether one gave up says nothing about the others:
+// only the host decides, by given_up.
 struct RsWait {
-    unsigned* abort;
+    const RsRun& run;
     long long limit, t0;
     int spins;
     bool last;
-    __device__ __forceinline__ RsWait(unsigned* a, long long l) : abort(a), limit(l), t0(0), spins(0), last(false) {}
+    __device__ __forceinline__ RsWait(const RsRun& r, long long l) : run(r), limit(l), t0(0), spins(0), last(false) {}
     __device__ __forceinline__ bool more()
     {
         if (last) {
-            __hip_atomic_store(abort, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            rs_give_up(run);
             return false;
         }
         if ((++spins & 31) != 0) return true;
         const long long now = wall_clock64();
         if (spins == 32) t0 = now;
-        last = now - t0 > limit || __hip_atomic_load(abort, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0u;
+        last = now - t0 > limit || __hip_atomic_load(run.abort, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0u;
         return true;
     }
 };
@@ -307,7 +318,7 @@ struct RsTeam {
         unsigned need = 0;
 #pragma unroll
         for (int j = 0; j < NH; ++j) need |= halo_slot(j) < H ? 1u << j : 0u;
-        RsWait wait(run.abort, limit);
+        RsWait wait(run, limit);
         while (need) {
             rs_words got[NH];
             asm volatile("" ::: "memory");  // load again
@@ -330,7 +341,7 @@ struct RsTeam {
     __device__ __forceinline__ bool await(const char* base, unsigned byte, bool use, double& v)
     {
         const auto buf = rs_buffer(base);
-        RsWait wait(run.abort, limit);
+        RsWait wait(run, limit);
         while (true) {
             asm volatile("" ::: "memory");  // load again
             const rs_words got = rs_load(buf, byte);
@@ -343,6 +354,7 @@ struct RsTeam {
     // First round: do the group's workgroups sit on one XCD?
     __device__ __forceinline__ bool start()
     {
+        if (L == run.absent) return false;
         if (s.groups * s.members == 1) return true;
         unsigned xcc;
         asm volatile("s_getreg_b32 %0, hwreg(HW_REG_XCC_ID)" : "=s"(xcc));
@@ -533,6 +545,10 @@ struct RsTeam {
 
     __device__ __forceinline__ void finish(int stop, int iters, int repl, double nb, double rr, double rrt)
     {
+        if (L == run.quit) {
+            if (tid == 0) rs_give_up(run);
+            return;
+        }
         if (has() && stop != STOP_CONV0) s.x[row] = stop == STOP_ZERO_RHS ? 0.0 : xo;
         if (tid == 0 && L == 0) *s.out = RsOut{stop, iters, repl, 0, nb, rr, rrt};
     }

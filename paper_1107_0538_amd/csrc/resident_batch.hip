@@ -55,7 +55,7 @@ __global__ __launch_bounds__(BS, BS == 512 ? 4 : 1) void k_rs_batch(RsBatchArgs 
     if (threadIdx.x == 0) {
         sh.fail = 0;
         __hip_atomic_fetch_add(a.gate, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        RsWait wait(a.run.abort, a.gate_limit);
+        RsWait wait(a.run, a.gate_limit);
         while (__hip_atomic_load(a.gate, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < gridDim.x) {
             __builtin_amdgcn_s_sleep(2);
             if (!wait.more()) {
@@ -114,7 +114,7 @@ struct cg_batch_resident {
     int* hcount = nullptr;
     unsigned* exported = nullptr;
     u64* words = nullptr;
-    RsOut* out = nullptr;  // pinned
+    RsOut* out = nullptr;  // pinned; behind the systems' the word of workgroups that gave up
     RsBatchArgs args{};
 };
 
@@ -264,7 +264,7 @@ cg_batch_resident* make_batch_resident(const RsBatchMatrix& m, int cus, hipStrea
         JPCG_HIP(hipMalloc(&r->hcount, sizeof(int) * slot));
         JPCG_HIP(hipMalloc(&r->exported, sizeof(unsigned) * bits));
         JPCG_HIP(hipMalloc(&r->words, sizeof(u64) * r->nwords));
-        JPCG_HIP(hipHostMalloc(&r->out, sizeof(RsOut) * m.nsys, hipHostMallocDefault));
+        JPCG_HIP(hipHostMalloc(&r->out, sizeof(RsOut) * (m.nsys + 1), hipHostMallocDefault));
         JPCG_HIP(hipMalloc(&djobs, sizeof(RsIndexJob) * slot));
         JPCG_HIP(hipMalloc(&dflag, sizeof(int)));
         auto up = [&](void* d, const void* h, size_t bytes) {
@@ -311,6 +311,7 @@ cg_batch_resident* make_batch_resident(const RsBatchMatrix& m, int cus, hipStrea
         a.common.xch_step = xw;
         a.run.abort = (unsigned*)(a.common.xch + 2 * xw);
         a.gate = a.run.abort + 32;
+        a.run.given_up = &r->out[m.nsys].stop;
         a.out = r->out;
         return r;
     } catch (...) {
@@ -335,16 +336,18 @@ bool run_batch_resident(cg_batch_resident* r, int device, hipStream_t st, const 
     a.run.limit_first = limit;
     a.run.limit = limit;
     a.gate_limit = limit / 160;
+    test_hooks().apply(a.run);
     std::lock_guard<std::mutex> lock(resident_mutex(device));
     for (int s = 0; s < r->nsys; ++s) r->out[s].stop = RS_ABORTED;
-    launch_rs_clear(st, r->words, r->nwords);
+    *a.run.given_up = 0;
+    launch_rs_clear(st, r->words, r->nwords, nullptr, nullptr, 0);
     void* args[] = {&a};
     JPCG_HIP(hipLaunchKernel(rs_batch_kernel(r->K, r->bs), dim3(r->grid), dim3(r->bs), args, r->lds, st));
     JPCG_HIP(hipStreamSynchronize(st));
     out = r->out;
     for (int s = 0; s < r->nsys; ++s)
         if (out[s].stop == RS_ABORTED) return false;
-    return true;
+    return *a.run.given_up == 0;
 }
 
 }  // namespace jpcg

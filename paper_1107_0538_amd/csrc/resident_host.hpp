@@ -5,6 +5,7 @@
 
 #include "context.hpp"
 #include "resident.hpp"
+#include "test_hooks.hpp"
 
 namespace jpcg {
 
@@ -36,7 +37,8 @@ struct RsLds {
 
 void launch_rs_index(hipStream_t st, const RsIndexJob* jobs, int njobs, const int* rowptr, const int* col, int hcap,
                      int* hcol, int* hcount, unsigned short* lidx, unsigned* exported, int* flag);
-void launch_rs_clear(hipStream_t st, u64* words, size_t nwords);
+// Clears the words and copies n entries of x to x0 (n may be 0).
+void launch_rs_clear(hipStream_t st, u64* words, size_t nwords, const double* x, double* x0, int64_t n);
 size_t rs_lds(int form, int K, int bs, int rows, int halo, int& slots);
 
 // Held by every launch whose workgroups wait for each other, until it ends.
@@ -53,7 +55,8 @@ struct cg_resident {
     unsigned* exported = nullptr;
     jpcg::u64* words = nullptr;  // exchange buffers and the abort word
     unsigned* abort = nullptr;
-    jpcg::RsOut* out = nullptr;  // pinned
+    double* x0 = nullptr;        // x as the caller passed it
+    jpcg::RsOut* out = nullptr;  // pinned; out[1].stop: a workgroup gave up
     jpcg::RsSys sys{};
 };
 
@@ -64,8 +67,8 @@ namespace jpcg {
 cg_resident* make_resident(cg_ctx* c);
 void destroy_resident(cg_resident* r);
 
-// False if the workgroups could not all be on the card in time; x is then as
-// it was.
+// False if some workgroup gave up waiting, as when they could not all be on the
+// card in time; x is then put back to what it was.
 bool run_resident(cg_ctx* c, cg_resident* r, int form, const double* b, double* x, double tol, int maxit, double drop,
                   double* hist, RsOut& res);
 
@@ -85,7 +88,7 @@ struct cg_batch_resident;
 cg_batch_resident* make_batch_resident(const RsBatchMatrix& m, int cus, hipStream_t st);
 void destroy_batch_resident(cg_batch_resident* r);
 // Solves on the batch's own b and x (maxit <= 0: each system's rows) and fills
-// out[nsys].  False if the workgroups could not all be on the card in time.
+// out[nsys].  False if some workgroup gave up waiting: none of x counts then.
 bool run_batch_resident(cg_batch_resident* r, int device, hipStream_t st, const double* b, double* x, double tol,
                         int maxit, long long limit, const RsOut*& out);
 

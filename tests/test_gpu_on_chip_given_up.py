@@ -1,0 +1,126 @@
+"""On-chip solves in which a workgroup gives up waiting.
+
+Every wait of the on-chip kernels is bounded.  Whatever the other workgroups
+have seen and written by then, the host takes nothing of such a launch: x goes
+back to what the caller passed and the general kernels solve the system, so
+the result is bitwise that of a context made for them.  A workgroup that is
+not there keeps the others waiting for as long as they may (a millisecond
+here); one that leaves at the very end is one whose last look came before its
+partners' words, which the partners have seen.
+"""
+import ctypes
+
+import numpy as np
+import pytest
+
+import workloads as W
+from test_gpu_resident import banded
+
+pytestmark = pytest.mark.gpu
+
+
+def _t(a, dev):
+    import torch
+
+    return torch.as_tensor(np.ascontiguousarray(a), device=dev)
+
+
+@pytest.fixture
+def on_chip(cuda):
+    """on_chip(wait_limit, absent, quit) sets the conditions for this thread's calls (-1: as ever)."""
+    from paper_1107_0538_amd import capi
+
+    f = capi.load().jpcg_test_on_chip
+    f.argtypes, f.restype = [ctypes.c_longlong, ctypes.c_int, ctypes.c_int], None
+    yield f
+    f(-1, -1, -1)
+
+
+def solved_on_chip(s):
+    from paper_1107_0538_amd import capi
+
+    f = capi.load().jpcg_test_solved_on_chip
+    f.argtypes, f.restype = [ctypes.c_void_p], ctypes.c_int
+    return f(s.ctx)
+
+
+def batch_solved_on_chip(bt):
+    from paper_1107_0538_amd import capi
+
+    f = capi.load().jpcg_test_batch_solved_on_chip
+    f.argtypes, f.restype = [ctypes.c_void_p], ctypes.c_int
+    return f(bt.h)
+
+
+MS = 100000  # device ticks
+HOW = {"first absent": (MS, 0, -1), "third absent": (MS, 2, -1), "first leaves": (-1, -1, 0),
+       "third leaves": (-1, -1, 2), "nobody": (-1, 10000, 10000)}
+
+
+@pytest.mark.parametrize("how", list(HOW))
+@pytest.mark.parametrize("form", ["standard", "single", "fp32"])
+@pytest.mark.parametrize("n,offsets", [(60, (1,)), (4000, (1, 30)), (30000, (1, 150))])  # one workgroup, group, eight
+def test_given_up_solve_is_done_again(cuda, on_chip, n, offsets, form, how):
+    from paper_1107_0538_amd import Solver
+
+    a = banded(n, offsets, seed=n)
+    rng = np.random.default_rng(n)
+    b, x0 = _t(rng.uniform(-1, 1, n), cuda), _t(rng.uniform(-1, 1, n), cuda)
+    kw = dict(form="single") if form == "single" else dict(fp32_copy=form == "fp32")
+
+    def solve(s):
+        return (s.solve_mixed_matrix if form == "fp32" else s.solve)(b, x0=x0)
+
+    # A chunk length keeps the reference off the chip (16 and 8 are the
+    # defaults), 32-bit columns off the slices, which small systems have not.
+    ref, iref = solve(Solver(a, chunk=8 if form == "fp32" else 16, col_bits=32, **kw))
+    s = Solver(a, **kw)
+    alone, _ = solve(s)
+    assert solved_on_chip(s) == 1
+    on_chip(*HOW[how])
+    x, info = solve(s)
+    expected = how == "nobody" or (n == 60 and "third" in how)  # a member that there is not
+    assert solved_on_chip(s) == int(expected)
+    if expected:
+        assert (x == alone).all()
+    else:
+        assert (x == ref).all() and (info["iters"], info["status"]) == (iref["iters"], iref["status"])
+    on_chip(-1, -1, -1)
+    x, _ = solve(Solver(a, **kw))
+    assert (x == alone).all()
+
+
+@pytest.mark.parametrize("how", list(HOW))
+def test_given_up_batch_is_done_again(cuda, on_chip, how):
+    from paper_1107_0538_amd import Batch
+
+    mats = [banded(n, (1, 30), seed=i) for i, n in enumerate((700, 3000, 65, 20000))]
+    rng = np.random.default_rng(4)
+    total = sum(a.n for a in mats)
+    b, x0 = _t(rng.uniform(-1, 1, total), cuda), _t(rng.uniform(-1, 1, total), cuda)
+    ref, iref = Batch(mats, nnz_per_lane=16).solve(b, x0=x0)
+    bt = Batch(mats)
+    alone, _ = bt.solve(b, x0=x0)
+    assert batch_solved_on_chip(bt) == 1
+    on_chip(*HOW[how])
+    x, info = bt.solve(b, x0=x0)
+    assert batch_solved_on_chip(bt) == int(how == "nobody")
+    if how == "nobody":
+        assert (x == alone).all()
+    else:
+        assert (x == ref).all() and [i["iters"] for i in info] == [i["iters"] for i in iref]
+    on_chip(-1, -1, -1)
+    x, _ = Batch(mats).solve(b, x0=x0)
+    assert (x == alone).all()
+
+
+def test_batch_reports_where_it_ran(cuda):
+    from paper_1107_0538_amd import Batch
+
+    a, rhs = W.problem(8, 0)
+    bt = Batch([a, a])
+    bt.solve(_t(np.concatenate([rhs, rhs]), cuda))
+    assert batch_solved_on_chip(bt) == 1
+    bt = Batch([a, a], nnz_per_lane=8)
+    bt.solve(_t(np.concatenate([rhs, rhs]), cuda))
+    assert batch_solved_on_chip(bt) == 0
