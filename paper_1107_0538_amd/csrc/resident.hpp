@@ -121,7 +121,9 @@ struct RsRun {
     int absent, quit;   // tests: this member of the team is not there, or gives up when the solve ends; else -1
     unsigned* abort;    // raised for the other workgroups
     int* given_up;      // and for the host (pinned)
-    long long limit_first, limit;  // bounds of a wait, device wall clock ticks
+    // Bounds of a wait, device wall clock ticks: until a solve's first round has
+    // brought every workgroup's sums, and from then on.
+    long long limit_first, limit;
 };
 
 // A double in flight: two 8-byte words, each with its tag, loaded and stored
@@ -375,7 +377,6 @@ struct RsTeam {
         __syncthreads();
         if (__builtin_amdgcn_readfirstlane(*fail)) return false;
         local = rs_uniform(tot[0]) != 0.0;
-        limit = run.limit;
         return true;
     }
 
@@ -619,6 +620,7 @@ struct RsTeam {
                 ++tag;
                 publish(z);
                 if (!round<true>(q, hv)) return false;
+                limit = run.limit;
                 rr = q[1];
                 if (begin) {
                     nb = rs_uniform(sqrt(q[2]));
@@ -738,6 +740,7 @@ struct RsTeam {
                     ++tag;
                     publish(own);
                     if (!round<true>(q, hv)) return false;
+                    limit = run.limit;
                     if (pass == 1) {
                         if (begin) {
                             rec = keep(q[0]);

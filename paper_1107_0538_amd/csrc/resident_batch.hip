@@ -106,6 +106,7 @@ static const void* rs_batch_kernel(int K, int bs)
 struct cg_batch_resident {
     int nsys = 0, K = 0, bs = 0, grid = 0;
     size_t lds = 0, nwords = 0;
+    long long rows = 0;  // of all systems
     RsBatchSys* sys = nullptr;
     RsBatchJob* jobs = nullptr;
     int* job_off = nullptr;
@@ -235,6 +236,7 @@ cg_batch_resident* make_batch_resident(const RsBatchMatrix& m, int cus, hipStrea
     int* dflag = nullptr;
     try {
         r->nsys = m.nsys;
+        r->rows = total;
         r->K = maxrow <= 16 ? 16 : 28;
         r->bs = per_cu == 1 ? 256 : 512;
         r->grid = kRsXcds * slots;
@@ -331,12 +333,16 @@ bool run_batch_resident(cg_batch_resident* r, int device, hipStream_t st, const 
     a.run.tol = tol;
     a.run.drop2 = 0.0;
     a.run.maxit = maxit;
-    // A wait for a team's other workgroups lasts as long as their earlier
-    // systems take; the gate only as long as a launch does.
-    a.run.limit_first = limit;
+    // A system's first round lasts as long as its workgroups' earlier systems
+    // take: as all are on the card (the gate) and these end by themselves, in
+    // maxit iterations or by a wait of their own that runs out, its limit is
+    // above what all systems' iterations can take (100 us each; 6 measured).  The
+    // gate waits only as long as a launch does.
     a.run.limit = limit;
     a.gate_limit = limit / 160;
     test_hooks().apply(a.run);
+    const long long iterations = maxit > 0 ? (long long)maxit * r->nsys : r->rows;
+    a.run.limit_first = a.run.limit + iterations * (limit / 80000);
     std::lock_guard<std::mutex> lock(resident_mutex(device));
     for (int s = 0; s < r->nsys; ++s) r->out[s].stop = RS_ABORTED;
     *a.run.given_up = 0;

@@ -88,7 +88,8 @@ struct cg_batch_resident;
 cg_batch_resident* make_batch_resident(const RsBatchMatrix& m, int cus, hipStream_t st);
 void destroy_batch_resident(cg_batch_resident* r);
 // Solves on the batch's own b and x (maxit <= 0: each system's rows) and fills
-// out[nsys].  False if some workgroup gave up waiting: none of x counts then.
+// out[nsys].  limit: 8 s in device ticks, the most that a round takes.  False if
+// some workgroup gave up waiting: none of x counts then.
 bool run_batch_resident(cg_batch_resident* r, int device, hipStream_t st, const double* b, double* x, double tol,
                         int maxit, long long limit, const RsOut*& out);
 

@@ -114,6 +114,28 @@ def test_given_up_batch_is_done_again(cuda, on_chip, how):
     assert (x == alone).all()
 
 
+def test_batch_waits_for_earlier_systems(cuda, on_chip):
+    # Systems that queue for the card, two of three solved in a tenth of the
+    # iterations: a team's first round lasts until its last workgroup is through
+    # with the system before, over 1 ms in ten of them, while no other round may
+    # take longer than 0.2 ms.
+    from paper_1107_0538_amd import Batch
+
+    mats, bs = [], []
+    for i in range(32):
+        a, b = W.problem(40 - i % 8, i)
+        mats.append(banded(a.n, (1, 30), seed=i) if i % 3 else a)
+        bs.append(b)
+    b = _t(np.concatenate(bs), cuda)
+    bt = Batch(mats)
+    alone, ialone = bt.solve(b)
+    assert batch_solved_on_chip(bt) == 1
+    on_chip(MS // 5, -1, -1)
+    x, info = bt.solve(b)
+    assert batch_solved_on_chip(bt) == 1
+    assert (x == alone).all() and [i["iters"] for i in info] == [i["iters"] for i in ialone]
+
+
 def test_batch_reports_where_it_ran(cuda):
     from paper_1107_0538_amd import Batch
 
