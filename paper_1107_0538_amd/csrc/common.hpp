@@ -237,4 +237,19 @@ struct HipError {
         if (e_ != hipSuccess) throw ::jpcg::HipError{e_, #call};   \
     } while (0)
 
+// In a handler: whether the exception is device memory running out (HIP's own
+// record of the error is then cleared).
+inline bool out_of_memory()
+{
+    try {
+        throw;
+    } catch (const HipError& e) {
+        if (e.code != hipErrorOutOfMemory) return false;
+        (void)hipGetLastError();
+        return true;
+    } catch (...) {
+        return false;
+    }
+}
+
 }  // namespace jpcg

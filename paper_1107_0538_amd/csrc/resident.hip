@@ -15,6 +15,11 @@ TestHooks& test_hooks()
     return h;
 }
 
+void rs_memory()
+{
+    if (test_hooks().no_memory) throw HipError{hipErrorOutOfMemory, "on-chip solver"};
+}
+
 constexpr int kMaxDevices = 64;
 
 std::mutex& resident_mutex(int device)
@@ -187,6 +192,7 @@ cg_resident* make_resident(cg_ctx* c)
     RsIndexJob* djobs = nullptr;
     int* dflag = nullptr;
     try {
+        rs_memory();
         r->K = maxrow <= 16 ? 16 : 28;
         r->rpw = rpw;
         r->bs = rpw <= 256 ? 256 : rpw <= 640 ? 640 : 1024;
@@ -256,7 +262,8 @@ cg_resident* make_resident(cg_ctx* c)
         if (djobs) (void)hipFree(djobs);
         if (dflag) (void)hipFree(dflag);
         destroy_resident(r);
-        throw;
+        if (!out_of_memory()) throw;
+        return nullptr;  // the other kernels do without
     }
 }
 
@@ -303,7 +310,12 @@ bool run_resident(cg_ctx* c, cg_resident* r, int form, const double* b, double* 
 
 extern "C" void jpcg_test_on_chip(long long wait_limit, int absent, int quit)
 {
-    jpcg::test_hooks() = jpcg::TestHooks{wait_limit, absent, quit};
+    jpcg::TestHooks& h = jpcg::test_hooks();
+    h.wait_limit = wait_limit;
+    h.absent = absent;
+    h.quit = quit;
 }
+
+extern "C" void jpcg_test_no_memory(int on) { jpcg::test_hooks().no_memory = on != 0; }
 
 extern "C" int jpcg_test_solved_on_chip(const cg_ctx* c) { return c->solved_on_chip; }

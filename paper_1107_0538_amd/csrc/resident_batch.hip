@@ -235,6 +235,7 @@ cg_batch_resident* make_batch_resident(const RsBatchMatrix& m, int cus, hipStrea
     RsIndexJob* djobs = nullptr;
     int* dflag = nullptr;
     try {
+        rs_memory();
         r->nsys = m.nsys;
         r->rows = total;
         r->K = maxrow <= 16 ? 16 : 28;
@@ -320,7 +321,8 @@ cg_batch_resident* make_batch_resident(const RsBatchMatrix& m, int cus, hipStrea
         if (djobs) (void)hipFree(djobs);
         if (dflag) (void)hipFree(dflag);
         destroy_batch_resident(r);
-        throw;
+        if (!out_of_memory()) throw;
+        return nullptr;  // the matrices are streamed
     }
 }
 

@@ -41,6 +41,9 @@ void launch_rs_index(hipStream_t st, const RsIndexJob* jobs, int njobs, const in
 void launch_rs_clear(hipStream_t st, u64* words, size_t nwords, const double* x, double* x0, int64_t n);
 size_t rs_lds(int form, int K, int bs, int rows, int halo, int& slots);
 
+// Throws out of memory where a test asks for that.
+void rs_memory();
+
 // Held by every launch whose workgroups wait for each other, until it ends.
 std::mutex& resident_mutex(int device);
 
@@ -63,7 +66,7 @@ struct cg_resident {
 namespace jpcg {
 
 // Null when the system does not fit (rows too long, too many, or referring to
-// too many other rows).
+// too many other rows), or there is no memory for it.
 cg_resident* make_resident(cg_ctx* c);
 void destroy_resident(cg_resident* r);
 
@@ -84,7 +87,7 @@ struct RsBatchMatrix {
     const double* dinv;
 };
 struct cg_batch_resident;
-// Null when some system does not fit.
+// Null when some system does not fit, or there is no memory.
 cg_batch_resident* make_batch_resident(const RsBatchMatrix& m, int cus, hipStream_t st);
 void destroy_batch_resident(cg_batch_resident* r);
 // Solves on the batch's own b and x (maxit <= 0: each system's rows) and fills

@@ -13,7 +13,9 @@ import ctypes
 import numpy as np
 import pytest
 
+import oracle
 import workloads as W
+from conftest import tol_recomputed
 from test_gpu_resident import banded
 
 pytestmark = pytest.mark.gpu
@@ -146,3 +148,24 @@ def test_batch_reports_where_it_ran(cuda):
     bt = Batch([a, a], nnz_per_lane=8)
     bt.solve(_t(np.concatenate([rhs, rhs]), cuda))
     assert batch_solved_on_chip(bt) == 0
+
+
+def test_no_memory_for_the_on_chip_solver(cuda):
+    # The on-chip solver is one way of several: contexts and batches are made
+    # without it where its arrays find no memory.
+    from paper_1107_0538_amd import Batch, Solver, capi
+
+    a, b = W.problem(12, 0)
+    no_memory = capi.load().jpcg_test_no_memory
+    no_memory(1)
+    try:
+        s = Solver(a)
+        bt = Batch([a, a])
+    finally:
+        no_memory(0)
+    for x, info in (s.solve(_t(b, cuda)), Solver(a).solve(_t(b, cuda))):
+        assert info["status"] == 0 and oracle.relres(a, b, x.cpu().numpy()) <= tol_recomputed(a.n)
+    assert solved_on_chip(s) == 0
+    x, infos = bt.solve(_t(np.concatenate([b, b]), cuda))
+    assert batch_solved_on_chip(bt) == 0 and all(i["status"] == 0 for i in infos)
+    assert (x[:a.n] == x[a.n:]).all() and oracle.relres(a, b, x[:a.n].cpu().numpy()) <= tol_recomputed(a.n)
