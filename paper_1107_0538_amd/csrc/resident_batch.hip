@@ -28,6 +28,7 @@ struct RsBatchSys {
     int slot0;   // first entry of its halo lists
     int bits0;   // first word of its exported bits
     int line0;   // first 128-byte line of its exchanged vectors
+    int sums0;   // of its sums
 };
 struct RsBatchJob {
     int sys, index;  // member `index` of the system's team
@@ -37,7 +38,7 @@ struct RsBatchArgs {
     const RsBatchSys* sys;
     const RsBatchJob* jobs;
     const int* job_off;  // per workgroup, and the end
-    RsSys common;        // bases of all systems' arrays (sums: two of kRsSumBytes per system)
+    RsSys common;        // bases of all systems' arrays
     RsOut* out;
     unsigned* gate;
     long long gate_limit;
@@ -83,7 +84,7 @@ __global__ __launch_bounds__(BS, BS == 512 ? 4 : 1) void k_rs_batch(RsBatchArgs 
         s.hcount += slot0;
         s.exported += rs_scalar(t.bits0);
         s.xch += 16 * (size_t)rs_scalar(t.line0);
-        s.sums += (size_t)sys * 2 * kRsSumBytes;
+        s.sums += 128 * (size_t)rs_scalar(t.sums0);
         s.out = a.out + sys;
         RsRun run = a.run;
         if (run.maxit <= 0) run.maxit = s.n;
@@ -208,7 +209,12 @@ cg_batch_resident* make_batch_resident(const RsBatchMatrix& m, int cus, hipStrea
     const int per_cu = spread <= 256 ? 1 : 2;
     const int slots = per_xcd * per_cu, target = per_cu == 1 ? std::max(128, spread) : 512;
     std::vector<RsBatchSys> sys(m.nsys);
-    int slot = 0, bits = 0, line = 0, rows_max = 0;
+    // Sums: 2 kRsSumBytes for a team of several groups; teams of one group have the
+    // places of a group each, 16 to as many bytes; a workgroup alone has none.  (A
+    // layout of 5 KB for a team of one group took solves of 4096 rows from 398 us to
+    // 418: it matters to the caches where the two parities lie.)
+    constexpr int kSumLines = (int)(2 * kRsSumBytes / 128), kGroupLines = 16 * kRsSums * kRsGroup / 128;
+    int slot = 0, bits = 0, line = 0, sums = 0, shared = 0, in_shared = kRsGroups, rows_max = 0;
     for (int s = 0; s < m.nsys; ++s) {
         RsBatchSys& t = sys[s];
         const int n = m.rows[s];
@@ -226,6 +232,18 @@ cg_batch_resident* make_batch_resident(const RsBatchMatrix& m, int cus, hipStrea
         t.slot0 = slot;
         t.bits0 = bits;
         t.line0 = line;
+        t.sums0 = 0;
+        if (t.groups > 1) {
+            t.sums0 = sums;
+            sums += kSumLines;
+        } else if (teams > 1) {
+            if (in_shared == kRsGroups) {
+                shared = sums;
+                sums += kSumLines;
+                in_shared = 0;
+            }
+            t.sums0 = shared + kGroupLines * in_shared++;
+        }
         slot += teams;
         bits += (n + 31) / 32;
         line += (n + 7) / 8;
@@ -257,7 +275,7 @@ cg_batch_resident* make_batch_resident(const RsBatchMatrix& m, int cus, hipStrea
             jobs.insert(jobs.end(), l.begin(), l.end());
             job_off.push_back((int)jobs.size());
         }
-        const size_t xw = 16 * (size_t)line, sw = 2 * kRsSumBytes / sizeof(u64) * (size_t)m.nsys;
+        const size_t xw = 16 * (size_t)line, sw = 16 * (size_t)sums;
         r->nwords = 2 * xw + sw + 32;  // a line each for the abort word and the gate
         JPCG_HIP(hipMalloc(&r->sys, sizeof(RsBatchSys) * m.nsys));
         JPCG_HIP(hipMalloc(&r->jobs, sizeof(RsBatchJob) * jobs.size()));

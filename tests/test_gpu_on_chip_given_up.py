@@ -169,3 +169,24 @@ def test_no_memory_for_the_on_chip_solver(cuda):
     x, infos = bt.solve(_t(np.concatenate([b, b]), cuda))
     assert batch_solved_on_chip(bt) == 0 and all(i["status"] == 0 for i in infos)
     assert (x[:a.n] == x[a.n:]).all() and oracle.relres(a, b, x[:a.n].cpu().numpy()) <= tol_recomputed(a.n)
+
+
+def test_many_small_systems_take_little_memory(cuda):
+    # Systems of one workgroup exchange no sums: 500 of them, with all their
+    # arrays, in less than 16 MB.
+    import torch
+
+    from paper_1107_0538_amd import Batch
+
+    a = banded(40, (1,), seed=3)
+    Batch([a] * 8)  # what the library and the runtime take once
+    torch.cuda.synchronize()
+    free = torch.cuda.mem_get_info()[0]
+    bt = Batch([a] * 500)
+    held = free - torch.cuda.mem_get_info()[0]
+    assert held < 16 << 20, held
+    b = _t(np.random.default_rng(5).uniform(-1, 1, 40), cuda).repeat(500)
+    x, infos = bt.solve(b)
+    assert batch_solved_on_chip(bt) == 1 and all(i["status"] == 0 for i in infos)
+    assert (x.view(500, 40) == x[:40]).all()
+    assert oracle.relres(a, b[:40].cpu().numpy(), x[:40].cpu().numpy()) <= tol_recomputed(40)
