@@ -231,11 +231,15 @@ cg_resident* make_resident(cg_ctx* c)
         (void)hipFree(dflag);
         djobs = nullptr;
         dflag = nullptr;
-        if (flag) {
+        int slots = 0;
+        if (!flag) r->halo = *std::max_element(hcount.begin(), hcount.end());
+        // The single-reduction form keeps more of the halo; a context of that form
+        // solves in the standard one too where it has FP32 values.
+        const int form = c->form == CG_FORM_SINGLE_REDUCTION && !c->val32 ? RS_SINGLE : RS_STANDARD;
+        if (flag || rs_lds(form, r->K, r->bs, r->rpw, r->halo, slots) > kRsMaxLds) {
             destroy_resident(r);
             return nullptr;
         }
-        r->halo = *std::max_element(hcount.begin(), hcount.end());
         RsSys& s = r->sys;
         s.row0 = 0;
         s.n = c->n;
@@ -287,7 +291,7 @@ bool run_resident(cg_ctx* c, cg_resident* r, int form, const double* b, double* 
     test_hooks().apply(run);
     const void* fn = rs_kernel(form, r->K, r->bs);
     const size_t lds = rs_lds(form, r->K, r->bs, r->rpw, r->halo, s.lds_slots);
-    if (lds > kRsMaxLds) return false;
+    if (lds > kRsMaxLds || !r->retry.now()) return false;
     JPCG_HIP(hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, kRsMaxLds));
     void* args[] = {&s, &run};
     // One resident solve per device at a time: two of them, each partly on
@@ -298,7 +302,9 @@ bool run_resident(cg_ctx* c, cg_resident* r, int form, const double* b, double* 
     launch_rs_clear(st, r->words, r->nwords, x, r->x0, c->n);
     JPCG_HIP(hipLaunchKernel(fn, dim3(kRsXcds * r->sys.members), dim3(r->bs), args, lds, st));
     JPCG_HIP(hipStreamSynchronize(st));
-    if (*run.given_up || r->out->stop == RS_ABORTED) {
+    const bool ok = !*run.given_up && r->out->stop != RS_ABORTED;
+    r->retry.done(ok);
+    if (!ok) {
         JPCG_HIP(hipMemcpyAsync(x, r->x0, sizeof(double) * c->n, hipMemcpyDeviceToDevice, st));
         return false;
     }

@@ -105,6 +105,7 @@ static const void* rs_batch_kernel(int K, int bs)
 }
 
 struct cg_batch_resident {
+    RsRetry retry;
     int nsys = 0, K = 0, bs = 0, grid = 0;
     size_t lds = 0, nwords = 0;
     long long rows = 0;  // of all systems
@@ -347,6 +348,7 @@ cg_batch_resident* make_batch_resident(const RsBatchMatrix& m, int cus, hipStrea
 bool run_batch_resident(cg_batch_resident* r, int device, hipStream_t st, const double* b, double* x, double tol,
                         int maxit, long long limit, const RsOut*& out)
 {
+    if (!r->retry.now()) return false;
     RsBatchArgs a = r->args;
     a.common.b = b;
     a.common.x = x;
@@ -371,9 +373,10 @@ bool run_batch_resident(cg_batch_resident* r, int device, hipStream_t st, const 
     JPCG_HIP(hipLaunchKernel(rs_batch_kernel(r->K, r->bs), dim3(r->grid), dim3(r->bs), args, r->lds, st));
     JPCG_HIP(hipStreamSynchronize(st));
     out = r->out;
-    for (int s = 0; s < r->nsys; ++s)
-        if (out[s].stop == RS_ABORTED) return false;
-    return *a.run.given_up == 0;
+    bool ok = *a.run.given_up == 0;
+    for (int s = 0; s < r->nsys; ++s) ok = ok && out[s].stop != RS_ABORTED;
+    r->retry.done(ok);
+    return ok;
 }
 
 }  // namespace jpcg

@@ -49,7 +49,31 @@ std::mutex& resident_mutex(int device);
 
 }  // namespace jpcg
 
+namespace jpcg {
+
+// After a launch that was given up the next ones go to the general kernels at
+// once, as the wait was in vain and what kept the workgroups off the card (other
+// work, a mask of compute units) may last: one solve, then two, four and so on
+// to 64, until one succeeds.
+struct RsRetry {
+    int skip = 0, pause = 0;
+    bool now()
+    {
+        if (skip == 0) return true;
+        --skip;
+        return false;
+    }
+    void done(bool ok)
+    {
+        pause = ok ? 0 : pause == 0 ? 1 : pause < 64 ? 2 * pause : 64;
+        skip = pause;
+    }
+};
+
+}  // namespace jpcg
+
 struct cg_resident {
+    jpcg::RsRetry retry;
     int K = 0, bs = 0, G = 0, rpw = 0, halo = 0;
     size_t nwords = 0;
     unsigned short* lidx = nullptr;
@@ -71,7 +95,7 @@ cg_resident* make_resident(cg_ctx* c);
 void destroy_resident(cg_resident* r);
 
 // False if some workgroup gave up waiting, as when they could not all be on the
-// card in time; x is then put back to what it was.
+// card in time, or just after such a launch; x is then what it was.
 bool run_resident(cg_ctx* c, cg_resident* r, int form, const double* b, double* x, double tol, int maxit, double drop,
                   double* hist, RsOut& res);
 
@@ -92,7 +116,8 @@ cg_batch_resident* make_batch_resident(const RsBatchMatrix& m, int cus, hipStrea
 void destroy_batch_resident(cg_batch_resident* r);
 // Solves on the batch's own b and x (maxit <= 0: each system's rows) and fills
 // out[nsys].  limit: 8 s in device ticks, the most that a round takes.  False if
-// some workgroup gave up waiting: none of x counts then.
+// some workgroup gave up waiting, or just after such a launch: none of x counts
+// then.
 bool run_batch_resident(cg_batch_resident* r, int device, hipStream_t st, const double* b, double* x, double tol,
                         int maxit, long long limit, const RsOut*& out);
 

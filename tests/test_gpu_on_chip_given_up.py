@@ -190,3 +190,32 @@ def test_many_small_systems_take_little_memory(cuda):
     assert batch_solved_on_chip(bt) == 1 and all(i["status"] == 0 for i in infos)
     assert (x.view(500, 40) == x[:40]).all()
     assert oracle.relres(a, b[:40].cpu().numpy(), x[:40].cpu().numpy()) <= tol_recomputed(40)
+
+
+@pytest.mark.parametrize("batch", [False, True])
+def test_given_up_launches_are_not_tried_at_once_again(cuda, on_chip, batch):
+    # One solve without a try after the first launch that is given up, then two,
+    # and none once a launch succeeds.
+    from paper_1107_0538_amd import Batch, Solver
+
+    a = banded(4000, (1, 30), seed=7)
+    b = _t(np.random.default_rng(8).uniform(-1, 1, a.n), cuda)
+    s = Batch([a]) if batch else Solver(a)
+    there = batch_solved_on_chip if batch else solved_on_chip
+
+    def solve():
+        x, info = s.solve(b)
+        assert (info[0] if batch else info)["status"] == 0
+        assert oracle.relres(a, b.cpu().numpy(), x.cpu().numpy()) <= tol_recomputed(a.n)
+        return there(s)
+
+    assert [solve(), solve()] == [1, 1]
+    leaves = (-1, -1, 1)
+    on_chip(*leaves)
+    assert solve() == 0
+    on_chip(-1, -1, -1)
+    assert [solve(), solve(), solve()] == [0, 1, 1]
+    on_chip(*leaves)
+    assert [solve(), solve(), solve()] == [0, 0, 0]  # the third is a try
+    on_chip(-1, -1, -1)
+    assert [solve(), solve(), solve()] == [0, 0, 1]
