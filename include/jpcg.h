@@ -154,8 +154,9 @@ int cg_create(const cg_csr *A, const cg_opts *opts, void *hip_stream, cg_ctx **o
  * and the true residual b - A x confirms it (otherwise r is replaced by the
  * true residual and the loop continues).  maxit <= 0 means n.  ||b|| = 0
  * gives x = 0 and 0 iterations.  Every scalar stays on the device.  A system of
- * at most 262144 rows of at most 28 nonzeros, created without a launch shape in
- * its options, is solved by one kernel that holds the matrix in registers (such
+ * at most 262144 rows of at most 28 nonzeros, whose runs of rows (a run per
+ * compute unit) refer to few other rows (at most 768, 1728 or 2880 from runs of
+ * up to 256, 640 or 1024), created without a launch shape in its options, is solved by one kernel that holds the matrix in registers (such
  * solves on one device, and batched ones, wait for each other); otherwise
  * iterations run as kernels launched in hipGraph chunks, over a second copy of
  * the matrix in slices of 64 rows where its rows are of about equal length (at
@@ -282,8 +283,9 @@ int cg_solve_block(cg_ctx *ctx, const double *B, double *X, int32_t s, double to
  * solved by a team of workgroups sized in proportion to its expected work,
  * with cg_solve's algorithm and stopping rules; its rows are cut into
  * product tiles and each workgroup of the team owns an equal run of them.
- * Where every system has at most 262144 rows of at most 28 nonzeros and opts
- * gives no tile width and no blocks_per_cu, the solve holds the matrices in
+ * Where every system has at most 262144 rows of at most 28 nonzeros, runs of
+ * 512 rows (256 in small batches) refer to at most 1792 (768) other rows, and
+ * opts gives no tile width and no blocks_per_cu, the solve holds the matrices in
  * registers instead, system after system on teams that come free, in the same
  * algorithm; cg_batch_teams reports the teams of the general path either way.
  * opts->precond applies to every system; opts->nnz_per_lane picks the tile

@@ -47,7 +47,7 @@ struct RsBatchArgs {
 
 __device__ __forceinline__ int rs_scalar(int v) { return __builtin_amdgcn_readfirstlane(v); }
 
-template <int K, int BS>
+template <int K, int BS, int NH>
 __global__ __launch_bounds__(BS, BS == 512 ? 4 : 1) void k_rs_batch(RsBatchArgs a)
 {
     extern __shared__ double pl[];
@@ -88,25 +88,34 @@ __global__ __launch_bounds__(BS, BS == 512 ? 4 : 1) void k_rs_batch(RsBatchArgs 
         s.out = a.out + sys;
         RsRun run = a.run;
         if (run.maxit <= 0) run.maxit = s.n;
-        RsTeam<K, BS, rs_halo(BS), false> team(s, run, index, pl, sh.red, sh.tot, &sh.fail);
+        RsTeam<K, BS, NH, false> team(s, run, index, pl, sh.red, sh.tot, &sh.fail);
         if (!team.solve_standard()) return;
         __syncthreads();  // the next system reuses the LDS
     }
 }
 
-static const void* rs_batch_kernel(int K, int bs)
+// Halo columns per thread: of a block of 512 threads three, as far as that goes
+// (rows of a 27-point lattice up to 53^3: 1332 columns for 512 rows; 128 registers
+// are short, and a fourth entry makes 26 of them spill, not 20); 54^3 to 64^3 have
+// up to 1408.
+constexpr int kBatchHalo = 3, kBatchHaloMost = 4;
+static_assert(rs_halo(256) == kBatchHaloMost, "one capacity for either block");
+
+template <int K>
+static const void* rs_batch_kernel_of(int bs, int nh)
 {
-    if (K <= 16) {
-        if (bs == 256) return (const void*)k_rs_batch<16, 256>;
-        return (const void*)k_rs_batch<16, 512>;
-    }
-    if (bs == 256) return (const void*)k_rs_batch<28, 256>;
-    return (const void*)k_rs_batch<28, 512>;
+    if (bs == 256) return (const void*)k_rs_batch<K, 256, rs_halo(256)>;
+    if (nh == kBatchHalo) return (const void*)k_rs_batch<K, 512, kBatchHalo>;
+    return (const void*)k_rs_batch<K, 512, kBatchHaloMost>;
+}
+static const void* rs_batch_kernel(int K, int bs, int nh)
+{
+    return K <= 16 ? rs_batch_kernel_of<16>(bs, nh) : rs_batch_kernel_of<28>(bs, nh);
 }
 
 struct cg_batch_resident {
     RsRetry retry;
-    int nsys = 0, K = 0, bs = 0, grid = 0;
+    int nsys = 0, K = 0, bs = 0, nh = 0, grid = 0;
     size_t lds = 0, nwords = 0;
     long long rows = 0;  // of all systems
     RsBatchSys* sys = nullptr;
@@ -260,7 +269,7 @@ cg_batch_resident* make_batch_resident(const RsBatchMatrix& m, int cus, hipStrea
         r->K = maxrow <= 16 ? 16 : 28;
         r->bs = per_cu == 1 ? 256 : 512;
         r->grid = kRsXcds * slots;
-        const int hcap = rs_halo(r->bs) * (r->bs - kWave);
+        const int hcap = kBatchHaloMost * (r->bs - kWave);
         std::vector<RsIndexJob> index(slot);
         for (const RsBatchSys& t : sys)
             for (int g = 0; g < t.groups * t.members; ++g) {
@@ -309,13 +318,16 @@ cg_batch_resident* make_batch_resident(const RsBatchMatrix& m, int cus, hipStrea
         djobs = nullptr;
         dflag = nullptr;
         RsBatchArgs& a = r->args;
-        if (!flag) r->lds = rs_lds(RS_STANDARD, r->K, r->bs, rows_max,
-                                   *std::max_element(hcount.begin(), hcount.end()), a.common.lds_slots);
+        if (!flag) {
+            const int halo = *std::max_element(hcount.begin(), hcount.end());
+            r->nh = halo <= kBatchHalo * (r->bs - kWave) ? kBatchHalo : kBatchHaloMost;
+            r->lds = rs_lds(RS_STANDARD, r->K, r->bs, rows_max, halo, a.common.lds_slots);
+        }
         if (flag || r->lds > kRsMaxLds / per_cu) {
             destroy_batch_resident(r);
             return nullptr;
         }
-        JPCG_HIP(hipFuncSetAttribute(rs_batch_kernel(r->K, r->bs), hipFuncAttributeMaxDynamicSharedMemorySize,
+        JPCG_HIP(hipFuncSetAttribute(rs_batch_kernel(r->K, r->bs, r->nh), hipFuncAttributeMaxDynamicSharedMemorySize,
                                      (int)(kRsMaxLds / per_cu)));
         a.sys = r->sys;
         a.jobs = r->jobs;
@@ -370,7 +382,7 @@ bool run_batch_resident(cg_batch_resident* r, int device, hipStream_t st, const 
     *a.run.given_up = 0;
     launch_rs_clear(st, r->words, r->nwords, nullptr, nullptr, 0);
     void* args[] = {&a};
-    JPCG_HIP(hipLaunchKernel(rs_batch_kernel(r->K, r->bs), dim3(r->grid), dim3(r->bs), args, r->lds, st));
+    JPCG_HIP(hipLaunchKernel(rs_batch_kernel(r->K, r->bs, r->nh), dim3(r->grid), dim3(r->bs), args, r->lds, st));
     JPCG_HIP(hipStreamSynchronize(st));
     out = r->out;
     bool ok = *a.run.given_up == 0;

@@ -219,3 +219,21 @@ def test_given_up_launches_are_not_tried_at_once_again(cuda, on_chip, batch):
     assert [solve(), solve(), solve()] == [0, 0, 0]  # the third is a try
     on_chip(-1, -1, -1)
     assert [solve(), solve(), solve()] == [0, 0, 1]
+
+
+@pytest.mark.parametrize("edges", [(53, 20), (54, 20), (64, 20), (64, 54, 53, 64)])
+def test_batch_halo_of_large_lattices(cuda, edges):
+    # 512 rows of a 27-point lattice refer to 1332 others at 53^3, 1354 at 54^3
+    # and 1408 at 64^3: three, then four for a thread.
+    from paper_1107_0538_amd import Batch, Solver
+
+    probs = [W.problem(n, i) for i, n in enumerate(edges)]
+    bt = Batch([p[0] for p in probs])
+    x, infos = bt.solve(_t(np.concatenate([p[1] for p in probs]), cuda))
+    assert batch_solved_on_chip(bt) == 1
+    for s, (a, b) in enumerate(probs):
+        xs = x[bt.offsets[s]:bt.offsets[s + 1]]
+        xo, io = Solver(a).solve(_t(b, cuda))
+        assert infos[s]["status"] == io["status"] == 0 and abs(infos[s]["iters"] - io["iters"]) <= 2
+        assert oracle.relres(a, b, xs.cpu().numpy()) <= tol_recomputed(a.n)
+        assert float((xs - xo).norm() / xo.norm()) <= 1e-8
