@@ -394,11 +394,12 @@ __global__ __launch_bounds__(kGemmBS, 2) void k_bc_gemm(BcGemmArgs g, BcState* s
 // ---------------------------------------------------------------------------
 
 // Y = A X over N x 64 blocks (spmm.hpp).
-__global__ __launch_bounds__(kSpmmBS, 6) void k_bc_spmm(RunMap<double> m, const double* __restrict__ X,
+template <SpmmKind KIND>
+__global__ __launch_bounds__(kSpmmBS, spmm_waves(KIND)) void k_bc_spmm(RunMap<double> m, const double* __restrict__ X,
                                                      double* __restrict__ Y, int G, const BcState* st, int gate)
 {
     if (bc_stopped(st, gate)) return;
-    spmm_block(m, X, Y, kB, G);
+    spmm_block<KIND>(m, X, Y, kB, G);
 }
 
 // R = B - AX (AX given), per-workgroup partials of r'r and b'b
@@ -879,7 +880,7 @@ struct BcOps {
     {
         RunMap<double> m = run_map(c);
         void* a[] = {&m, &X, &Y, &b->spmm_G, &b->st, &gate};
-        launch((const void*)k_bc_spmm, b->spmm_G, kSpmmBS, st, a);
+        launch(c->streams ? (const void*)k_bc_spmm<SPMM_FOURS_STREAMS> : (const void*)k_bc_spmm<SPMM_FOURS>, b->spmm_G, kSpmmBS, st, a);
     }
     // With `norms` the column norms of the last BC_RUP too.
     void sum_grams(int nop, int G, int gate, bool norms = false)

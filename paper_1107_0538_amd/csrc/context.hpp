@@ -29,7 +29,9 @@ struct cg_ctx {
     float* dinv32 = nullptr;  // fp32_copy
     float* rowsum32 = nullptr;  // fp32_copy: row sums of A (FP64 sums, FP32 storage)
     double* rowsum64 = nullptr; // fp32_copy: the same row sums in FP64 (FP32-matrix form)
-    int* runs = nullptr;      // which fours of rows the row-block products take together (spmm.hpp)
+    int* runs = nullptr;      // how the row-block products take each four of rows (spmm.hpp)
+    bool streams = false;     // some of them as a stream
+    bool mostly_runs = false; // most of them as runs
     std::vector<int> h_rowptr;
 
     // Work vectors for single-RHS solves (one allocation, each vector at a
@@ -87,8 +89,10 @@ void partition_rows(const std::vector<int>& rowptr, int G, std::vector<int>& out
 
 int set_error(cg_ctx* c, int code, const std::string& msg);
 
-// Find c->runs, on the context's stream (multi.hip).
-void make_runs(cg_ctx* c);
+// Find c->runs, on the context's stream, adding to found[0 .. 2] (device) what
+// use_runs is to know (multi.hip).
+void make_runs(cg_ctx* c, int* found);
+void use_runs(cg_ctx* c, const int* found);
 
 // Free the multi-RHS solver state of a context (multi.hip).
 void free_multi(cg_ctx* c);

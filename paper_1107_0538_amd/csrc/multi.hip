@@ -185,7 +185,7 @@ __device__ __forceinline__ bool mr_any_active(const MrState* st)
 // Residual R = B - A X and partials (r'r, r'z, b'b) per column.  mode 0: setup
 // (every column), 1: check (only pending columns are rewritten), 2: report
 // (nothing is written but the partials).
-template <typename T>
+template <SpmmKind KIND, typename T>
 __global__ __launch_bounds__(kMrBS) void k_mr_residual(MrArgs<T> a, int mode)
 {
     const SpmmLane l(a.s);
@@ -199,7 +199,7 @@ __global__ __launch_bounds__(kMrBS) void k_mr_residual(MrArgs<T> a, int mode)
         v[1][u] += (double)ri * (double)zi;
         v[2][u] += (double)bi * (double)bi;
     };
-    spmm_rows<false, T>(
+    spmm_rows<false, KIND, T>(
         a.m, a.X, l, a.G, [&](int i) { return l.load(a.B, i); },
         [&](int i, T y1, T y2, Pair<T> b) {
             take(i + l.half, 0, w1, b.x, y1);
@@ -281,13 +281,13 @@ __global__ __launch_bounds__(kMrBS) void k_mr_flush(MrArgs<T> a)
 static __global__ void k_mr_flushed(MrState* st) { st->pend[threadIdx.x] = 0; }
 
 // q = A p; partials of p'q.
-template <typename T>
-__global__ __launch_bounds__(kMrBS, 5) void k_mr_product(MrArgs<T> a)
+template <SpmmKind KIND, typename T>
+__global__ __launch_bounds__(kMrBS, KIND == SPMM_SINGLE ? spmm_waves(KIND) : 5) void k_mr_product(MrArgs<T> a)
 {
     if (!mr_any_active(a.st)) return;
     const SpmmLane l(a.s);
     double v[1][2] = {};
-    spmm_rows<sizeof(T) == 4, T>(
+    spmm_rows<sizeof(T) == 4, KIND, T>(
         a.m, a.P, l, a.G, [&](int i) { return l.load(a.P, i); },
         [&](int i, T q1, T q2, Pair<T> p) {
             l.store(a.Q, i, q1, q2);
@@ -508,6 +508,7 @@ struct cg_multi {
     double* part = nullptr;
     jpcg::MrState* st = nullptr;
     jpcg::MrState* hst = nullptr;
+    const void *product = nullptr, *residual = nullptr;
     hipGraphExec_t exec = nullptr;
     hipEvent_t ev = nullptr;
     jpcg::MrArgs<double> args{};
@@ -540,9 +541,10 @@ MrArgs<double>& margs<double>(cg_multi* m) { return m->args; }
 template <>
 MrArgs<float>& margs<float>(cg_multi* m) { return m->args32; }
 
-// The words of spmm.hpp's fours of rows.
+// The words of spmm.hpp's fours of rows; found: how many are to be streams, how
+// many of those hold a row longer than half a wave, and how many are runs.
 static __global__ __launch_bounds__(256) void k_find_runs(int n, const int* __restrict__ rowptr,
-                                                          const int* __restrict__ col, int* __restrict__ runs)
+                                                          const int* __restrict__ col, int* __restrict__ runs, int* found)
 {
     const int g = blockIdx.x * 256 + threadIdx.x, i0 = g * kRunRows;
     if (i0 >= n) return;
@@ -555,24 +557,61 @@ static __global__ __launch_bounds__(256) void k_find_runs(int n, const int* __re
         const int c = col[k0 + e / 3 * 3] + e % 3;
         for (int r = 0; ok && r < kRunRows; ++r) ok = col[k0 + r * len + e] == c + r;
     }
-    runs[g] = ok && len ? len : most <= kSpmmShort ? SPMM_SHORT : SPMM_LONG;
+    const int own = rowptr[i0 + rows] - k0;
+    const bool stream = most > kSpmmShort || rows * most > kSpmmPadding * own + 8;
+    runs[g] = ok && len ? len : stream ? SPMM_STREAM : SPMM_EVEN;
+    const int uneven = __popcll(__ballot(runs[g] < 0)), longer = __popcll(__ballot(most > kSpmmShort));
+    const int whole = __popcll(__ballot(runs[g] > 0));
+    if ((threadIdx.x & (kWave - 1)) == 0) {
+        if (uneven) atomicAdd(&found[0], uneven);
+        if (longer) atomicAdd(&found[1], longer);
+        if (whole) atomicAdd(&found[2], whole);
+    }
 }
 
-void make_runs(cg_ctx* c)
+void make_runs(cg_ctx* c, int* found)
 {
     const int fours = (c->n + kRunRows - 1) / kRunRows;
     JPCG_HIP(hipMalloc(&c->runs, sizeof(int) * fours));
-    k_find_runs<<<(fours + 255) / 256, 256, 0, c->stream>>>(c->n, c->rowptr, c->col, c->runs);
+    k_find_runs<<<(fours + 255) / 256, 256, 0, c->stream>>>(c->n, c->rowptr, c->col, c->runs, found);
     JPCG_HIP(hipGetLastError());
+}
+
+// A few fours of unequal rows, as at the ends of a lattice's lines, may well be
+// taken side by side: the kernels without streams have the registers for one more
+// wave per SIMD (51^3, 64 columns: 72 us a product, 77 with streams).
+void use_runs(cg_ctx* c, const int* found)
+{
+    const int fours = (c->n + kRunRows - 1) / kRunRows;
+    c->streams = found[1] > 0 || 32LL * found[0] > fours;
+    c->mostly_runs = 2LL * found[2] > fours;
 }
 
 RunMap<double> run_map(const cg_ctx* c) { return {c->n, c->runs, c->rowptr, c->col, c->val, nullptr}; }
 
 // Y = A X (row-major N x s).
-__global__ __launch_bounds__(kSpmmBS, 6) void k_spmm(RunMap<double> m, const double* __restrict__ X,
+template <SpmmKind KIND>
+__global__ __launch_bounds__(kSpmmBS, spmm_waves(KIND)) void k_spmm(RunMap<double> m, const double* __restrict__ X,
                                                   double* __restrict__ Y, int s, int G)
 {
-    spmm_block(m, X, Y, s, G);
+    spmm_block<KIND>(m, X, Y, s, G);
+}
+
+// A row per wave serves small matrices, whose fours of rows would leave most of the
+// card idle, as long as a wave has few rows: up to 16^3 of a lattice, whose fours
+// need half the gathers (64 columns, 10^3, 16^3, 20^3: 4.2, 6.5, 10.5 us against 13.9,
+// 8.2, 10.6), and up to 24^3 of other rows (in random order 19 us and 21, 107 entries
+// a row 61 and 63; a mesh of 20000 nodes 23 and 20), as
+// to one column, for which runs save nothing (20^3 11 and 13).
+static bool spmm_single(const cg_ctx* c, int s) { return c->n <= (c->mostly_runs && s > 1 ? 6144 : 16384); }
+
+static void launch_spmm(cg_ctx* c, const double* X, double* Y, int s, int wpc)
+{
+    const bool single = spmm_single(c, s);
+    const int G = single ? spmm_grid(c, 8, 1) : spmm_grid(c, wpc);
+    const auto kernel = single ? k_spmm<SPMM_SINGLE> : c->streams ? k_spmm<SPMM_FOURS_STREAMS> : k_spmm<SPMM_FOURS>;
+    kernel<<<G, kSpmmBS, 0, c->stream>>>(run_map(c), X, Y, s, G);
+    JPCG_HIP(hipGetLastError());
 }
 
 // The multi-column product's grid: workgroups per CU.  Without autotune the
@@ -599,13 +638,11 @@ int spmm_blocks_per_cu(cg_ctx* c)
         JPCG_HIP(hipEventCreate(&e0));
         JPCG_HIP(hipEventCreate(&e1));
         for (int w : {1, 2, 3, 4, 6, 8}) {
-            const int G = spmm_grid(c, w);
-            k_spmm<<<G, kSpmmBS, 0, c->stream>>>(run_map(c), X, Y, s, G);
+            launch_spmm(c, X, Y, s, w);
             JPCG_HIP(hipEventRecord(e0, c->stream));
             constexpr int kReps = 8;
             for (int r = 0; r < kReps; ++r)
-                k_spmm<<<G, kSpmmBS, 0, c->stream>>>(run_map(c), X, Y, s, G);
-            JPCG_HIP(hipGetLastError());
+                launch_spmm(c, X, Y, s, w);
             JPCG_HIP(hipEventRecord(e1, c->stream));
             JPCG_HIP(hipEventSynchronize(e1));
             float ms = 0.f;
@@ -639,19 +676,35 @@ constexpr int kMrVectorWpc = 4;
 // 169 us per iteration against 139, 149, 168 and 205 through the cache.
 constexpr double kMrStreamBytes = 300e6;
 
+template <SpmmKind KIND, typename T>
+static void set_products(cg_multi* m)
+{
+    m->product = (const void*)k_mr_product<KIND, T>;
+    m->residual = (const void*)k_mr_residual<KIND, T>;
+}
+
 template <typename T>
 static cg_multi* make_multi(cg_ctx* c, int s)
 {
-    const int wpc = spmm_blocks_per_cu(c);
+    int wpc = spmm_blocks_per_cu(c), rows = kRunRows;
     cg_multi* m = new cg_multi();
     try {
         m->s = s;
         m->fp32 = sizeof(T) == 4;
         m->chunk = 8;
+        set_products<SPMM_FOURS, T>(m);
+        if (c->streams) set_products<SPMM_FOURS_STREAMS, T>(m);
+        if constexpr (sizeof(T) == 4) {
+            if (!c->mostly_runs) {
+                set_products<SPMM_SINGLE, T>(m);
+                wpc = spmm_waves(SPMM_SINGLE);
+                rows = 1;
+            }
+        }
         const size_t ns = (size_t)c->n * s;
         m->stream = sizeof(T) * 5.0 * (double)ns + (sizeof(T) + 4.0) * (double)c->nnz > kMrStreamBytes;
         MrArgs<T>& a = margs<T>(m);
-        a.G = spmm_grid(c, wpc);
+        a.G = spmm_grid(c, wpc, rows);
         a.Gv = std::max(8, std::min(c->cus * kMrVectorWpc, (c->n + 63) / 64) / 8 * 8);
         a.rows = (c->n + a.Gv - 1) / a.Gv;
         JPCG_HIP(hipMalloc(&m->work, sizeof(T) * ns * 5));
@@ -712,7 +765,7 @@ static void capture_multi(cg_multi* m)
         int ph_sig = MR_SIGMA, ph_it = MR_ITER;
         void* a0[] = {&args};
         mr_launch(direction, args.Gv, kMrBS, cap, a0);
-        mr_launch((const void*)k_mr_product<T>, args.G, kMrBS, cap, a0);
+        mr_launch(m->product, args.G, kMrBS, cap, a0);
         void* a1[] = {&args, &ph_sig};
         mr_launch((const void*)k_mr_scalars<T>, kCols, 256, cap, a1);
         mr_launch(update, args.Gv, kMrBS, cap, a0);
@@ -773,7 +826,7 @@ static MrState run_multi(cg_ctx* c, cg_multi* m)
     const int s = m->s;
     int mode = 0, ph = MR_SETUP;
     void* ra[] = {&args, &mode};
-    mr_launch((const void*)k_mr_residual<T>, args.G, kMrBS, st, ra);
+    mr_launch(m->residual, args.G, kMrBS, st, ra);
     void* sa[] = {&args, &ph};
     mr_launch((const void*)k_mr_scalars<T>, kCols, 256, st, sa);
     void* za[] = {&args};
@@ -798,7 +851,7 @@ static MrState run_multi(cg_ctx* c, cg_multi* m)
             if (!pending) break;
             mode = 1;
             ph = MR_CHECK;
-            mr_launch((const void*)k_mr_residual<T>, args.G, kMrBS, st, ra);
+            mr_launch(m->residual, args.G, kMrBS, st, ra);
             mr_launch((const void*)k_mr_scalars<T>, kCols, 256, st, sa);
             continue;
         }
@@ -811,7 +864,7 @@ static MrState run_multi(cg_ctx* c, cg_multi* m)
     if (args.confirm) {
         mode = 2;
         ph = MR_REPORT;
-        mr_launch((const void*)k_mr_residual<T>, args.G, kMrBS, st, ra);
+        mr_launch(m->residual, args.G, kMrBS, st, ra);
         mr_launch((const void*)k_mr_scalars<T>, kCols, 256, st, sa);
     }
     return mr_read(c, m);
@@ -835,9 +888,7 @@ int spmm(cg_ctx* c, const double* X, double* Y, int32_t s)
     if (!c) return CG_EINVAL;
     if (!X || !Y || X == Y || s < 1 || s > kCols) return set_error(c, CG_EINVAL, "spmm: bad arguments");
     try {
-        const int G = spmm_grid(c, spmm_blocks_per_cu(c));
-        k_spmm<<<G, kSpmmBS, 0, c->stream>>>(run_map(c), X, Y, s, G);
-        JPCG_HIP(hipGetLastError());
+        launch_spmm(c, X, Y, s, spmm_blocks_per_cu(c));
         return 0;
     } catch (const HipError& e) {
         return set_error(c, CG_EHIP, std::string("spmm: ") + e.what + ": " + hipGetErrorString(e.code));
@@ -916,7 +967,7 @@ int cg_solve_multi_mixed(cg_ctx* c, const double* B, double* X, int32_t s, doubl
             // r = b - A x in FP64 and the per-column tests.
             int mode = 0, ph = MR_SETUP;
             void* ra[] = {&m64->args, &mode};
-            mr_launch((const void*)k_mr_residual<double>, m64->args.G, kMrBS, st, ra);
+            mr_launch(m64->residual, m64->args.G, kMrBS, st, ra);
             void* sa[] = {&m64->args, &ph};
             mr_launch((const void*)k_mr_scalars<double>, kCols, 256, st, sa);
             if (outer == 0) {  // x_j = 0 for b_j = 0

@@ -1281,19 +1281,20 @@ int cg_create(const cg_csr* A, const cg_opts* opts, void* hip_stream, cg_ctx** o
             rowsum_kernel<<<(n + 255) / 256, 256, 0, c->stream>>>(n, c->rowptr, c->val, c->rowsum32, c->rowsum64);
             JPCG_HIP(hipGetLastError());
         }
-        make_runs(c);
-        int* bad = nullptr;
-        JPCG_HIP(hipMalloc(&bad, sizeof(int)));
-        JPCG_HIP(hipMemsetAsync(bad, 0, sizeof(int), c->stream));
+        int* found = nullptr;  // a bad diagonal; three counts for the multi-column products
+        JPCG_HIP(hipMalloc(&found, 4 * sizeof(int)));
+        JPCG_HIP(hipMemsetAsync(found, 0, 4 * sizeof(int), c->stream));
+        make_runs(c, found + 1);
         jacobi_kernel<<<(n + 255) / 256, 256, 0, c->stream>>>(n, c->rowptr, c->col, c->val,
                                                               c->opts.precond == CG_PRECOND_JACOBI, c->dinv,
-                                                              c->dinv32, bad);
+                                                              c->dinv32, found);
         JPCG_HIP(hipGetLastError());
-        int hbad = 0;
-        JPCG_HIP(hipMemcpyAsync(&hbad, bad, sizeof(int), hipMemcpyDeviceToHost, c->stream));
+        int hfound[4] = {};
+        JPCG_HIP(hipMemcpyAsync(hfound, found, 4 * sizeof(int), hipMemcpyDeviceToHost, c->stream));
         JPCG_HIP(hipStreamSynchronize(c->stream));
-        JPCG_HIP(hipFree(bad));
-        if (hbad) {
+        JPCG_HIP(hipFree(found));
+        use_runs(c, hfound + 1);
+        if (hfound[0]) {
             free_ctx(c);
             return CG_EDIAG;
         }
