@@ -555,18 +555,29 @@ const bf16* weights<bf16>(mlp_net* n, int l) { return n->pb + n->woff[l]; }
 // Fixed chunks of the batch that the weight gradients are summed in.
 static int batch_splits(int Bn) { return std::max(1, std::min(16, Bn / 128)); }
 
+static int64_t tiles_of(int a, int b) { return (int64_t)((a + GT - 1) / GT) * ((b + GT - 1) / GT); }
+
 // The small-network kernels serve networks and batches no layer of which fills
 // the chip with 64 x 64 tiles: up to 256 of them per product.  24-256-256-64 in
 // BF16, a step with batches of 32, 256 and 4096: 35, 45 and 343 us against 207,
-// 410 and 2831, a forward pass 19, 18 and 85 against 90, 95 and 104; hidden
-// layers of 1024 with 1024 (256 tiles): 674 and 223 us against 1198 and 327; with
-// 2048 (512 tiles) about equal.
+// 410 and 2831; hidden layers of 1024 with 1024 (256 tiles): 674 us against 1198;
+// with 2048 (512 tiles) about equal.
 static bool small_net(const mlp_net* n, int Bn)
 {
-    auto tiles = [](int a, int b) { return (int64_t)((a + GT - 1) / GT) * ((b + GT - 1) / GT); };
     for (int l = 0; l < n->L; ++l)
-        if (tiles(Bn, n->dims[l + 1]) > kSmallTiles || tiles(n->dims[l], n->dims[l + 1]) > kSmallTiles) return false;
+        if (tiles_of(Bn, n->dims[l + 1]) > kSmallTiles || tiles_of(n->dims[l], n->dims[l + 1]) > kSmallTiles) return false;
     return true;
+}
+
+// A forward pass by itself: a layer of K inputs and t tiles takes 5 + 0.02 t + 0.15 K
+// us in large tiles and 4.5 + 0.02 t + 0.00068 t K here (K = 64 to 1024, t = 64 to
+// 256; 256 tiles of 64, 256 and 1024 inputs: 20, 48, 160 us and 21, 49, 184), so
+// layers of over 220 tiles are better off in large ones.
+static bool small_pass(const mlp_net* n, int Bn)
+{
+    double more = -735.0 * n->L;  // 0.00068 t K - 0.15 K - 0.5, in units of 0.00068 us
+    for (int l = 0; l < n->L; ++l) more += n->dims[l] * (tiles_of(Bn, n->dims[l + 1]) - 220.0);
+    return more <= 0.0 && small_net(n, Bn);
 }
 
 // The forward pass of a small network; with targets also the last layer's
@@ -651,7 +662,7 @@ template <typename TW>
 static void forward_t(mlp_net* n, const float* X, int Bn, float* Y)
 {
     hipStream_t st = n->stream;
-    if (Y && small_net(n, Bn)) {
+    if (Y && small_pass(n, Bn)) {
         // A single layer reads X while it writes its output, which may be X.
         small_forward<TW>(n, X, Bn, n->L > 1 ? Y : nullptr, nullptr);
         if (n->L > 1) return;
