@@ -387,9 +387,9 @@ static cg_graphs* make_graphs(cg_ctx* c, int form, bool fp32, int npl, int bs, i
 // The standard form over the context's slices; mat32 and drop as above.  The
 // product's partial sums are reduced by every workgroup of the update and its
 // sums by every workgroup of the next direction, so the grids are no larger
-// than they need be: at 128^3 2048 workgroups for the product take 146.6 us
-// per iteration, 1024 149, 8192 150; 1024 for the vectors 146.6, 256 157.
-constexpr int kEllMaxGrid = 2048, kEllUpdateGrid = 1024;
+// than they need be: at 128^3 1024 workgroups for the vectors 146.6 us per
+// iteration, 256 157; 8192 for the product 150.
+constexpr int kEllMaxGrid = 4096, kEllUpdateGrid = 1024;
 
 // Rows per workgroup of the elementwise kernels, whole passes of its threads,
 // and their grid: 65^3 14.51 ms a solve against 14.66 with the rows spread evenly
@@ -399,6 +399,19 @@ static void ell_rows(int n, int grid, int& R, int& G)
 {
     R = ((n + grid - 1) / grid + kEllBS - 1) / kEllBS * kEllBS;
     G = ((n + R - 1) / R + 7) / 8 * 8;
+}
+
+// Workgroups of the product kernels for S slices: whole passes of a slice per wave,
+// one while that takes fewer than kEllMaxGrid, else a power of two of them.  (At
+// 84^3 a fifth slice for the four waves of 2048 workgroups took 48 us an iteration
+// against 43 in one pass, 45 in two; 88^3 54, 47, 51; 104^3 79 against 75 in two; at
+// 128^3 2048 in four passes 141 us, 2736 in three 146, 1024 149.)
+static int ell_grid(int S)
+{
+    auto grid = [&](int passes) { return (S + passes * kEllWaves - 1) / (passes * kEllWaves); };
+    int passes = 1;
+    while (grid(passes) >= kEllMaxGrid) passes *= 2;
+    return (grid(passes) + 7) / 8 * 8;
 }
 
 static cg_graphs* make_ell_graphs(cg_ctx* c, int chunk, bool mat32, double drop)
@@ -413,7 +426,7 @@ static cg_graphs* make_ell_graphs(cg_ctx* c, int chunk, bool mat32, double drop)
         EllArgs& a = g->eargs;
         a.m = c->ell->map;
         a.keep = mat32 ? c->ell->keep32 : c->ell->keep;
-        a.G = std::min(kEllMaxGrid, ((a.m.S + kEllWaves - 1) / kEllWaves + 7) / 8 * 8);
+        a.G = ell_grid(a.m.S);
         ell_rows(c->n, kEllUpdateGrid, a.R, a.Gu);
         JPCG_HIP(hipMalloc(&g->part, sizeof(double) * (6 * (size_t)a.G + 2 * (size_t)a.Gu)));
         JPCG_HIP(hipMalloc(&g->st, g->st_bytes));
@@ -448,7 +461,7 @@ static cg_graphs* make_ell_graphs(cg_ctx* c, int chunk, bool mat32, double drop)
 }
 
 // The single-reduction form over the context's slices.  Every workgroup of the
-// update reduces both kernels' partials, so the grids are half of the above.
+// update reduces both kernels' partials, so there are half as many of it.
 static cg_graphs* make_ell_sr_graphs(cg_ctx* c, int chunk)
 {
     cg_graphs* g = new cg_graphs();
@@ -461,7 +474,7 @@ static cg_graphs* make_ell_sr_graphs(cg_ctx* c, int chunk)
         EllSrArgs& a = g->esargs;
         a.m = c->ell->map;
         a.keep = c->ell->keep;
-        a.G = std::min(kEllMaxGrid / 2, ((a.m.S + kEllWaves - 1) / kEllWaves + 7) / 8 * 8);
+        a.G = ell_grid(a.m.S);
         ell_rows(c->n, kEllUpdateGrid / 2, a.R, a.Gu);
         JPCG_HIP(hipMalloc(&g->part, sizeof(double) * (4 * (size_t)a.G + 8 * (size_t)a.Gu)));
         JPCG_HIP(hipMalloc(&g->st, g->st_bytes));
