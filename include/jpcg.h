@@ -76,7 +76,8 @@ typedef struct {
     int32_t fp32_copy;     /* 1: also keep an FP32 copy of the values (mixed form)       */
     int32_t autotune;      /* 1: time launch shapes at create and keep the fastest       */
                            /* (cg_create: reused for later matrices of the same size    */
-                           /* and row profile; cg_batch_create: the tile width)         */
+                           /* and row profile; cg_batch_create: the tile width), or the */
+                           /* on-chip solver or slices where those are faster still     */
     int32_t nnz_per_lane;  /* 4, 8 or 16: a product tile holds 64x that; 0 = 16       */
     int32_t blocks_per_cu; /* 0 = default; workgroups per compute unit of the grid      */
     int32_t history;       /* 1: record ||r_k|| / ||b|| for every iteration            */
@@ -101,11 +102,16 @@ typedef struct {
     double seconds;       /* device time of the solve, HIP events around the kernels */
 } cg_info;
 
-/* The launch shape a context uses (after autotuning, if requested). */
+/* The kernels that a context's solves and products run through: the launch shape
+ * below is that of the tile kernels, which also serve cg_solve_mixed and, where
+ * another solver gives up, cg_solve. */
+enum { CG_KERNELS_TILES = 0, CG_KERNELS_SLICES = 1, CG_KERNELS_ON_CHIP = 2 };
+
+/* The launch shape of a context (after autotuning, if requested). */
 typedef struct {
     int32_t nnz_per_lane;  /* a product tile holds up to 64 * nnz_per_lane nonzeros */
     int32_t block_size;
-    int32_t grid;          /* workgroups of every solver kernel                   */
+    int32_t grid;          /* workgroups of every tile kernel of the solver       */
     int32_t tiles;         /* product tiles (runs of whole rows) of the matrix    */
     int32_t chunk;         /* iterations per hipGraph chunk                       */
     int32_t form;          /* CG_FORM_STANDARD or CG_FORM_SINGLE_REDUCTION        */
@@ -117,12 +123,14 @@ typedef struct {
     int32_t spmv_block_size;   /* solver's shape if opts gave one, else tile width */
     int32_t spmv_grid;         /* 8, block 512, two workgroups per CU (autotuned   */
                                /* separately when opts->autotune is set)           */
-    double spmv_us;        /* autotuner's best spmv time, 0 if not tuned          */
-    double iter_us;        /* autotuner's best solver time per iteration, or 0    */
+    double spmv_us;        /* autotuner's spmv time by the kernels used, or 0     */
+    double iter_us;        /* its solver time per iteration by these, or 0        */
     int32_t spmm_blocks_per_cu; /* workgroups per CU of the multi-column product   */
                                 /* (spmm, cg_solve_multi, cg_solve_block): 0 until  */
                                 /* first used; timed at first use with autotune     */
-    int32_t spmm_pad;
+    int32_t kernels;       /* CG_KERNELS_* of the last cg_solve or                 */
+                           /* cg_solve_mixed_matrix (before it: of the first one), */
+                           /* plus 256 times that of spmv                          */
     double spmm_us;        /* autotuner's best 64-column product time, or 0       */
 } cg_config;
 

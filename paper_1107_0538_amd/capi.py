@@ -20,6 +20,7 @@ GRAM_SCRATCH_DOUBLES, GRAM_CHUNK = 4 << 20, 2048
 CG_MEM_HOST, CG_MEM_DEVICE = 0, 1
 CG_PRECOND_DEFAULT, CG_PRECOND_JACOBI, CG_PRECOND_NONE = 0, 1, 2
 CG_FORM_STANDARD, CG_FORM_SINGLE_REDUCTION = 0, 1
+CG_KERNELS_TILES, CG_KERNELS_SLICES, CG_KERNELS_ON_CHIP = 0, 1, 2
 FORMS = {"standard": CG_FORM_STANDARD, "single": CG_FORM_SINGLE_REDUCTION}
 
 _P = ctypes.c_void_p
@@ -52,7 +53,7 @@ class cg_config(ctypes.Structure):
                 ("tune_cached", ctypes.c_int32), ("col_bits", ctypes.c_int32),
                 ("spmv_nnz_per_lane", ctypes.c_int32), ("spmv_block_size", ctypes.c_int32),
                 ("spmv_grid", ctypes.c_int32), ("spmv_us", ctypes.c_double), ("iter_us", ctypes.c_double),
-                ("spmm_blocks_per_cu", ctypes.c_int32), ("spmm_pad", ctypes.c_int32), ("spmm_us", ctypes.c_double)]
+                ("spmm_blocks_per_cu", ctypes.c_int32), ("kernels", ctypes.c_int32), ("spmm_us", ctypes.c_double)]
 
     def as_dict(self):
         return {k: getattr(self, k) for k, _ in self._fields_}

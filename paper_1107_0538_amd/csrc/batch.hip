@@ -141,7 +141,7 @@ struct cg_batch {
     long long limit = 0;
     jpcg::cg_batch_resident* resident = nullptr;  // the systems on chip, where all of them fit
     int solved_on_chip = -1;  // the last solve's result came from there
-    bool general = false;  // solve by streaming the matrices all the same (while timing tile widths)
+    bool general = false;  // solve by streaming the matrices all the same (autotuning: while timing, or as the faster)
     std::string err;
 };
 
@@ -221,21 +221,12 @@ static int create_batch(int32_t nsys, const cg_csr* systems, const cg_opts* opts
     if (o.col_bits != 0 && o.col_bits != 32) return CG_EINVAL;
     if (o.autotune) {
         // Build the batch at each tile width, time 20 iterations of every
-        // system (tol 0, b = 1) and keep the fastest.
+        // system (tol 0, b = 1) and keep the fastest; on chip, if that is faster
+        // still.
         cg_batch* best = nullptr;
         double best_s = 1e300;
         int last_rc = CG_EINVAL;
-        for (int npl : {4, 8, 16}) {
-            cg_opts o2 = o;
-            o2.autotune = 0;
-            o2.nnz_per_lane = npl;
-            cg_batch* cand = nullptr;
-            last_rc = create_batch(nsys, systems, &o2, hip_stream, &cand, on_chip);
-            if (last_rc != 0) {
-                if (last_rc == CG_EINVAL || last_rc == CG_EDIAG) return last_rc;  // input errors
-                continue;
-            }
-            cand->general = true;  // it is the tile width that is timed
+        auto time = [&](cg_batch* cand) {
             double t = 1e300;
             double *bv = nullptr, *xv = nullptr;
             std::vector<cg_info> info(nsys);
@@ -252,7 +243,20 @@ static int create_batch(int32_t nsys, const cg_csr* systems, const cg_opts* opts
             }
             if (bv) (void)hipFree(bv);
             if (xv) (void)hipFree(xv);
-            cand->general = false;
+            return t;
+        };
+        for (int npl : {4, 8, 16}) {
+            cg_opts o2 = o;
+            o2.autotune = 0;
+            o2.nnz_per_lane = npl;
+            cg_batch* cand = nullptr;
+            last_rc = create_batch(nsys, systems, &o2, hip_stream, &cand, on_chip);
+            if (last_rc != 0) {
+                if (last_rc == CG_EINVAL || last_rc == CG_EDIAG) return last_rc;  // input errors
+                continue;
+            }
+            cand->general = true;
+            const double t = time(cand);
             if (t < best_s) {
                 cg_batch_destroy(best);
                 best = cand;
@@ -262,6 +266,10 @@ static int create_batch(int32_t nsys, const cg_csr* systems, const cg_opts* opts
             }
         }
         if (!best) return last_rc != 0 ? last_rc : CG_EHIP;
+        if (best->resident) {
+            best->general = false;
+            best->general = !(time(best) <= best_s && best->solved_on_chip);
+        }
         *out = best;
         return 0;
     }

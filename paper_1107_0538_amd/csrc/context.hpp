@@ -51,10 +51,11 @@ struct cg_ctx {
     void* mixed_dev = nullptr;
     void* mixed_host = nullptr;
     struct cg_ell* ell = nullptr;            // the matrix in slices, where its rows suit them
+    bool ell_solves = true, ell_spmv = true; // solves, spmv run over them (autotuning: if that is the fastest)
     struct cg_graphs* graphs_ell = nullptr;  // standard form over slices
     struct cg_graphs* graphs_ell32 = nullptr;  // the same streaming FP32 values
     struct cg_resident* resident = nullptr;  // the on-chip solver, where the system fits it
-    int solved_on_chip = -1;                 // the last solve's result came from it
+    int solved = -1;                         // CG_KERNELS_* that the last solve ran through
     struct cg_spmv_plan* spmv = nullptr;     // the standalone product's tiling and grid
     struct cg_multi* multi = nullptr;        // multi-RHS solver for one block width
     struct cg_multi* multi32 = nullptr;      // FP32 multi-RHS inner solver (mixed form)

@@ -609,9 +609,11 @@ static cg_spmv_plan* make_spmv_plan(cg_ctx* c, int npl, int bs, int G)
 // call against 5.5 by tiles, 36^3 6.4 against 7.0, 46^3 7.1 against 8.1).
 constexpr int kEllSpmvRows = 40000;
 
+static bool spmv_over_slices(const cg_ctx* c) { return c->ell && c->ell_spmv && c->n >= kEllSpmvRows; }
+
 static void launch_spmv(cg_ctx* c, const double* x, double* y)
 {
-    if (c->ell && c->n >= kEllSpmvRows) {
+    if (spmv_over_slices(c)) {
         launch_ell_spmv(c->ell, c->stream, x, y);
         return;
     }
@@ -920,8 +922,8 @@ static SolveResult run_any(cg_ctx* c, int form, const double* b, double* x, doub
                            double* hist, Graphs graphs)
 {
     RsOut o;
-    c->solved_on_chip = c->resident && run_resident(c, c->resident, form, b, x, tol, maxit, drop, hist, o);
-    if (c->solved_on_chip) {
+    if (c->resident && run_resident(c, c->resident, form, b, x, tol, maxit, drop, hist, o)) {
+        c->solved = CG_KERNELS_ON_CHIP;
         SolveResult r;
         r.stop = o.stop;
         r.iters = o.iters;
@@ -931,7 +933,18 @@ static SolveResult run_any(cg_ctx* c, int form, const double* b, double* x, doub
         r.rr_true = o.rr_true;
         return r;
     }
-    return run_solve(c, graphs(), b, x, tol, maxit, hist);
+    cg_graphs* g = graphs();
+    c->solved = g->ell ? CG_KERNELS_SLICES : CG_KERNELS_TILES;
+    return run_solve(c, g, b, x, tol, maxit, hist);
+}
+
+// The FP64 solve's graphs: over slices, or the tile kernels'.
+static cg_graphs* solve_graphs(cg_ctx* c)
+{
+    if (!c->ell || !c->ell_solves) return c->graphs;
+    if (!c->graphs_ell)
+        c->graphs_ell = c->form == CG_FORM_STANDARD ? make_ell_graphs(c, c->chunk, false, 0.0) : make_ell_sr_graphs(c, c->chunk);
+    return c->graphs_ell ? c->graphs_ell : c->graphs;
 }
 
 // Mixed precision: FP64 outer residual, scaling, refinement update and final
@@ -1028,6 +1041,8 @@ struct TuneResult {
     int npl, bs, G;
     double iter_us, spmv_us;
     int spmv_npl, spmv_bs, spmv_G;
+    // What other kernels take, 0 where they were not timed (tune_kernels).
+    double chip_us, ell_us, ell_spmv_us;
 };
 static std::mutex g_tune_mutex;
 static std::map<TuneKey, TuneResult> g_tune_cache;
@@ -1152,7 +1167,78 @@ static void autotune(cg_ctx* c)
     JPCG_HIP(hipFree(yb));
     std::lock_guard<std::mutex> lock(g_tune_mutex);
     g_tune_cache[key] = TuneResult{c->npl,          c->bs,          c->grid,     c->tuned_iter_us, c->tuned_spmv_us,
-                                   c->spmv->npl, c->spmv->bs, c->spmv->G};
+                                   c->spmv->npl, c->spmv->bs, c->spmv->G, 0.0, 0.0, 0.0};
+}
+
+// With autotuning: the on-chip solver and the slices against the tile shapes
+// chosen, in the same solves and products; what is slower is not used.
+static void tune_kernels(cg_ctx* c)
+{
+    const TuneKey key = tune_key(c);
+    TuneResult r;
+    {
+        std::lock_guard<std::mutex> lock(g_tune_mutex);
+        r = g_tune_cache[key];
+    }
+    const bool chip = c->resident && r.chip_us == 0.0, ell = c->ell && !c->resident && r.ell_us == 0.0;
+    const bool spmv = spmv_over_slices(c) && r.ell_spmv_us == 0.0;
+    if (chip || ell || spmv) {
+        double *xb = nullptr, *yb = nullptr;
+        hipEvent_t e0 = nullptr, e1 = nullptr;
+        auto done = [&] {
+            if (xb) (void)hipFree(xb);
+            if (yb) (void)hipFree(yb);
+            if (e0) (void)hipEventDestroy(e0);
+            if (e1) (void)hipEventDestroy(e1);
+        };
+        try {
+            JPCG_HIP(hipMalloc(&xb, sizeof(double) * c->n));
+            JPCG_HIP(hipMalloc(&yb, sizeof(double) * c->n));
+            std::vector<double> ones(c->n, 1.0);
+            JPCG_HIP(hipMemcpyAsync(yb, ones.data(), sizeof(double) * c->n, hipMemcpyHostToDevice, c->stream));
+            JPCG_HIP(hipEventCreate(&e0));
+            JPCG_HIP(hipEventCreate(&e1));
+            auto us = [&](int reps, auto run) {
+                float ms = 0.f;
+                JPCG_HIP(hipMemsetAsync(xb, 0, sizeof(double) * c->n, c->stream));
+                run();  // warm
+                JPCG_HIP(hipEventRecord(e0, c->stream));
+                for (int k = 0; k < reps; ++k) run();
+                JPCG_HIP(hipEventRecord(e1, c->stream));
+                JPCG_HIP(hipEventSynchronize(e1));
+                JPCG_HIP(hipEventElapsedTime(&ms, e0, e1));
+                return ms * 1e3 / reps;
+            };
+            const int iters = std::max(16, std::min(64, c->n));  // as in autotune
+            if (chip) {
+                RsOut o;
+                bool ran = true;
+                const double t = us(1, [&] {
+                    ran = ran && run_resident(c, c->resident, c->form == CG_FORM_SINGLE_REDUCTION ? RS_SINGLE : RS_STANDARD,
+                                              yb, xb, 0.0, iters, 0.0, nullptr, o);
+                });
+                if (ran) r.chip_us = t / iters;
+            }
+            if (ell && solve_graphs(c)->ell)
+                r.ell_us = us(1, [&] { run_solve(c, solve_graphs(c), yb, xb, 0.0, iters, nullptr); }) / iters;
+            if (spmv) r.ell_spmv_us = us(20, [&] { launch_spmv(c, yb, xb); });
+            done();
+        } catch (...) {
+            done();
+            throw;
+        }
+        std::lock_guard<std::mutex> lock(g_tune_mutex);
+        g_tune_cache[key] = r;
+    }
+    if (c->resident && r.chip_us > r.iter_us) {
+        destroy_resident(c->resident);
+        c->resident = nullptr;
+    }
+    c->ell_solves = !(r.ell_us > r.iter_us);
+    c->ell_spmv = !(r.ell_spmv_us > r.spmv_us);
+    if (c->resident) c->tuned_iter_us = r.chip_us;
+    else if (c->ell && c->ell_solves) c->tuned_iter_us = r.ell_us;
+    if (spmv_over_slices(c)) c->tuned_spmv_us = r.ell_spmv_us;
 }
 
 static void free_ctx(cg_ctx* c)
@@ -1340,6 +1426,7 @@ int cg_create(const cg_csr* A, const cg_opts* opts, void* hip_stream, cg_ctx** o
         // runs over them where the system is solved on chip and is small.
         if ((!c->resident || c->n >= kEllSpmvRows) && !c->opts.nnz_per_lane && !c->opts.block_size && !c->opts.blocks_per_cu && !c->opts.col_bits)
             c->ell = make_ell(c);
+        if (c->opts.autotune) tune_kernels(c);
         // The mixed form needs the standard FP64 graphs (outer residual) and
         // FP32 standard graphs (inner solve) with the same tile shape.
         if (c->opts.fp32_copy) {
@@ -1387,14 +1474,7 @@ int cg_solve(cg_ctx* c, const double* b, double* x, double tol, int32_t maxit, c
         }
         JPCG_HIP(hipEventRecord(c->ev0, c->stream));
         const SolveResult st = run_any(c, c->form == CG_FORM_SINGLE_REDUCTION ? RS_SINGLE : RS_STANDARD, b, x, tol,
-                                       maxit, 0.0, hist, [&] {
-                                           if (!c->ell) return c->graphs;
-                                           if (!c->graphs_ell)
-                                               c->graphs_ell = c->form == CG_FORM_STANDARD
-                                                                   ? make_ell_graphs(c, c->chunk, false, 0.0)
-                                                                   : make_ell_sr_graphs(c, c->chunk);
-                                           return c->graphs_ell ? c->graphs_ell : c->graphs;
-                                       });
+                                       maxit, 0.0, hist, [&] { return solve_graphs(c); });
         JPCG_HIP(hipEventRecord(c->ev1, c->stream));
         JPCG_HIP(hipEventSynchronize(c->ev1));
         float ms = 0.f;
@@ -1460,7 +1540,7 @@ int cg_solve_mixed_matrix(cg_ctx* c, const double* b, double* x, double tol, int
     if (drop == 0.0) drop = 1e-2;
     try {
         auto graphs = [&] {
-            if (c->ell) {
+            if (c->ell && c->ell_solves) {
                 if (c->graphs_ell32 && c->graphs_ell32->eargs.drop2 != drop * drop) {
                     destroy_graphs(c->graphs_ell32);
                     c->graphs_ell32 = nullptr;
@@ -1544,7 +1624,11 @@ int cg_get_config(cg_ctx* c, cg_config* cfg)
     cfg->spmv_us = c->tuned_spmv_us;
     cfg->iter_us = c->tuned_iter_us;
     cfg->spmm_blocks_per_cu = c->spmm_wpc;
-    cfg->spmm_pad = 0;
+    const int solves = c->solved >= 0 ? c->solved
+                       : c->resident  ? CG_KERNELS_ON_CHIP
+                       : c->ell && c->ell_solves ? CG_KERNELS_SLICES
+                                                 : CG_KERNELS_TILES;
+    cfg->kernels = solves | (spmv_over_slices(c) ? CG_KERNELS_SLICES : CG_KERNELS_TILES) << 8;
     cfg->spmm_us = c->tuned_spmm_us;
     return 0;
 }

@@ -324,4 +324,4 @@ extern "C" void jpcg_test_on_chip(long long wait_limit, int absent, int quit)
 
 extern "C" void jpcg_test_no_memory(int on) { jpcg::test_hooks().no_memory = on != 0; }
 
-extern "C" int jpcg_test_solved_on_chip(const cg_ctx* c) { return c->solved_on_chip; }
+extern "C" int jpcg_test_solved_on_chip(const cg_ctx* c) { return c->solved < 0 ? -1 : c->solved == CG_KERNELS_ON_CHIP; }
