@@ -287,8 +287,8 @@ bool run_resident(cg_ctx* c, cg_resident* r, int form, const double* b, double* 
     s.b = b;
     s.x = x;
     s.hist = hist;
-    RsRun run{tol, drop * drop, maxit, -1, -1, r->abort, &r->out[1].stop, c->limit_ticks / 80, c->limit_ticks};
-    test_hooks().apply(run);
+    RsRun run{tol, drop * drop, maxit, r->abort, &r->out[1].stop, c->limit_ticks / 80, c->limit_ticks};
+    if (test_hooks().wait_limit >= 0) run.limit_first = run.limit = test_hooks().wait_limit;
     const void* fn = rs_kernel(form, r->K, r->bs);
     const size_t lds = rs_lds(form, r->K, r->bs, r->rpw, r->halo, s.lds_slots);
     if (lds > kRsMaxLds || !r->retry.now()) return false;
@@ -300,8 +300,10 @@ bool run_resident(cg_ctx* c, cg_resident* r, int form, const double* b, double* 
     r->out->stop = RS_ABORTED;
     *run.given_up = 0;
     launch_rs_clear(st, r->words, r->nwords, x, r->x0, c->n);
-    JPCG_HIP(hipLaunchKernel(fn, dim3(kRsXcds * r->sys.members), dim3(r->bs), args, lds, st));
+    const int members = std::max(1, r->sys.members - test_hooks().absent);
+    JPCG_HIP(hipLaunchKernel(fn, dim3(kRsXcds * members), dim3(r->bs), args, lds, st));
     JPCG_HIP(hipStreamSynchronize(st));
+    if (test_hooks().given_up) *run.given_up = 1;
     const bool ok = !*run.given_up && r->out->stop != RS_ABORTED;
     r->retry.done(ok);
     if (!ok) {
@@ -314,12 +316,12 @@ bool run_resident(cg_ctx* c, cg_resident* r, int form, const double* b, double* 
 
 }  // namespace jpcg
 
-extern "C" void jpcg_test_on_chip(long long wait_limit, int absent, int quit)
+extern "C" void jpcg_test_on_chip(long long wait_limit, int absent, int given_up)
 {
     jpcg::TestHooks& h = jpcg::test_hooks();
     h.wait_limit = wait_limit;
     h.absent = absent;
-    h.quit = quit;
+    h.given_up = given_up != 0;
 }
 
 extern "C" void jpcg_test_no_memory(int on) { jpcg::test_hooks().no_memory = on != 0; }

@@ -118,7 +118,6 @@ struct RsSys {
 struct RsRun {
     double tol, drop2;  // drop2 > 0: the FP32-matrix form's reliable updates (see CgArgsT)
     int maxit;
-    int absent, quit;   // tests: this member of the team is not there, or gives up when the solve ends; else -1
     unsigned* abort;    // raised for the other workgroups
     int* given_up;      // and for the host (pinned)
     // Bounds of a wait, device wall clock ticks: until a solve's first round has
@@ -356,7 +355,6 @@ struct RsTeam {
     // First round: do the group's workgroups sit on one XCD?
     __device__ __forceinline__ bool start()
     {
-        if (L == run.absent) return false;
         if (s.groups * s.members == 1) return true;
         unsigned xcc;
         asm volatile("s_getreg_b32 %0, hwreg(HW_REG_XCC_ID)" : "=s"(xcc));
@@ -546,10 +544,6 @@ struct RsTeam {
 
     __device__ __forceinline__ void finish(int stop, int iters, int repl, double nb, double rr, double rrt)
     {
-        if (L == run.quit) {
-            if (tid == 0) rs_give_up(run);
-            return;
-        }
         if (has() && stop != STOP_CONV0) s.x[row] = stop == STOP_ZERO_RHS ? 0.0 : xo;
         if (tid == 0 && L == 0) *s.out = RsOut{stop, iters, repl, 0, nb, rr, rrt};
     }

@@ -374,7 +374,7 @@ bool run_batch_resident(cg_batch_resident* r, int device, hipStream_t st, const 
     // gate waits only as long as a launch does.
     a.run.limit = limit;
     a.gate_limit = limit / 160;
-    test_hooks().apply(a.run);
+    if (test_hooks().wait_limit >= 0) a.run.limit = test_hooks().wait_limit;
     const long long iterations = maxit > 0 ? (long long)maxit * r->nsys : r->rows;
     a.run.limit_first = a.run.limit + iterations * (limit / 80000);
     std::lock_guard<std::mutex> lock(resident_mutex(device));
@@ -384,6 +384,7 @@ bool run_batch_resident(cg_batch_resident* r, int device, hipStream_t st, const 
     void* args[] = {&a};
     JPCG_HIP(hipLaunchKernel(rs_batch_kernel(r->K, r->bs, r->nh), dim3(r->grid), dim3(r->bs), args, r->lds, st));
     JPCG_HIP(hipStreamSynchronize(st));
+    if (test_hooks().given_up) *a.run.given_up = 1;
     out = r->out;
     bool ok = *a.run.given_up == 0;
     for (int s = 0; s < r->nsys; ++s) ok = ok && out[s].stop != RS_ABORTED;

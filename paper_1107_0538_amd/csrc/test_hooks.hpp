@@ -8,16 +8,9 @@ namespace jpcg {
 
 struct TestHooks {
     long long wait_limit = -1;  // device ticks that a workgroup waits; < 0: as ever
-    int absent = -1;            // this member of every team leaves at once, as if it had not come
-    int quit = -1;              // this member of every team gives up at the end of the solve
+    int absent = 0;             // members of every group that a solve is launched without
+    bool given_up = false;      // a workgroup gave up as the others finished
     bool no_memory = false;     // there is no memory for on-chip solvers
-
-    void apply(RsRun& run) const
-    {
-        if (wait_limit >= 0) run.limit_first = run.limit = wait_limit;
-        run.absent = absent;
-        run.quit = quit;
-    }
 };
 
 TestHooks& test_hooks();
@@ -26,7 +19,7 @@ TestHooks& test_hooks();
 
 extern "C" {
 // For the calling thread, until the next call.
-void jpcg_test_on_chip(long long wait_limit, int absent, int quit);
+void jpcg_test_on_chip(long long wait_limit, int absent, int given_up);
 void jpcg_test_no_memory(int on);
 // Whether the last solve's result came from the chip (-1: not solved yet).
 int jpcg_test_solved_on_chip(const cg_ctx* c);

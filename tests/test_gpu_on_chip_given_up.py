@@ -5,8 +5,8 @@ have seen and written by then, the host takes nothing of such a launch: x goes
 back to what the caller passed and the general kernels solve the system, so
 the result is bitwise that of a context made for them.  A workgroup that is
 not there keeps the others waiting for as long as they may (a millisecond
-here); one that leaves at the very end is one whose last look came before its
-partners' words, which the partners have seen.
+here); one that gives up as the others finish, its last look having come before
+words that they have seen, tells the host alone.
 """
 import ctypes
 
@@ -29,13 +29,13 @@ def _t(a, dev):
 
 @pytest.fixture
 def on_chip(cuda):
-    """on_chip(wait_limit, absent, quit) sets the conditions for this thread's calls (-1: as ever)."""
+    """on_chip(wait_limit, absent, given_up) sets the conditions for this thread's calls (-1, 0, 0: as ever)."""
     from paper_1107_0538_amd import capi
 
     f = capi.load().jpcg_test_on_chip
     f.argtypes, f.restype = [ctypes.c_longlong, ctypes.c_int, ctypes.c_int], None
     yield f
-    f(-1, -1, -1)
+    f(-1, 0, 0)
 
 
 def solved_on_chip(s):
@@ -55,8 +55,7 @@ def batch_solved_on_chip(bt):
 
 
 MS = 100000  # device ticks
-HOW = {"first absent": (MS, 0, -1), "third absent": (MS, 2, -1), "first leaves": (-1, -1, 0),
-       "third leaves": (-1, -1, 2), "nobody": (-1, 10000, 10000)}
+HOW = {"one absent": (MS, 1, 0), "one gave up at the end": (-1, 0, 1), "nobody": (-1, 0, 0)}
 
 
 @pytest.mark.parametrize("how", list(HOW))
@@ -81,13 +80,13 @@ def test_given_up_solve_is_done_again(cuda, on_chip, n, offsets, form, how):
     assert solved_on_chip(s) == 1
     on_chip(*HOW[how])
     x, info = solve(s)
-    expected = how == "nobody" or (n == 60 and "third" in how)  # a member that there is not
+    expected = how == "nobody" or (n == 60 and how == "one absent")  # alone, and there
     assert solved_on_chip(s) == int(expected)
     if expected:
         assert (x == alone).all()
     else:
         assert (x == ref).all() and (info["iters"], info["status"]) == (iref["iters"], iref["status"])
-    on_chip(-1, -1, -1)
+    on_chip(-1, 0, 0)
     x, _ = solve(Solver(a, **kw))
     assert (x == alone).all()
 
@@ -106,12 +105,12 @@ def test_given_up_batch_is_done_again(cuda, on_chip, how):
     assert batch_solved_on_chip(bt) == 1
     on_chip(*HOW[how])
     x, info = bt.solve(b, x0=x0)
-    assert batch_solved_on_chip(bt) == int(how == "nobody")
-    if how == "nobody":
+    assert batch_solved_on_chip(bt) == int(how != "one gave up at the end")
+    if how != "one gave up at the end":  # a batch is launched whole
         assert (x == alone).all()
     else:
         assert (x == ref).all() and [i["iters"] for i in info] == [i["iters"] for i in iref]
-    on_chip(-1, -1, -1)
+    on_chip(-1, 0, 0)
     x, _ = Batch(mats).solve(b, x0=x0)
     assert (x == alone).all()
 
@@ -132,7 +131,7 @@ def test_batch_waits_for_earlier_systems(cuda, on_chip):
     bt = Batch(mats)
     alone, ialone = bt.solve(b)
     assert batch_solved_on_chip(bt) == 1
-    on_chip(MS // 5, -1, -1)
+    on_chip(MS // 5, 0, 0)
     x, info = bt.solve(b)
     assert batch_solved_on_chip(bt) == 1
     assert (x == alone).all() and [i["iters"] for i in info] == [i["iters"] for i in ialone]
@@ -210,14 +209,14 @@ def test_given_up_launches_are_not_tried_at_once_again(cuda, on_chip, batch):
         return there(s)
 
     assert [solve(), solve()] == [1, 1]
-    leaves = (-1, -1, 1)
+    leaves = (-1, 0, 1)
     on_chip(*leaves)
     assert solve() == 0
-    on_chip(-1, -1, -1)
+    on_chip(-1, 0, 0)
     assert [solve(), solve(), solve()] == [0, 1, 1]
     on_chip(*leaves)
     assert [solve(), solve(), solve()] == [0, 0, 0]  # the third is a try
-    on_chip(-1, -1, -1)
+    on_chip(-1, 0, 0)
     assert [solve(), solve(), solve()] == [0, 0, 1]
 
 
