@@ -52,9 +52,43 @@ def solve_bytes(n, nnz, iters, checks, form="standard", vb=8, ib=4):
     return setup + iters * iter_bytes(n, nnz, form, vb, ib) + checks * (matrix + 3 * vb * n)
 
 
-# Systems up to this size are solved in one kernel that reads the matrix once
-# (cg_solve's rule on sizes; the workload's rows have 27 entries).
-ON_CHIP_ROWS = 262144
+# What cg_config's `kernels` says of the last solve (its low byte) and of the product.
+TILES, SLICES, ON_CHIP = 0, 1, 2
+SOLVE_KERNELS = {
+    (TILES, "standard"): "k_direction + k_update (one CG iteration)",
+    (TILES, "single"): "k_sr_iter (one CG iteration)",
+    (SLICES, "standard"): "k_ell_direction + k_ell_product + k_ell_update (one CG iteration)",
+    (SLICES, "single"): "k_ell_sr_update + k_ell_sr_product (one CG iteration)",
+    (ON_CHIP, "standard"): "k_rs_solve (the whole solve)",
+    (ON_CHIP, "single"): "k_rs_solve (the whole solve)",
+}
+SPMV_KERNELS = {TILES: "k_spmv (tiles of rows)", SLICES: "k_ell_spmv (slices of 64 rows)"}
+
+# Bytes that one launch (on chip) or one iteration moves between the L2s and the
+# last-level cache or memory, from the counters in profiles/: (kernels, form, grid edge).
+TRAFFIC_FILE = "profiles/workloads_hbm_counters.txt"
+TRAFFIC = {
+    (ON_CHIP, "standard", 51): 833.45e6,
+    (ON_CHIP, "single", 51): 797.23e6,
+    (SLICES, "standard", 128): 779.26e6,
+}
+SPMV_TRAFFIC = {(SLICES, 51): 38.73e6, (SLICES, 128): 608.07e6}
+
+
+def solve_kernels(launch):
+    return launch["kernels"] & 0xff
+
+
+def spmv_kernels(launch):
+    return launch["kernels"] >> 8
+
+
+def traffic_of(key, table):
+    """The `traffic` fields for one entry of the tables above, or why there is none."""
+    if key in table:
+        return {"traffic": table[key], "traffic_source": f"{TRAFFIC_FILE} (FETCH_SIZE and WRITE_SIZE, scaled; "
+                                                         "recorded there, not in this run)"}
+    return {"traffic": None, "traffic_source": "no counters recorded for these kernels at this size"}
 
 
 def hbm_probe(dev, stream, mib=512, reps=20):
@@ -98,29 +132,30 @@ def roofline(form, n, nnz, run):
     and is bound by the latency of its iterations' exchanges: the unit is the
     whole solve, `achieved` what it has to move over its event-timed device
     time, and `csr_equivalent_gbs` what a solver that streams the CSR bytes in
-    every iteration would have to reach.  Larger systems stream the matrix over
-    slices of 64 rows, the standard form in three kernels an iteration and the
-    single-reduction form in two, launched in hipGraph chunks: the unit is one
-    iteration, its duration the device time over the iteration count (setup
-    and the final check are two products in 410 iterations).
+    every iteration would have to reach.  Other systems stream the matrix, over
+    slices of 64 rows or by tiles, in kernels launched in hipGraph chunks: the
+    unit is one iteration, its duration the device time over the iteration
+    count (setup and the final check are two products in 410 iterations).
+    Which kernels ran is what the context says (run["launch"]).
     """
     per_iter_s = run["device_s"] / max(run["iters"], 1)
     ib = iter_bytes(n, nnz, form)
-    if n <= ON_CHIP_ROWS:
-        kernel, bound = "k_rs_solve (the whole solve)", "latency"
+    kernels = solve_kernels(run["launch"])
+    kernel = SOLVE_KERNELS[kernels, form]
+    if kernels == ON_CHIP:
+        bound = "latency"
         nbytes, seconds = 12 * nnz + 4 * (n + 1) + 32 * n, run["device_s"]  # matrix, b, x0, dinv read, x written
         extra = {"csr_equivalent_gbs": ib / per_iter_s / 1e9, "iteration_s": per_iter_s}
     else:
-        kernel = "k_ell_sr_update + k_ell_sr_product" if form == "single" else \
-            "k_ell_direction + k_ell_product + k_ell_update"
-        kernel, bound, nbytes, seconds = kernel + " (one CG iteration)", "hbm", ib, per_iter_s
+        bound, nbytes, seconds = "hbm", ib, per_iter_s
         # The stored format's bytes: 16-bit column offsets save 2 per nonzero, and
-        # the single-reduction form stores u and reads u, p and w again.
-        fb = ib - 2 * nnz + (24 * n if form == "single" else 0)
+        # over slices the single-reduction form stores u and reads u, p and w again.
+        fb = ib - (2 * nnz if run["launch"]["col_bits"] == 16 else 0)
+        fb += 24 * n if kernels == SLICES and form == "single" else 0
         extra = {"format_bytes_per_launch": fb, "format_frac": fb / per_iter_s / 1e9 / HBM_PEAK_GBS}
     return {
         "kernel": kernel, "bound": bound, "achieved": nbytes / seconds / 1e9, "peak": HBM_PEAK_GBS, "unit": "GB/s",
-        "frac": nbytes / seconds / 1e9 / HBM_PEAK_GBS, "traffic": None, "traffic_source": "not measured",
+        "frac": nbytes / seconds / 1e9 / HBM_PEAK_GBS, **traffic_of((kernels, form, round(n ** (1 / 3))), TRAFFIC),
         "bytes_per_launch": nbytes, "launch_s": seconds, **extra,
     }
 
@@ -204,7 +239,6 @@ def bench_hbm128(args, dev, stream):
     a, b = system(128)
     n, nnz = a.n, a.nnz
     s = Solver(a)
-    cfg = s.config()
     warm, cold = spmv_warm_cold(s, n, dev, stream, reps=50, cold_reps=10)
     sb = spmv_bytes(n, nnz)
     bt = torch.as_tensor(b, device=dev)
@@ -217,14 +251,18 @@ def bench_hbm128(args, dev, stream):
     it = infos[-1]
     assert all(i["status"] == 0 for i in infos), it
     per_iter = statistics.mean(i["seconds"] for i in infos) / it["iters"]
+    cfg = s.config()
+    assert solve_kernels(cfg) != ON_CHIP, cfg
     ib = iter_bytes(n, nnz, "standard")
     out = {
         "workload": f"q1hex 128^3 sigma+mass, N={n}, nnz={nnz}, FP64 Jacobi-PCG standard form, tol 1e-10",
-        "kernel": "k_ell_direction + k_ell_product + k_ell_update (one CG iteration)", "bound": "hbm",
+        "kernel": SOLVE_KERNELS[solve_kernels(cfg), "standard"], "bound": "hbm",
         "achieved": ib / per_iter / 1e9, "peak": HBM_PEAK_GBS, "unit": "GB/s",
         "frac": ib / per_iter / 1e9 / HBM_PEAK_GBS, "bytes_per_launch": ib, "launch_s": per_iter,
+        **traffic_of((solve_kernels(cfg), "standard", 128), TRAFFIC),
         "iters": it["iters"], "relres_true": it["relres_true"],
-        "spmv": {"kernel": "k_ell_spmv (slices of 64 rows)", "bytes": sb,
+        "spmv": {"kernel": SPMV_KERNELS[spmv_kernels(cfg)], "bytes": sb,
+                 **traffic_of((spmv_kernels(cfg), 128), SPMV_TRAFFIC),
                  "warm_us": warm * 1e6, "warm_gbs": sb / warm / 1e9, "warm_frac": sb / warm / 1e9 / HBM_PEAK_GBS,
                  "cold_us": cold * 1e6, "cold_gbs": sb / cold / 1e9, "cold_frac": sb / cold / 1e9 / HBM_PEAK_GBS},
     }
@@ -714,13 +752,14 @@ def main():
             "us": spmv_us, "gbs": sb / spmv_us / 1e3, "frac_hbm_peak": sb / spmv_us / 1e3 / HBM_PEAK_GBS,
             "cold_us_median": cold_us, "cold_gbs": sb / cold_us / 1e3,
             "bytes": sb, "format_bytes": sb - (2 * nnz if cfg["col_bits"] == 16 else 0),
-            "kernel": "k_ell_spmv (slices of 64 rows)",
+            "kernel": SPMV_KERNELS[spmv_kernels(cfg)],
+            **traffic_of((spmv_kernels(cfg), args.n), SPMV_TRAFFIC),
         },
         "roofline": dict(roofline(best, n, nnz, r), achievable=probe["gbs"],
                          frac_of_achievable=roofline(best, n, nnz, r)["achieved"] / probe["gbs"],
                          cache_resident=(f"the {args.n}^3 system stays in the compute units' registers for the "
                                          "whole solve; roofline_128 is the HBM-bound figure")
-                         if n <= ON_CHIP_ROWS else None),
+                         if solve_kernels(r["launch"]) == ON_CHIP else None),
         "hbm_probe": probe,
         "paper_context": {"opencl_1gpu_tesla_t10_s": 0.659, "matlab_core2duo_s": 3.17,
                           "note": "different (unavailable) matrix and hardware; context only"},
