@@ -164,13 +164,16 @@ int cg_create(const cg_csr *A, const cg_opts *opts, void *hip_stream, cg_ctx **o
  * gives x = 0 and 0 iterations.  Every scalar stays on the device.  A system of
  * at most 262144 rows of at most 28 nonzeros, whose runs of rows (a run per
  * compute unit) refer to few other rows (at most 768, 1728 or 2880 from runs of
- * up to 256, 640 or 1024), created without a launch shape in its options, is solved by one kernel that holds the matrix in registers (such
- * solves on one device, and batched ones, wait for each other); otherwise
- * iterations run as kernels launched in hipGraph chunks, over a second copy of
- * the matrix in slices of 64 rows where its rows are of about equal length (at
- * most 64), no launch shape or column width was given and there is memory for
- * it.  The call synchronises
- * the context's stream.
+ * up to 256, 640 or 1024), created without a launch shape in its options, is
+ * solved by one kernel that holds the matrix in registers (such solves on one
+ * device, and batched ones, wait for each other).  Otherwise, and where that
+ * kernel's workgroups did not all come to run together (the solve then starts
+ * again from the caller's x, and a number of later ones do without), iterations
+ * run as kernels launched in hipGraph chunks, over a second copy of the matrix in
+ * slices of 64 rows where its rows are of about equal length (at most 64), no
+ * launch shape or column width was given and there is memory for it.  A context
+ * created with autotune leaves out what it timed as slower; cg_get_config says
+ * which kernels ran.  The call synchronises the context's stream.
  * info may be NULL.  Returns the status (>= 0) or an API error (< 0).
  */
 int cg_solve(cg_ctx *ctx, const double *b, double *x, double tol, int32_t maxit, cg_info *info);
@@ -301,9 +304,9 @@ int cg_solve_block(cg_ctx *ctx, const double *B, double *X, int32_t s, double to
  * workgroups per compute unit (0 = the occupancy limit, the most that can be
  * co-resident; larger values are clamped to it); opts->col_bits as for
  * cg_create (the 16-bit form is used only if it fits every system's tiles).
- * Teams wait for each
- * other at bounded barriers, so a device shared with other work while the
- * batch runs can end the solve with CG_ETIMEOUT.  At most one system per
+ * Teams wait for each other at bounded barriers, so a device shared with other
+ * work while the batch runs can end the general path with CG_ETIMEOUT; a solve in
+ * registers that waits in vain starts again there, from the caller's x.  At most one system per
  * co-resident workgroup slot (else CG_EINVAL).
  * Returns 0, CG_EINVAL, CG_EDIAG (some system lacks a positive diagonal),
  * CG_ENOMEM or CG_EHIP.

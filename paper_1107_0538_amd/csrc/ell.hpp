@@ -14,14 +14,15 @@
 // independent of the others, and neighbouring rows gather neighbouring
 // columns, so a gather touches 4-5 lines where the tile walk of tiles.hpp
 // (lanes along a row) touches 20 or more, and the row sums need no LDS.
-// Product at 128^3 (710.9 MB in CSR, 583 MB here): 149 us by tiles, 98 here; at
-// 96^3, which the last-level cache holds, 50 and 37; at 51^3 9.4 and 8.7, a
-// launch included.
+// Product at 128^3 (710.9 MB in CSR, 602 MB here): 149 us by tiles, 108 here again
+// and again, 112 with three matrices in turn; at 51^3 9.4 and 8.7, a launch
+// included.
 //
 // A matrix larger than the 256 MB last-level cache is read with non-temporal
 // loads except for a fixed share of its slices, spread evenly, which then stay
-// in the cache from one product to the next: at 128^3 122 us with plain loads
-// only, 112 with non-temporal ones only, 98 with 30 % of the slices kept.
+// in the cache from one product to the next: the product at 128^3 by itself 122 us
+// with plain loads only, 112 with non-temporal ones only, 98 with 170 MB (30 %) of
+// the slices kept; ell.hip says how much the solver and spmv keep.
 #pragma once
 
 #include "common.hpp"

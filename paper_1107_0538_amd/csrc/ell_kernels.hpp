@@ -12,8 +12,8 @@
 // and z = M^-1 r is formed where it is used: 12 vectors of N doubles move per
 // iteration besides the matrix.  Forming p inside the product's gathers as the
 // tile kernels do saves a launch but gathers two vectors: at 128^3 164 us per
-// iteration (146 of them the product) against 147 in three kernels (111 + 18 +
-// 14 and the gaps), and 196 by tiles; streaming FP32 values 111 against 177.
+// iteration (146 of them the product) against 141 in three kernels (109 + 18 +
+// 14), and 196 by tiles; streaming FP32 values 107 against 177.
 #pragma once
 
 #include "ell_host.hpp"

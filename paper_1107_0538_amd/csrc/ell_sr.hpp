@@ -9,8 +9,8 @@
 //
 // Forming u inside the gathers, as the one kernel over tiles does, fetches 32
 // bytes per entry; u stored once moves 14 vectors of N doubles an iteration
-// besides the matrix.  A solve at 66^3, 80^3, 96^3 and 118^3 takes 15.0, 24.9,
-// 48.0 and 112 ms, over tiles 17.6, 32.2, 70.0 and 155.
+// besides the matrix.  A solve at 66^3, 84^3, 96^3 and 118^3 takes 13.9, 27.9,
+// 46.1 and 110 ms, over tiles 17.6, 36.7, 70.0 and 155.
 #pragma once
 
 #include "ell_kernels.hpp"

@@ -387,14 +387,15 @@ static cg_graphs* make_graphs(cg_ctx* c, int form, bool fp32, int npl, int bs, i
 // The standard form over the context's slices; mat32 and drop as above.  The
 // product's partial sums are reduced by every workgroup of the update and its
 // sums by every workgroup of the next direction, so the grids are no larger
-// than they need be: at 128^3 1024 workgroups for the vectors 146.6 us per
-// iteration, 256 157; 8192 for the product 150.
+// than they need be: at 128^3, when an iteration took 147 us, 1024 workgroups
+// for the vectors took 146.6, 256 157; 8192 for the product 150.
 constexpr int kEllMaxGrid = 4096, kEllUpdateGrid = 1024;
 
 // Rows per workgroup of the elementwise kernels, whole passes of its threads,
 // and their grid: 65^3 14.51 ms a solve against 14.66 with the rows spread evenly
 // over the largest grid (a second pass for 13 rows), 84^3 31.9 and 32.2, 110^3
-// 78.8 and 79.4; 96^3 46.6 and 46.3.
+// 78.8 and 79.4; 96^3 46.6 and 46.3 (all with 2048 workgroups for the product at
+// most, of which ell_grid tells).
 static void ell_rows(int n, int grid, int& R, int& G)
 {
     R = ((n + grid - 1) / grid + kEllBS - 1) / kEllBS * kEllBS;
